@@ -511,7 +511,7 @@ __global__ __launch_bounds__(64 * NW) void k_fwd_raw_mfma(const T* __restrict__ 
             }
         }
     };
-    int64_t tile = (int64_t)blockIdx.x * NW + wave;
+    int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x;
     if (tile < n_tiles) load_raw(tile);
     for (; tile < n_tiles; tile += tstride) {
         {
@@ -733,6 +733,127 @@ __global__ __launch_bounds__(64 * NW) void k_fwd_raw_mfma_fixed(const T* __restr
     }
 }
 
+// The lane's record x (its four lane groups hold the same one) encoded into the
+// LDS row h0, a share of the features per group: groups 0..2 the frequency
+// encoding of position coordinate g (the same code for the three, features
+// 12g .. 12g + 11), group 3 the rest (36 .. 63).  valid = false: a row of zeros.
+template <typename T, int PRESET, int LAYOUT, int RW>
+__device__ inline void encode_shared(const float (&x)[RW], T* h0, int g, bool valid) {
+    float f[64];
+    if (g < 3) {
+        float xc[RW];
+        xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
+        encode_part<PRESET, LAYOUT, 0>(xc, f);
+        if (!valid) {
+            #pragma unroll
+            for (int k = 0; k < 12; ++k) f[k] = 0.0f;
+        }
+        #pragma unroll
+        for (int q = 0; q < 3; ++q) store4<T>(h0 + 12 * g + 4 * q, f + 4 * q);
+    } else {
+        encode_part<PRESET, LAYOUT, 3>(x, f);
+        encode_part<PRESET, LAYOUT, 4>(x, f);
+        if (!valid) {
+            #pragma unroll
+            for (int k = 36; k < 64; ++k) f[k] = 0.0f;
+        }
+        #pragma unroll
+        for (int q = 9; q < 16; ++q) store4<T>(h0 + 4 * q, f + 4 * q);
+    }
+}
+
+// Inference over few records (width 64, any depth): four waves share a 64-record
+// tile, 16 records (one operand column block) each, so a tile's chain of layers
+// is a quarter as long as in the kernels above and a small batch reaches four
+// times as many SIMDs.  RAWL >= 0: the source's rows are raw records, encoded by
+// the four lane groups together while the weight fragments are on their way to
+// LDS.  Every record sees the same products in the same order as above, so the
+// outputs are equal bit for bit.  Bound by latency: 1,000 records take 3.5 us
+// (7.0 us in 64-record tiles of one wave, a workgroup for each 12 of them), of
+// which an empty launch is about 2.7.
+template <typename T, int RAWL, int PRESET, typename Src>
+__global__ __launch_bounds__(256) void k_fwd_small(const T* __restrict__ ffr, int n_frags, Src src,
+                                                       int n_hidden, int fcol) {
+    using V = typename Vec8<T>::type;
+    constexpr int W = 64, KC = 2, NT = 256, ROW = 72;
+    constexpr int RW = RAWL == NRC_RAW16 ? 16 : 14;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    V* sfr = reinterpret_cast<V*>(smem_raw);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, ln = lane & 15;
+    T* h0 = reinterpret_cast<T*>(smem_raw + n_frags * 1024) + (wave * 16 + ln) * ROW;
+    const int64_t n_tiles = src.n_tiles();
+
+    float x[RW];
+    V nxt[KC];
+    auto load_in = [&](int64_t t) {          // rows past the end read the last row
+        const void* e;
+        int64_t base, cnt;
+        float* out;
+        src.locate(t, e, base, cnt, out);
+        int64_t row = base + 16 * wave + ln;
+        row = row < cnt ? row : cnt - 1;
+        if constexpr (RAWL >= 0) {
+            const float* s = reinterpret_cast<const float*>(e) + row * RW;
+            #pragma unroll
+            for (int q = 0; q < RW / 2; ++q) {
+                const float2 v = reinterpret_cast<const float2*>(s)[q];
+                x[2 * q] = v.x; x[2 * q + 1] = v.y;
+            }
+        } else {
+            #pragma unroll
+            for (int c = 0; c < KC; ++c)
+                nxt[c] = *reinterpret_cast<const V*>(reinterpret_cast<const T*>(e) + row * kEncWidth + 32 * c + 8 * g);
+        }
+    };
+    int64_t tile = blockIdx.x;
+    if (tile < n_tiles) load_in(tile);
+    // the fragments' first loads are in flight beside the first tile's encoding
+    constexpr int NL = 12;
+    const int total = n_frags * 64;
+    const V* gf = reinterpret_cast<const V*>(ffr);
+    V tmp[NL];
+    #pragma unroll
+    for (int u = 0; u < NL; ++u)
+        if (tid + u * NT < total) tmp[u] = gf[tid + u * NT];
+    if constexpr (RAWL >= 0) {
+        if (tile < n_tiles) encode_shared<T, PRESET, RAWL>(x, h0, g, true);
+    }
+    #pragma unroll
+    for (int u = 0; u < NL; ++u)
+        if (tid + u * NT < total) sfr[tid + u * NT] = tmp[u];
+    for (int i = tid + NL * NT; i < total; i += NT) sfr[i] = gf[i];
+    __syncthreads();
+
+    for (; tile < n_tiles; tile += gridDim.x) {
+        V b[1][KC];
+        if constexpr (RAWL >= 0) {
+            wave_lds_sync();
+            #pragma unroll
+            for (int c = 0; c < KC; ++c) b[0][c] = *reinterpret_cast<const V*>(h0 + 32 * c + 8 * g);
+            wave_lds_sync();
+        } else {
+            #pragma unroll
+            for (int c = 0; c < KC; ++c) b[0][c] = nxt[c];
+        }
+        const bool more = tile + gridDim.x < n_tiles;
+        if (more) load_in(tile + gridDim.x);
+        float r[1][3];
+        reflectance_operand(b[0][1], fcol, ln, r[0]);
+        f32x4 o[1];
+        mlp_tile<T, W, 1>(sfr, b, n_hidden, lane, o);
+        const void* e;
+        int64_t base, cnt;
+        float* out;
+        src.locate(tile, e, base, cnt, out);
+        store_rgb<1>(o, r, base + 16 * wave, cnt, g, ln, out);
+        if constexpr (RAWL >= 0) {
+            if (more) encode_shared<T, PRESET, RAWL>(x, h0, g, true);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Training: forward + loss gradient + data backward + per-tile weight gradient
 // ---------------------------------------------------------------------------
@@ -855,9 +976,6 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
             V pre[NPRE > 0 ? NPRE : 1];
             #pragma unroll
             for (int i = 0; i < NPRE; ++i) pre[i] = gf[(i % (2 * MB)) * 64 + (i < 2 * MB ? 0 : lo_f)];
-            // The four lane groups of a record share its encoding: groups 0..2
-            // the frequency encoding of position coordinate g (the same code
-            // for the three, features 12g ..12g + 11), group 3 the rest (36 ..63).
             float x[RW];
             if (valid) {
                 const float* rr = reinterpret_cast<const float*>(enc) + src * RW;
@@ -867,27 +985,7 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
                 #pragma unroll
                 for (int k = 0; k < RW; ++k) x[k] = 0.0f;
             }
-            float f[64];
-            if (g < 3) {
-                float xc[RW];
-                xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
-                encode_part<PRESET, RAWL, 0>(xc, f);
-                if (!valid) {
-                    #pragma unroll
-                    for (int k = 0; k < 12; ++k) f[k] = 0.0f;
-                }
-                #pragma unroll
-                for (int q = 0; q < 3; ++q) store4<T>(h0 + 12 * g + 4 * q, f + 4 * q);
-            } else {
-                encode_part<PRESET, RAWL, 3>(x, f);
-                encode_part<PRESET, RAWL, 4>(x, f);
-                if (!valid) {
-                    #pragma unroll
-                    for (int k = 36; k < 64; ++k) f[k] = 0.0f;
-                }
-                #pragma unroll
-                for (int q = 9; q < 16; ++q) store4<T>(h0 + 4 * q, f + 4 * q);
-            }
+            encode_shared<T, PRESET, RAWL>(x, h0, g, valid);
             wave_lds_sync();
             #pragma unroll
             for (int c = 0; c < 2; ++c) b[c] = *reinterpret_cast<const V*>(h0 + 32 * c + 8 * g);
@@ -1214,11 +1312,32 @@ inline int64_t resident_fwd_blocks(size_t lds) {
 // Waves per workgroup of k_fwd_mfma_fixed (one workgroup per CU).
 constexpr int kEncWaves = 12;
 
+// Batches of up to four 64-record tiles per CU (65,536 records) take
+// k_fwd_small.  Measured (FP16, 5 layers, raw records, us per launch, small
+// against the persistent kernels with a workgroup per tile): 1,000 records 3.5 /
+// 5.0, 16,384 3.7 / 5.4, 49,152 5.3 / 7.0, 70,000 6.4 / 7.1, 100,000 7.9 / 7.3;
+// encoded rows 49,152 5.0 / 5.6, 70,000 6.0 / 5.9; 8 layers, raw records, 65,536
+// 7.9 / 7.9.  Workgroups of 8 or 12 waves were no faster below the line.
+constexpr int kSmallTilesPerCu = 4;
+inline bool small_batch(int64_t tiles) { return tiles <= (int64_t)kSmallTilesPerCu * device_cu_count(); }
+
+template <typename T, int RAWL, int PRESET, typename Src>
+hipError_t fwd_small_launch(const Geo& d, const void* ffr, const Src& src, int64_t tiles, hipStream_t s) {
+    const size_t lds = (size_t)d.n_fwd_frags() * 1024 + (RAWL >= 0 ? (size_t)64 * 72 * sizeof(T) : 0);
+    const int64_t resident = resident_fwd_blocks(lds);
+    auto k = k_fwd_small<T, RAWL, PRESET, Src>;
+    // up to 64 KB (6 layers) need no permission, and the call costs the host 0.2 us
+    if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3((unsigned)(tiles < resident ? tiles : resident)), dim3(256), lds, s, (const T*)ffr,
+                       d.n_fwd_frags(), src, d.H, d.F);
+    return hipGetLastError();
+}
+
 template <typename T, typename Src>
 hipError_t fwd_fixed_launch(const void* ffr, const Src& src, int64_t tiles, int fcol, hipStream_t s) {
     constexpr int NW = kEncWaves;
-    int64_t blocks = (tiles + NW - 1) / NW;
-    if (blocks > device_cu_count()) blocks = device_cu_count();
+    // a workgroup per tile up to one per CU: the tiles spread over the chip
+    const int64_t blocks = tiles < device_cu_count() ? tiles : device_cu_count();
     hipLaunchKernelGGL((k_fwd_mfma_fixed<T, NW, Src>), dim3((unsigned)blocks), dim3(64 * NW), 0, s,
                        (const T*)ffr, src, fcol);
     return hipGetLastError();
@@ -1229,6 +1348,7 @@ hipError_t fwd_segs_dispatch(const Geo& d, const void* ffr, const SegList& segs,
     constexpr int COLS = 4;
     const int64_t tiles = segs.tile_end[segs.count - 1];
     if (tiles == 0) return hipSuccess;
+    if (W == 64 && small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncSegs{segs}, tiles, s);
     if (W == 64 && d.H == 5) return fwd_fixed_launch<T>(ffr, EncSegs{segs}, tiles, d.F, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 64 * 16;
     int64_t blocks = (tiles + 3) / 4;
@@ -1248,6 +1368,7 @@ hipError_t fwd_dispatch(const Geo& d, const void* ffr, const void* enc, int64_t 
     constexpr int COLS = 4;
     const int64_t tiles = (n + 16 * COLS - 1) / (16 * COLS);
     if (tiles == 0) return hipSuccess;
+    if (W == 64 && small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncBatch{enc, n, rgb}, tiles, s);
     if (W == 64 && d.H == 5) return fwd_fixed_launch<T>(ffr, EncBatch{enc, n, rgb}, tiles, d.F, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 64 * 16;
     int64_t blocks = (tiles + 3) / 4;
@@ -1273,9 +1394,9 @@ hipError_t fwd_raw_launch(const Geo& d, const void* ffr, const float* raw, int64
                           hipStream_t s, int max_blocks) {
     const int64_t tiles = (n + 63) / 64;
     if (tiles == 0) return hipSuccess;
+    if (small_batch(tiles)) return fwd_small_launch<T, LAYOUT, PRESET>(d, ffr, EncBatch{raw, n, rgb}, tiles, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 1024 + (size_t)NW * 64 * 72 * sizeof(T);
-    int64_t blocks = (tiles + NW - 1) / NW;
-    if (blocks > max_blocks) blocks = max_blocks;
+    const int64_t blocks = tiles < max_blocks ? tiles : max_blocks;
     auto k = k_fwd_raw_mfma<T, W, PRESET, LAYOUT, NW>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * NW), lds, s, (const T*)ffr, d.n_fwd_frags(), raw,
@@ -1291,8 +1412,8 @@ hipError_t fwd_raw_fixed_launch(const Geo& d, const void* ffr, const float* raw,
     constexpr int NW = kRawWaves;
     const int64_t tiles = (n + 63) / 64;
     if (tiles == 0) return hipSuccess;
-    int64_t blocks = (tiles + NW - 1) / NW;
-    if (blocks > max_blocks) blocks = max_blocks;
+    if (small_batch(tiles)) return fwd_small_launch<T, LAYOUT, PRESET>(d, ffr, EncBatch{raw, n, rgb}, tiles, s);
+    const int64_t blocks = tiles < max_blocks ? tiles : max_blocks;   // spread over the CUs
     hipLaunchKernelGGL((k_fwd_raw_mfma_fixed<T, PRESET, LAYOUT, 5, NW>), dim3((unsigned)blocks),
                        dim3(64 * NW), 0, s, (const T*)ffr, raw, n, rgb, d.F);
     return hipGetLastError();

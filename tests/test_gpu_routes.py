@@ -1,0 +1,54 @@
+"""Inference over few and over many records takes different kernels; a record's
+prediction must not depend on which.
+
+Every accumulator sees the same products in the same order in all of them, so
+the predictions of a batch and of its slices (of a few records, down to one) are
+equal bit for bit: no tolerance.  (The slices are copied out: device buffers are
+16-byte aligned.)
+"""
+import numpy as np
+import pytest
+import torch
+
+import synthdata as sd
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def N():
+    from paper_2106_12372_amd import nrc
+    return nrc
+
+
+# Records per 64-record tile and compute unit at which the kernels change.
+def _lines(cus):
+    return {("fp16", 64): 4 * 64 * cus, ("bf16", 64): 4 * 64 * cus, ("fp16", 128): 6 * 64 * cus,
+            ("bf16", 128): 6 * 64 * cus, ("fp32", 64): 24 * 64 * cus}
+
+
+SLICES = ((0, 1), (0, 63), (64, 1001), (5, 22))
+
+
+@pytest.mark.parametrize("prec,width,n_hidden", [("fp16", 64, 5), ("bf16", 64, 5), ("fp16", 64, 1), ("bf16", 64, 8),
+                                                 ("fp16", 128, 5), ("bf16", 128, 1), ("bf16", 128, 4),
+                                                 ("fp32", 64, 5), ("fp32", 64, 1), ("fp32", 64, 6)])
+@pytest.mark.parametrize("raw_form", [False, True])
+@pytest.mark.parametrize("past", [0, 1, 64 * 300 + 37])
+def test_batches_and_their_slices_agree(N, prec, width, n_hidden, raw_form, past):
+    if raw_form and width == 128:
+        pytest.skip("raw records feed the 64-wide network only")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = _lines(cus)[(prec, width)] + past
+    cfg = N.make_config(width=width, n_hidden=n_hidden, precision=prec, factorize=n_hidden % 2 == 1)
+    c = N.Cache(cfg)
+    c.set_weights(sd.glorot_weights(width, n_hidden, seed=3))
+    raw = torch.from_numpy(sd.raw_records(n, 40 + n_hidden)).cuda()
+    enc = N.nrc_encode(c, raw)
+    whole = N.nrc_forward_raw(c, raw) if raw_form else N.nrc_forward(c, enc)
+    assert bool(torch.isfinite(whole).all())
+    for lo, hi in SLICES + ((n - 1000, n), (n - 1, n)):
+        part = enc[lo:hi].clone()
+        assert torch.equal(N.nrc_forward(c, part), whole[lo:hi]), (lo, hi)
+        if width == 64:
+            assert torch.equal(N.nrc_forward_raw(c, raw[lo:hi].clone()), whole[lo:hi]), (lo, hi)
