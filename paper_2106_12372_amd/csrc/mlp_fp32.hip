@@ -161,13 +161,12 @@ __device__ inline void mlp_query_mfma(const f4* __restrict__ sw, int H, int lane
     }
 }
 
-// Inference: RAW = false reads 64 encoded features per query; RAW = true reads
-// raw records and encodes them in the lane (Sec. 3.6).  A wave takes 64
-// consecutive queries per tile; lanes past the end compute on the last query
-// and store nothing, so every lane joins every matrix instruction.
-template <bool RAW, int PRESET, int LAYOUT>
-__device__ inline void query_fp32(const float* __restrict__ w, const float* __restrict__ in, int64_t n,
-                                  float* __restrict__ rgb, int H, int fcol) {
+// Inference from many raw records, encoded in the lane (Sec. 3.6).  A wave
+// takes 64 consecutive queries per tile; lanes past the end compute on the last
+// query and store nothing, so every lane joins every matrix instruction.
+template <int PRESET, int LAYOUT>
+__device__ inline void query_tiles(const float* __restrict__ w, const float* __restrict__ raw, int64_t n,
+                                   float* __restrict__ rgb, int H, int fcol) {
     extern __shared__ f4 sw[];
     __shared__ int claimed;                 // tiles of the workgroup's share handed out so far
     constexpr int RW = LAYOUT == NRC_RAW14 ? 14 : 16;
@@ -192,23 +191,14 @@ __device__ inline void query_fp32(const float* __restrict__ w, const float* __re
         const bool valid = s < n;
         if (!valid) s = n - 1;
         float h[kW];
-        if (RAW) {
-            float x[RW];
-            const float2* src = reinterpret_cast<const float2*>(in + s * RW);
-            #pragma unroll
-            for (int q = 0; q < RW / 2; ++q) {
-                const float2 v = src[q];
-                x[2 * q] = v.x; x[2 * q + 1] = v.y;
-            }
-            encode_record<PRESET, LAYOUT>(x, h);
-        } else {
-            const float4* row = reinterpret_cast<const float4*>(in + s * kEncWidth);
-            #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const float4 v = row[q];
-                h[4 * q] = v.x; h[4 * q + 1] = v.y; h[4 * q + 2] = v.z; h[4 * q + 3] = v.w;
-            }
+        float x[RW];
+        const float2* src = reinterpret_cast<const float2*>(raw + s * RW);
+        #pragma unroll
+        for (int q = 0; q < RW / 2; ++q) {
+            const float2 v = src[q];
+            x[2 * q] = v.x; x[2 * q + 1] = v.y;
         }
+        encode_record<PRESET, LAYOUT>(x, h);
         float r[kNOut], y[kNOut];
         reflectance_row(h, fcol, r);
         mlp_query_mfma(sw, H, lane, wo, h, y);
@@ -216,18 +206,200 @@ __device__ inline void query_fp32(const float* __restrict__ w, const float* __re
     }
 }
 
-__global__ __launch_bounds__(64 * kQWaves) void k_fwd_fp32(const float* __restrict__ w,
-                                                          const float* __restrict__ enc, int64_t n,
-                                                          float* __restrict__ rgb, int n_hidden, int fcol) {
-    query_fp32<false, NRC_PRESET_CONFIG, NRC_RAW14>(w, enc, n, rgb, n_hidden, fcol);
-}
-
-// Inference from raw records with the encoding fused in.
 template <int PRESET, int LAYOUT>
 __global__ __launch_bounds__(64 * kQWaves) void k_fwd_raw_fp32(const float* __restrict__ w,
                                                               const float* __restrict__ raw, int64_t n,
                                                               float* __restrict__ rgb, int n_hidden, int fcol) {
-    query_fp32<true, PRESET, LAYOUT>(w, raw, n, rgb, n_hidden, fcol);
+    query_tiles<PRESET, LAYOUT>(w, raw, n, rgb, n_hidden, fcol);
+}
+
+// The lane's record x (its four lane groups hold the same one) encoded into the
+// LDS row h0, a share of the features per group: groups 0..2 the frequency
+// encoding of position coordinate g (the same code for the three, features
+// 12g .. 12g + 11), group 3 the rest (36 .. 63).  valid = false: a row of zeros.
+template <int PRESET, int LAYOUT, int RW>
+__device__ inline void encode_shared(const float (&x)[RW], float* h0, int g, bool valid) {
+    float f[64];
+    if (g < 3) {
+        float xc[RW];
+        xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
+        encode_part<PRESET, LAYOUT, 0>(xc, f);
+        if (!valid) {
+            #pragma unroll
+            for (int k = 0; k < 12; ++k) f[k] = 0.0f;
+        }
+        #pragma unroll
+        for (int q = 0; q < 3; ++q)
+            *reinterpret_cast<float4*>(h0 + 12 * g + 4 * q) =
+                make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
+    } else {
+        encode_part<PRESET, LAYOUT, 3>(x, f);
+        encode_part<PRESET, LAYOUT, 4>(x, f);
+        if (!valid) {
+            #pragma unroll
+            for (int k = 36; k < 64; ++k) f[k] = 0.0f;
+        }
+        #pragma unroll
+        for (int q = 9; q < 16; ++q)
+            *reinterpret_cast<float4*>(h0 + 4 * q) = make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
+    }
+}
+
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inference in units of 16 queries (one operand column) per wave: encoded rows
+// (RAW = false), or few raw records, encoded by the four lane groups together.
+// A unit keeps its wave for a quarter of a 64-query tile's 18 us, so the units
+// fill the SIMDs of a small batch and the last round of a large one.  A
+// column's products per layer and accumulator are those of mlp_query_mfma in
+// the same order, and the output layer's sums too, so the outputs are equal bit
+// for bit.  Bound by the FP32 matrix cores: each A fragment read from LDS
+// feeds 4 products instead of 16, a quarter of the LDS rate.  Encoded rows, us
+// before (64-query tiles) and now: 1,000 queries 43.6 / 10.2, 70,000 45.8 /
+// 30.0, 300,000 119 / 99, 2,073,600 638 / 628.
+template <bool RAW, int PRESET, int LAYOUT>
+__device__ inline void query_units(const float* __restrict__ w, const float* __restrict__ in, int64_t n,
+                                   float* __restrict__ rgb, int H, int fcol) {
+    extern __shared__ f4 sw[];
+    constexpr int RW = LAYOUT == NRC_RAW14 ? 14 : 16, NT = 64 * kQWaves;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, j = lane & 15;
+    float* h0 = reinterpret_cast<float*>(sw + 16 * H * 64) + (wave * 16 + j) * kLd;
+    // the workgroup owns a contiguous share of the 16-query units; its waves take
+    // one each, then claim the rest one at a time
+    __shared__ int claimed;
+    if (tid == 0) claimed = kQWaves;
+    const int64_t n_units = (n + 15) / 16;
+    const int64_t per = n_units / gridDim.x, extra = n_units % gridDim.x;
+    const int64_t u_begin = (int64_t)blockIdx.x * per + ((int64_t)blockIdx.x < extra ? blockIdx.x : extra);
+    const int64_t u_end = u_begin + per + ((int64_t)blockIdx.x < extra ? 1 : 0);
+    int64_t unit = u_begin + wave;
+    float x[RAW ? RW : 1];
+    float4 nxt[4];
+    auto row_of = [&](int64_t u) { return u * 16 + j; };
+    auto load_in = [&](int64_t t) {          // rows past the end read the last row
+        int64_t s = row_of(t);
+        s = s < n ? s : n - 1;
+        if constexpr (RAW) {
+            const float2* src = reinterpret_cast<const float2*>(in + s * RW);
+            #pragma unroll
+            for (int q = 0; q < RW / 2; ++q) {
+                const float2 v = src[q];
+                x[2 * q] = v.x; x[2 * q + 1] = v.y;
+            }
+        } else {
+            #pragma unroll
+            for (int b = 0; b < 4; ++b) nxt[b] = *reinterpret_cast<const float4*>(in + s * kEncWidth + 16 * b + 4 * g);
+        }
+    };
+    if (unit < u_end) load_in(unit);
+    // the weights' first loads are in flight beside the first unit's encoding
+    const int total = 16 * H * 64;
+    auto frag = [&](int idx) {
+        const int f = idx >> 6, ln = idx & 63;
+        const int l = f >> 4, ob = (f >> 2) & 3, obp = f & 3;
+        return *reinterpret_cast<const f4*>(w + l * kW * kW + (16 * ob + (ln & 15)) * kW + 16 * obp + 4 * (ln >> 4));
+    };
+    constexpr int NL = 10;
+    f4 tmp[NL];
+    #pragma unroll
+    for (int u = 0; u < NL; ++u)
+        if (tid + u * NT < total) tmp[u] = frag(tid + u * NT);
+    f4 wo[4];
+    load_out_weights(w, H, lane, wo);
+    if constexpr (RAW) {
+        if (unit < u_end) encode_shared<PRESET, LAYOUT>(x, h0, g, true);
+    }
+    #pragma unroll
+    for (int u = 0; u < NL; ++u)
+        if (tid + u * NT < total) sw[tid + u * NT] = tmp[u];
+    for (int i = tid + NL * NT; i < total; i += NT) sw[i] = frag(i);
+    __syncthreads();
+
+    for (int64_t after; unit < u_end; unit = after) {
+        int k = 0;
+        if (lane == 0) k = atomicAdd(&claimed, 1);
+        after = u_begin + __builtin_amdgcn_readfirstlane(k);
+        float act[16], r[kNOut] = {1.0f, 1.0f, 1.0f};
+        if constexpr (RAW) {
+            wave_lds_sync();
+            #pragma unroll
+            for (int b = 0; b < 4; ++b) nxt[b] = *reinterpret_cast<const float4*>(h0 + 16 * b + 4 * g);
+            if (fcol) {
+                #pragma unroll
+                for (int o = 0; o < kNOut; ++o) r[o] = h0[fcol + o] + h0[fcol + 3 + o];
+            }
+            wave_lds_sync();
+        } else if (fcol) {
+            int64_t s = row_of(unit);
+            s = s < n ? s : n - 1;
+            const float* er = in + s * kEncWidth + fcol;
+            #pragma unroll
+            for (int o = 0; o < kNOut; ++o) r[o] = er[o] + er[3 + o];
+        }
+        #pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            act[4 * b] = nxt[b].x; act[4 * b + 1] = nxt[b].y; act[4 * b + 2] = nxt[b].z; act[4 * b + 3] = nxt[b].w;
+        }
+        const bool more = after < u_end;
+        if (more) load_in(after);
+        for (int l = 0; l < H; ++l) {
+            const f4* fl = sw + l * 16 * 64 + lane;
+            f4 acc[4];
+            #pragma unroll
+            for (int ob = 0; ob < 4; ++ob) acc[ob] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            #pragma unroll
+            for (int obp = 0; obp < 4; ++obp) {
+                f4 a[4];
+                #pragma unroll
+                for (int ob = 0; ob < 4; ++ob) a[ob] = fl[(4 * ob + obp) * 64];
+                #pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    #pragma unroll
+                    for (int ob = 0; ob < 4; ++ob)
+                        acc[ob] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ob][q], act[4 * obp + q], acc[ob], 0, 0, 0);
+            }
+            #pragma unroll
+            for (int ob = 0; ob < 4; ++ob)
+                #pragma unroll
+                for (int q = 0; q < 4; ++q) act[4 * ob + q] = relu(acc[ob][q]);
+        }
+        f4 po = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        #pragma unroll
+        for (int b = 0; b < 4; ++b)
+            #pragma unroll
+            for (int q = 0; q < 4; ++q) po = __builtin_amdgcn_mfma_f32_4x4x1f32(wo[b][q], act[4 * b + q], po, 0, 0, 0);
+        float y[kNOut];
+        #pragma unroll
+        for (int o = 0; o < kNOut; ++o) {
+            // (group 0 + group 1) + (group 2 + group 3), as mlp_query_mfma adds them
+            const float s1 = po[o] + __shfl_xor(po[o], 16, 64);
+            y[o] = s1 + __shfl_xor(s1, 32, 64);
+        }
+        const int64_t s = row_of(unit);
+        if (g == 0 && s < n) store_query(rgb, s, y, r);
+        if constexpr (RAW) {
+            if (more) encode_shared<PRESET, LAYOUT>(x, h0, g, true);
+        }
+    }
+}
+
+__global__ __launch_bounds__(64 * kQWaves) void k_fwd_fp32(const float* __restrict__ w,
+                                                          const float* __restrict__ enc, int64_t n,
+                                                          float* __restrict__ rgb, int n_hidden, int fcol) {
+    query_units<false, NRC_PRESET_CONFIG, NRC_RAW14>(w, enc, n, rgb, n_hidden, fcol);
+}
+
+template <int PRESET, int LAYOUT>
+__global__ __launch_bounds__(64 * kQWaves) void k_fwd_raw_fp32_units(const float* __restrict__ w,
+                                                                    const float* __restrict__ raw, int64_t n,
+                                                                    float* __restrict__ rgb, int n_hidden,
+                                                                    int fcol) {
+    query_units<true, PRESET, LAYOUT>(w, raw, n, rgb, n_hidden, fcol);
 }
 
 // UPSTREAM = false: targets given, relative L2 loss (Eq. 5) produces dL/dy.
@@ -327,9 +499,6 @@ __global__ __launch_bounds__(64 * (kChainWaves + kGradWaves)) void k_train_fp32(
       if (chain) {
         constexpr int RW = RAWL == NRC_RAW14 ? 14 : 16;
         float* h0 = hs + sl * kLd;
-        // The four lane groups of a record share its encoding: groups 0..2 the
-        // frequency encoding of position coordinate g (the same code for the
-        // three, features 12g ..12g + 11), group 3 the rest (features 36 ..63).
         float x[RW];
         if (valid) {
             const float* rr = enc + src * RW;
@@ -339,33 +508,8 @@ __global__ __launch_bounds__(64 * (kChainWaves + kGradWaves)) void k_train_fp32(
             #pragma unroll
             for (int k = 0; k < RW; ++k) x[k] = 0.0f;
         }
-        float f[64];
-        if (g < 3) {
-            float xc[RW];
-            xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
-            encode_part<PRESET, RAWL, 0>(xc, f);
-            if (!valid) {
-                #pragma unroll
-                for (int k = 0; k < 12; ++k) f[k] = 0.0f;
-            }
-            #pragma unroll
-            for (int q = 0; q < 3; ++q)
-                *reinterpret_cast<float4*>(h0 + 12 * g + 4 * q) =
-                    make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
-        } else {
-            encode_part<PRESET, RAWL, 3>(x, f);
-            encode_part<PRESET, RAWL, 4>(x, f);
-            if (!valid) {
-                #pragma unroll
-                for (int k = 36; k < 64; ++k) f[k] = 0.0f;
-            }
-            #pragma unroll
-            for (int q = 9; q < 16; ++q)
-                *reinterpret_cast<float4*>(h0 + 4 * q) = make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        encode_shared<PRESET, RAWL>(x, h0, g, valid);
+        wave_lds_sync();
         #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const float4 v = *reinterpret_cast<const float4*>(h0 + 16 * b + 4 * g);
@@ -766,32 +910,43 @@ __global__ __launch_bounds__(64 * (kChainWaves + kGradWaves)) void k_train_fp32(
 
 // Query grid: one workgroup of kQWaves waves per CU (the fragments of every
 // hidden layer, 16 H KB, fill most of the CU's LDS), its waves claiming the
-// 64-query tiles of the workgroup's share.
+// tiles or units of the workgroup's share.
 inline size_t query_lds_bytes(const Geo& d) { return (size_t)(16 * d.H) * 64 * sizeof(f4); }
-inline int64_t query_blocks(int64_t n) {
-    const int64_t tiles = (n + 63) / 64;
-    const int64_t b = (tiles + kQWaves - 1) / kQWaves;
-    const int64_t cus = device_cu_count();
-    return b < cus ? b : cus;
-}
-
 template <typename K>
-hipError_t launch_query(K kernel, const Geo& d, const float* w, const float* in, int64_t n, float* rgb,
+hipError_t query_launch(K kernel, const Geo& d, size_t lds, const float* w, const float* in, int64_t n, float* rgb,
                         hipStream_t s) {
-    const int64_t blocks = query_blocks(n);
-    if (blocks == 0) return hipSuccess;
-    const size_t lds = query_lds_bytes(d);
+    const int64_t tiles = (n + 63) / 64, cus = device_cu_count();
+    if (tiles == 0) return hipSuccess;
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * kQWaves), lds, s, w, in, n, rgb, d.H, d.F);
+    // one workgroup per CU, or one per tile where there are fewer tiles
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles < cus ? tiles : cus)), dim3(64 * kQWaves), lds, s, w, in, n, rgb,
+                       d.H, d.F);
     return hipGetLastError();
+}
+
+// Raw records: units of 16 queries up to 24 64-query tiles per CU (393,216
+// queries), tiles of 64 above.  A tile keeps its wave for 18 us, so with few
+// tiles per wave the last round is long; a unit takes a quarter of that, but
+// the divergent shared encoding costs 170 vector instructions per 16 queries
+// instead of 270 per 64.  Measured (5 layers, us, units / tiles): 1,000 queries
+// 9.9 / 23.6, 20,011 14.8 / 23.8, 70,000 30.5 / 42.5, 300,000 105.5 / 119.1,
+// 400,000 136 / 139, 500,000 163 / 158, 2,073,600 655 / 618.
+constexpr int kUnitTilesPerCu = 24;
+
+template <int PRESET, int LAYOUT>
+hipError_t launch_raw_query(const Geo& d, const float* w, const float* raw, int64_t n, float* rgb, hipStream_t s) {
+    if ((n + 63) / 64 <= (int64_t)kUnitTilesPerCu * device_cu_count())
+        return query_launch(k_fwd_raw_fp32_units<PRESET, LAYOUT>, d,
+                            query_lds_bytes(d) + (size_t)kQWaves * 16 * kLd * sizeof(float), w, raw, n, rgb, s);
+    return query_launch(k_fwd_raw_fp32<PRESET, LAYOUT>, d, query_lds_bytes(d), w, raw, n, rgb, s);
 }
 
 }  // namespace
 
 hipError_t launch_fwd_fp32(const Geo& d, const float* w, const float* enc, int64_t n, float* rgb,
                            hipStream_t s) {
-    return launch_query(k_fwd_fp32, d, w, enc, n, rgb, s);
+    return query_launch(k_fwd_fp32, d, query_lds_bytes(d), w, enc, n, rgb, s);
 }
 
 hipError_t launch_fwd_raw_fp32(const Geo& d, int preset, int layout, const float* w, const float* raw,
@@ -799,17 +954,17 @@ hipError_t launch_fwd_raw_fp32(const Geo& d, int preset, int layout, const float
     const bool r14 = layout == NRC_RAW14;
     switch (preset) {
     case NRC_PRESET_PAPER_GAUSS:
-        return r14 ? launch_query(k_fwd_raw_fp32<NRC_PRESET_PAPER_GAUSS, NRC_RAW14>, d, w, raw, n, rgb, s)
-                   : launch_query(k_fwd_raw_fp32<NRC_PRESET_PAPER_GAUSS, NRC_RAW16>, d, w, raw, n, rgb, s);
+        return r14 ? launch_raw_query<NRC_PRESET_PAPER_GAUSS, NRC_RAW14>(d, w, raw, n, rgb, s)
+                   : launch_raw_query<NRC_PRESET_PAPER_GAUSS, NRC_RAW16>(d, w, raw, n, rgb, s);
     case NRC_PRESET_PAPER_TRI:
-        return r14 ? launch_query(k_fwd_raw_fp32<NRC_PRESET_PAPER_TRI, NRC_RAW14>, d, w, raw, n, rgb, s)
-                   : launch_query(k_fwd_raw_fp32<NRC_PRESET_PAPER_TRI, NRC_RAW16>, d, w, raw, n, rgb, s);
+        return r14 ? launch_raw_query<NRC_PRESET_PAPER_TRI, NRC_RAW14>(d, w, raw, n, rgb, s)
+                   : launch_raw_query<NRC_PRESET_PAPER_TRI, NRC_RAW16>(d, w, raw, n, rgb, s);
     case NRC_PRESET_PAPER:
-        return r14 ? launch_query(k_fwd_raw_fp32<NRC_PRESET_PAPER, NRC_RAW14>, d, w, raw, n, rgb, s)
-                   : launch_query(k_fwd_raw_fp32<NRC_PRESET_PAPER, NRC_RAW16>, d, w, raw, n, rgb, s);
+        return r14 ? launch_raw_query<NRC_PRESET_PAPER, NRC_RAW14>(d, w, raw, n, rgb, s)
+                   : launch_raw_query<NRC_PRESET_PAPER, NRC_RAW16>(d, w, raw, n, rgb, s);
     default:
-        return r14 ? launch_query(k_fwd_raw_fp32<NRC_PRESET_CONFIG, NRC_RAW14>, d, w, raw, n, rgb, s)
-                   : launch_query(k_fwd_raw_fp32<NRC_PRESET_CONFIG, NRC_RAW16>, d, w, raw, n, rgb, s);
+        return r14 ? launch_raw_query<NRC_PRESET_CONFIG, NRC_RAW14>(d, w, raw, n, rgb, s)
+                   : launch_raw_query<NRC_PRESET_CONFIG, NRC_RAW16>(d, w, raw, n, rgb, s);
     }
 }
 
