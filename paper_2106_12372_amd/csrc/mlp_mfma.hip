@@ -468,6 +468,97 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma_segs(const T* __restrict__ 
     }
 }
 
+template <int N> struct IntC { static constexpr int value = N; };
+constexpr int kWideWaves = 16;
+
+// Inference from encoded rows for width 128 (1 to 5 hidden layers): one
+// workgroup of 16 waves per CU shares one LDS copy of the weights (148 KB at
+// depth 5), owns a contiguous share of the units of 16 * COLS records and its
+// waves claim them one at a time.  A layer runs two row blocks at a time, their
+// 32 outputs packed into one chunk of the next operand before the next two
+// start: 8 * COLS accumulator registers instead of 32 * COLS, so four waves fit
+// a SIMD, and the conversion of one pair issues beside the products of the
+// next.  Same products in the same order per accumulator as mlp_tile.  Bound by
+// the matrix cores beside the weights' LDS reads: 500,003 records take 53 us,
+// 1.4 PFLOP/s (82 us with one wave per SIMD and all row blocks at once).
+template <typename T, int COLS, typename Src>
+__global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restrict__ ffr, int n_frags, Src src, int n_hidden,
+                                                      int fcol) {
+    using V = typename Vec8<T>::type;
+    constexpr int W = 128, KC = 4, PER = 4 / COLS;         // units per 64-record tile
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    __shared__ int claimed;
+    V* sfr = reinterpret_cast<V*>(smem_raw);
+    const int lane = threadIdx.x & 63;
+    const int g = lane >> 4, ln = lane & 15;
+    if (threadIdx.x == 0) claimed = 0;
+    stage_frags<64 * kWideWaves>(sfr, reinterpret_cast<const V*>(ffr), n_frags);
+    __syncthreads();
+    const Geo geo(W, n_hidden);
+    const int64_t units = src.n_tiles() * PER;
+    const int64_t per = units / gridDim.x, extra = units % gridDim.x;
+    const int64_t u_begin = (int64_t)blockIdx.x * per + ((int64_t)blockIdx.x < extra ? blockIdx.x : extra);
+    const int64_t u_end = u_begin + per + ((int64_t)blockIdx.x < extra ? 1 : 0);
+    for (;;) {
+        int k = 0;
+        if (lane == 0) k = atomicAdd(&claimed, 1);
+        const int64_t u = u_begin + __builtin_amdgcn_readfirstlane(k);
+        if (u >= u_end) break;
+        const void* e;
+        int64_t base, cnt;
+        float* out;
+        src.locate(u / PER, e, base, cnt, out);
+        base += 16 * COLS * (u % PER);
+        const T* enc = reinterpret_cast<const T*>(e);
+        V b[COLS][KC];
+        #pragma unroll
+        for (int col = 0; col < COLS; ++col) {              // rows past the end read the last row
+            int64_t row = base + 16 * col + ln;
+            row = row < cnt ? row : cnt - 1;
+            #pragma unroll
+            for (int c = 0; c < 2; ++c)
+                b[col][c] = *reinterpret_cast<const V*>(enc + row * kEncWidth + 32 * c + 8 * g);
+        }
+        float r[COLS][3];
+        #pragma unroll
+        for (int col = 0; col < COLS; ++col) reflectance_operand(b[col][1], fcol, ln, r[col]);
+        auto layer = [&](const V* fl, auto kc_) {
+            constexpr int kc = decltype(kc_)::value;
+            V nb[COLS][KC];
+            #pragma unroll
+            for (int p = 0; p < KC; ++p) {
+                f32x4 acc[COLS][2];
+                #pragma unroll
+                for (int c = 0; c < kc; ++c)
+                    #pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const V a = fl[((2 * p + h) * kc + c) * 64];
+                        #pragma unroll
+                        for (int col = 0; col < COLS; ++col)
+                            acc[col][h] = mfma(a, b[col][c], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[col][h]);
+                    }
+                #pragma unroll
+                for (int col = 0; col < COLS; ++col) nb[col][p] = relu_packed(pack8<T, V>(acc[col][0], acc[col][1]));
+            }
+            #pragma unroll
+            for (int col = 0; col < COLS; ++col)
+                #pragma unroll
+                for (int p = 0; p < KC; ++p) b[col][p] = nb[col][p];
+        };
+        layer(sfr + lane, IntC<2>{});                       // the input layer has K = 64
+        for (int l = 1; l < n_hidden; ++l) layer(sfr + geo.fwd_base(l) * 64 + lane, IntC<KC>{});
+        const V* fo = sfr + geo.fwd_base(n_hidden) * 64 + lane;
+        f32x4 o[COLS];
+        #pragma unroll
+        for (int col = 0; col < COLS; ++col) o[col] = mfma(fo[0], b[col][0], f32x4{0.f, 0.f, 0.f, 0.f});
+        #pragma unroll
+        for (int c = 1; c < KC; ++c)
+            #pragma unroll
+            for (int col = 0; col < COLS; ++col) o[col] = mfma(fo[c * 64], b[col][c], o[col]);
+        store_rgb<COLS>(o, r, base, cnt, g, ln, out);
+    }
+}
+
 // Inference from raw records with the encoding fused in (Sec. 3.6 encodings,
 // Sec. 4 network).  Each wave owns a 64-record tile: lane r encodes record r
 // (the next tile's raw floats are loaded while the current tile computes),
@@ -1343,18 +1434,44 @@ hipError_t fwd_fixed_launch(const void* ffr, const Src& src, int64_t tiles, int 
     return hipGetLastError();
 }
 
+// Width 128: units of 16 records up to six 64-record tiles per CU (98,304
+// records), of 32 records above.  Measured (BF16, 5 layers, us per launch, 16 /
+// 32): 1,000 records 6.9 / 8.4, 49,152 9.5 / 10.5, 100,000 15.6 / 16.4, 131,072
+// 19.7 / 18.8, 500,003 58.5 / 53.2 (4-wave workgroups of 64-record tiles before:
+// 15.3, 16.0, 25.2, 25.2, 82.3).  8 and 12 waves, and 64-record units, were
+// slower or equal (52.9 to 54.8 at 500,003).
+constexpr int kWideTilesPerCu = 6;
+
+template <typename T, int COLS, typename Src>
+hipError_t fwd_wide_launch(const Geo& d, const void* ffr, const Src& src, int64_t tiles, hipStream_t s) {
+    const size_t lds = (size_t)d.n_fwd_frags() * 1024;
+    int64_t blocks = tiles * (4 / COLS);
+    if (blocks > device_cu_count()) blocks = device_cu_count();
+    auto k = k_fwd_wide<T, COLS, Src>;
+    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kWideWaves), lds, s, (const T*)ffr, d.n_fwd_frags(), src, d.H,
+                       d.F);
+    return hipGetLastError();
+}
+template <typename T, typename Src>
+hipError_t fwd_wide(const Geo& d, const void* ffr, const Src& src, int64_t tiles, hipStream_t s) {
+    if (tiles <= (int64_t)kWideTilesPerCu * device_cu_count()) return fwd_wide_launch<T, 1>(d, ffr, src, tiles, s);
+    return fwd_wide_launch<T, 2>(d, ffr, src, tiles, s);
+}
+
 template <typename T, int W>
 hipError_t fwd_segs_dispatch(const Geo& d, const void* ffr, const SegList& segs, hipStream_t s) {
     constexpr int COLS = 4;
     const int64_t tiles = segs.tile_end[segs.count - 1];
     if (tiles == 0) return hipSuccess;
-    if (W == 64 && small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncSegs{segs}, tiles, s);
-    if (W == 64 && d.H == 5) return fwd_fixed_launch<T>(ffr, EncSegs{segs}, tiles, d.F, s);
+    if constexpr (W == 128) return fwd_wide<T>(d, ffr, EncSegs{segs}, tiles, s);
+    if (small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncSegs{segs}, tiles, s);
+    if (d.H == 5) return fwd_fixed_launch<T>(ffr, EncSegs{segs}, tiles, d.F, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 64 * 16;
     int64_t blocks = (tiles + 3) / 4;
     const int64_t resident = resident_fwd_blocks(lds);
     if (blocks > resident) blocks = resident;
-    auto k = k_fwd_mfma_segs<T, W, COLS>;
+    auto k = k_fwd_mfma_segs<T, 64, COLS>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), lds, s, (const T*)ffr, d.n_fwd_frags(), segs, d.H,
                        d.F);
@@ -1368,13 +1485,14 @@ hipError_t fwd_dispatch(const Geo& d, const void* ffr, const void* enc, int64_t 
     constexpr int COLS = 4;
     const int64_t tiles = (n + 16 * COLS - 1) / (16 * COLS);
     if (tiles == 0) return hipSuccess;
-    if (W == 64 && small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncBatch{enc, n, rgb}, tiles, s);
-    if (W == 64 && d.H == 5) return fwd_fixed_launch<T>(ffr, EncBatch{enc, n, rgb}, tiles, d.F, s);
+    if constexpr (W == 128) return fwd_wide<T>(d, ffr, EncBatch{enc, n, rgb}, tiles, s);
+    if (small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncBatch{enc, n, rgb}, tiles, s);
+    if (d.H == 5) return fwd_fixed_launch<T>(ffr, EncBatch{enc, n, rgb}, tiles, d.F, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 64 * 16;
     int64_t blocks = (tiles + 3) / 4;
     const int64_t resident = resident_fwd_blocks(lds);
     if (blocks > resident) blocks = resident;
-    auto k = k_fwd_mfma<T, W, COLS>;
+    auto k = k_fwd_mfma<T, 64, COLS>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), lds, s, (const T*)ffr, d.n_fwd_frags(),
                        (const T*)enc, n, rgb, d.H, d.F);
