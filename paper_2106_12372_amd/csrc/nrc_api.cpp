@@ -347,13 +347,9 @@ int nrc_set_weights_device(nrc_cache* cache, const float* dev_w, int64_t n, void
     if (((uintptr_t)dev_w & 3) != 0) return fail(NRC_EINVAL, "misaligned weights");
     const Geo d(cache->cfg.width, cache->cfg.n_hidden);
     if (n != d.n_params()) return fail(NRC_EINVAL, "expected %d weights, got %lld", d.n_params(), (long long)n);
-    hipStream_t s = (hipStream_t)stream;
-    const size_t bytes = (size_t)d.n_params() * 4;
-    hipError_t e = hipMemcpyAsync(cache->w(), dev_w, bytes, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(cache->m(), 0, bytes, s);
-    if (e == hipSuccess) e = hipMemsetAsync(cache->v(), 0, bytes, s);
-    if (e == hipSuccess) e = hipMemsetAsync(cache->tslots(), 0, 16, s);
-    if (e == hipSuccess) e = reset_ema_and_frags(cache, s);
+    const hipError_t e = launch_install(cache->cfg.precision, d, dev_w, cache->w(), cache->m(), cache->v(),
+                                        cache->tslots(), cache->e(), cache->wbar(), cache->ffr(), cache->bfr(),
+                                        cache->effr(), (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "device weight upload");
     cache->parity = 0;
     return ok();

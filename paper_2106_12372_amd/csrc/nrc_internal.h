@@ -309,6 +309,12 @@ hipError_t launch_self_train(const float* radiance, const float* throughput, con
 size_t error_norms_scratch_bytes();
 hipError_t launch_error_norms(const float* got, const double* ref, int64_t n, double* scratch, double* out,
                               hipStream_t s);
+// Sets the weights from device memory (src may be w itself), clears the moments
+// and the step slots, restarts the EMA set (e, wbar: NULL without one) and
+// writes the reduced-precision copies (NULL in the FP32 forms): one launch.
+hipError_t launch_install(int precision, const Geo& d, const float* src, float* w, float* m, float* v,
+                          int32_t* tslots, float* e, float* wbar, void* ffr, void* bfr, void* effr,
+                          hipStream_t s);
 // Writes W's forward fragments to ffr and ffr2 (each may be NULL) and its
 // backward fragments to bfr (may be NULL).
 hipError_t launch_build_frags(int precision, const Geo& d, const float* w, void* ffr, void* bfr,

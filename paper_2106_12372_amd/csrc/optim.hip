@@ -258,6 +258,39 @@ __global__ __launch_bounds__(256) void k_build_frags(const float* __restrict__ w
     if (ffr2) write_frags<T>(d, p, w[p], ffr2, (T*)nullptr);
 }
 
+// Weights set from device memory, everything that goes with them in one launch:
+// the master copy, the Adam moments and step count cleared, the EMA set at
+// W_bar = W, E = 0 (e, wbar NULL: none) and the fragments of each
+// reduced-precision copy (ffr NULL: none; the slots no weight maps to stay the
+// zeros they were created with).  Bound by latency: a thread per weight, ~28
+// bytes each; it replaces two copies, up to seven fills and the fragment build
+// (W = 128, 5 layers: 61 -> 5 us of device time per call).
+template <typename T>
+__global__ __launch_bounds__(256) void k_install(const float* src, float* w, float* __restrict__ m,
+                                                 float* __restrict__ v, int32_t* __restrict__ tslots,
+                                                 float* __restrict__ e, float* __restrict__ wbar,
+                                                 T* __restrict__ ffr, T* __restrict__ bfr, T* __restrict__ effr,
+                                                 int width, int n_hidden) {
+    const Geo d(width, n_hidden);
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p < 4) tslots[p] = 0;
+    if (p >= d.n_params()) return;
+    const float x = src[p];
+    w[p] = x;
+    m[p] = 0.0f;
+    v[p] = 0.0f;
+    if (wbar) {
+        wbar[p] = x;
+        e[p] = 0.0f;
+    }
+    if (ffr) {
+        int64_t fi, bi;
+        frag_slots(d, p, fi, bi);
+        put_frags<T>(d, fi, bi, x, ffr, bfr, __is_same(T, __bf16));
+        if (effr) put_frags<T>(d, fi, bi, x, effr, (T*)nullptr, false);
+    }
+}
+
 }  // namespace
 
 int reduce_blocks(int n_params) { return (n_params + kRedParams - 1) / kRedParams; }
@@ -304,6 +337,20 @@ hipError_t launch_build_frags(int precision, const Geo& d, const float* w, void*
     else if (precision == NRC_BF16)
         hipLaunchKernelGGL(k_build_frags<__bf16>, grid, block, 0, s, w, (__bf16*)ffr, (__bf16*)bfr,
                            (__bf16*)ffr2, d.W, d.H);
+    return hipGetLastError();
+}
+
+hipError_t launch_install(int precision, const Geo& d, const float* src, float* w, float* m, float* v,
+                          int32_t* tslots, float* e, float* wbar, void* ffr, void* bfr, void* effr,
+                          hipStream_t s) {
+    const dim3 grid((d.n_params() + 255) / 256), block(256);
+    if (precision == NRC_BF16)
+        hipLaunchKernelGGL(k_install<__bf16>, grid, block, 0, s, src, w, m, v, tslots, e, wbar, (__bf16*)ffr,
+                           (__bf16*)bfr, (__bf16*)effr, d.W, d.H);
+    else
+        // FP32 caches have no reduced-precision copies (ffr, bfr, effr are NULL)
+        hipLaunchKernelGGL(k_install<_Float16>, grid, block, 0, s, src, w, m, v, tslots, e, wbar, (_Float16*)ffr,
+                           (_Float16*)bfr, (_Float16*)effr, d.W, d.H);
     return hipGetLastError();
 }
 

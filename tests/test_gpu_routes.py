@@ -52,3 +52,24 @@ def test_batches_and_their_slices_agree(N, prec, width, n_hidden, raw_form, past
         assert torch.equal(N.nrc_forward(c, part), whole[lo:hi]), (lo, hi)
         if width == 64:
             assert torch.equal(N.nrc_forward_raw(c, raw[lo:hi].clone()), whole[lo:hi]), (lo, hi)
+
+
+@pytest.mark.parametrize("prec,width,n_hidden,ema", [("fp16", 64, 5, 0.0), ("bf16", 64, 8, 0.99), ("fp16", 128, 3, 0.9),
+                                                     ("bf16", 128, 5, 0.0), ("fp32", 64, 2, 0.5),
+                                                     ("fp32_valu", 64, 1, 0.0)])
+def test_weights_from_the_device_equal_weights_from_the_host(N, prec, width, n_hidden, ema):
+    """One launch sets what the host path sets with copies and fills: every byte of the
+    workspace (weights, moments, step count, EMA set, fragment copies) is the same."""
+    cfg = N.make_config(width=width, n_hidden=n_hidden, precision=prec, ema_alpha=ema)
+    w = sd.glorot_weights(width, n_hidden, seed=5)
+    caches = [N.Cache(cfg), N.Cache(cfg)]
+    raw = sd.raw_records(130, 8)
+    for c in caches:                                   # leave something in every field
+        c.set_weights(sd.glorot_weights(width, n_hidden, seed=9))
+        enc = N.nrc_encode(c, torch.from_numpy(raw).cuda())
+        for _ in range(3):
+            N.nrc_train_step(c, enc, torch.from_numpy(sd.targets(raw)).cuda())
+    caches[0].set_weights(w)
+    caches[1].set_weights_device(torch.from_numpy(w).cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(caches[0].ws, caches[1].ws)
