@@ -59,7 +59,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = {"k_fwd_raw_mfma_fixed": ["mlp_mfma.hip", "encode_impl.h", "nrc_internal.h"],
+KERNEL_SOURCES = {"k_fwd_raw_mfma_fixed": ["mlp_mfma.hip", "mfma_ops.h", "encode_impl.h", "nrc_internal.h"],
                   "k_fwd_raw_fp32": ["mlp_fp32.hip", "encode_impl.h", "nrc_internal.h"],
                   "k_fwd_raw_fp32_valu": ["mlp_fp32_valu.hip", "encode_impl.h", "nrc_internal.h"]}
 

@@ -27,75 +27,11 @@
 #include <atomic>
 
 #include "encode_impl.h"
+#include "mfma_ops.h"
 #include "nrc_internal.h"
 
 namespace nrc {
 namespace {
-
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <typename T> struct Vec8;
-template <> struct Vec8<_Float16> { typedef f16x8 type; };
-template <> struct Vec8<__bf16> { typedef bf16x8 type; };
-
-__device__ inline f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-__device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-template <typename T> __device__ inline T to_t(float x) { return (T)x; }
-
-template <typename V> __device__ inline V zero8() {
-    V v;
-    #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = 0;
-    return v;
-}
-
-// Two accumulator blocks (features 4g..4g+3 and 16+4g..16+4g+3 of a chunk)
-// -> one B operand in chained order.
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-template <typename T, typename V> __device__ inline V pack8(f32x4 lo, f32x4 hi) {
-    if constexpr (sizeof(T) == 2 && !__is_same(T, _Float16)) {
-        // BF16: one v_cvt_pk_bf16_f32 per pair (the generic vector conversion
-        // is split into single conversions and byte permutes)
-        u32x4 r;
-        r[0] = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{lo[0], lo[1]}, bf16x2));
-        r[1] = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{lo[2], lo[3]}, bf16x2));
-        r[2] = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{hi[0], hi[1]}, bf16x2));
-        r[3] = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{hi[2], hi[3]}, bf16x2));
-        return __builtin_bit_cast(V, r);
-    } else {
-        const f32x8 f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        return __builtin_convertvector(f, V);
-    }
-}
-
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-
-// ReLU on a packed FP16/BF16 operand: a negative value has its sign bit set,
-// so as a signed 16-bit integer it is negative and max(., 0) maps it to +0;
-// non-negative values are unchanged.  Rounding preserves sign, so
-// relu(round(x)) == round(relu(x)).
-template <typename V> __device__ inline V relu_packed(V v) {
-    s16x8 i = __builtin_bit_cast(s16x8, v);
-    i = __builtin_elementwise_max(i, (s16x8)(0));
-    return __builtin_bit_cast(V, i);
-}
-
-__device__ inline f32x4 relu4(f32x4 a) {
-    f32x4 r;
-    #pragma unroll
-    for (int j = 0; j < 4; ++j) r[j] = fmaxf(a[j], 0.0f);
-    return r;
-}
 
 // ---------------------------------------------------------------------------
 // Inference
@@ -215,25 +151,6 @@ __device__ inline void mlp_tile_colwise(const typename Vec8<T>::type* sfr, typen
     const V a0 = fo[0], a1 = fo[64];
     #pragma unroll
     for (int col = 0; col < COLS; ++col) o[col] = mfma(a1, b[col][1], mfma(a0, b[col][0], f32x4{0.f, 0.f, 0.f, 0.f}));
-}
-
-// Reflectance factor alpha + beta (Sec. 5) of record ln from the B operand
-// holding input features 32..63 in natural order (lane 16g + ln: features
-// 32 + 8g .. 32 + 8g + 7); valid in lanes 0..15, 1 when fcol == 0.  Config
-// preset: diffuse 53..55 sit in lane 32 + ln, slots 5..7, and specular 56..58
-// in lane 48 + ln, slots 0..2; paper presets: both in lane 48 + ln, slots 0..5.
-template <typename V>
-__device__ inline void reflectance_operand(const V& b1, int fcol, int ln, float (&r)[3]) {
-    if (fcol == kAlbedoColConfig) {
-        #pragma unroll
-        for (int c = 0; c < 3; ++c)
-            r[c] = __shfl((float)b1[5 + c], 32 + ln, 64) + __shfl((float)b1[c], 48 + ln, 64);
-    } else if (fcol == kAlbedoColPaper) {
-        #pragma unroll
-        for (int c = 0; c < 3; ++c) r[c] = __shfl((float)b1[c] + (float)b1[3 + c], 48 + ln, 64);
-    } else {
-        r[0] = r[1] = r[2] = 1.0f;
-    }
 }
 
 template <int COLS>
@@ -468,7 +385,6 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma_segs(const T* __restrict__ 
     }
 }
 
-template <int N> struct IntC { static constexpr int value = N; };
 constexpr int kWideWaves = 16;
 
 // Inference from encoded rows for width 128 (1 to 5 hidden layers): one
@@ -481,9 +397,13 @@ constexpr int kWideWaves = 16;
 // next.  Same products in the same order per accumulator as mlp_tile.  Bound by
 // the matrix cores beside the weights' LDS reads: 500,003 records take 53 us,
 // 1.4 PFLOP/s (82 us with one wave per SIMD and all row blocks at once).
-template <typename T, int COLS, typename Src>
-__global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restrict__ ffr, int n_frags, Src src, int n_hidden,
-                                                      int fcol) {
+// ACT: the forward pass of the autograd form; every hidden layer's activations
+// also go to act [record][layer][feature] and the network outputs to act_y
+// [record][4].
+template <typename T, int COLS, bool ACT, typename Src>
+__global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restrict__ ffr, int n_frags, Src src,
+                                                             int n_hidden, int fcol, T* __restrict__ act,
+                                                             float* __restrict__ act_y) {
     using V = typename Vec8<T>::type;
     constexpr int W = 128, KC = 4, PER = 4 / COLS;         // units per 64-record tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -522,7 +442,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restric
         float r[COLS][3];
         #pragma unroll
         for (int col = 0; col < COLS; ++col) reflectance_operand(b[col][1], fcol, ln, r[col]);
-        auto layer = [&](const V* fl, auto kc_) {
+        auto layer = [&](const V* fl, auto kc_, int l) {
             constexpr int kc = decltype(kc_)::value;
             V nb[COLS][KC];
             #pragma unroll
@@ -544,9 +464,25 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restric
             for (int col = 0; col < COLS; ++col)
                 #pragma unroll
                 for (int p = 0; p < KC; ++p) b[col][p] = nb[col][p];
+            if constexpr (ACT) {
+                typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+                #pragma unroll
+                for (int col = 0; col < COLS; ++col) {
+                    const int64_t row = base + 16 * col + ln;
+                    if (row < cnt) {
+                        T* dst = act + (row * n_hidden + l) * W + 4 * g;
+                        #pragma unroll
+                        for (int p = 0; p < KC; ++p) {
+                            const u32x4 u = __builtin_bit_cast(u32x4, b[col][p]);
+                            *reinterpret_cast<u32x2*>(dst + 32 * p) = u32x2{u[0], u[1]};
+                            *reinterpret_cast<u32x2*>(dst + 32 * p + 16) = u32x2{u[2], u[3]};
+                        }
+                    }
+                }
+            }
         };
-        layer(sfr + lane, IntC<2>{});                       // the input layer has K = 64
-        for (int l = 1; l < n_hidden; ++l) layer(sfr + geo.fwd_base(l) * 64 + lane, IntC<KC>{});
+        layer(sfr + lane, IntC<2>{}, 0);                    // the input layer has K = 64
+        for (int l = 1; l < n_hidden; ++l) layer(sfr + geo.fwd_base(l) * 64 + lane, IntC<KC>{}, l);
         const V* fo = sfr + geo.fwd_base(n_hidden) * 64 + lane;
         f32x4 o[COLS];
         #pragma unroll
@@ -556,6 +492,14 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restric
             #pragma unroll
             for (int col = 0; col < COLS; ++col) o[col] = mfma(fo[c * 64], b[col][c], o[col]);
         store_rgb<COLS>(o, r, base, cnt, g, ln, out);
+        if constexpr (ACT) {
+            #pragma unroll
+            for (int col = 0; col < COLS; ++col) {
+                const int64_t row = base + 16 * col + ln;
+                if (g == 0 && row < cnt)
+                    *reinterpret_cast<f32x4*>(act_y + row * 4) = f32x4{o[col][0], o[col][1], o[col][2], 0.0f};
+            }
+        }
     }
 }
 
@@ -639,36 +583,6 @@ __global__ __launch_bounds__(64 * NW) void k_fwd_raw_mfma(const T* __restrict__ 
     }
 }
 
-// Encodes the lane's record x and stores its 64 features, rounded to T, at
-// dst (a 16-byte aligned LDS row), followed by the record's reflectance
-// factor alpha + beta (Sec. 5) as 3 floats in the row's 16 spare bytes: the
-// rounded diffuse plus the rounded specular albedo per channel, the same
-// arithmetic reflectance_operand does on the B operand, here in the lane that
-// holds the record instead of three shuffles per channel and column.
-// Features 8q .. 8q + 7 of f, rounded to T, into an LDS row.
-template <typename T>
-__device__ inline void store8(T* dst, const float* f, int q) {
-    using V = typename Vec8<T>::type;
-    const f32x4 lo = f32x4{f[8 * q], f[8 * q + 1], f[8 * q + 2], f[8 * q + 3]};
-    const f32x4 hi = f32x4{f[8 * q + 4], f[8 * q + 5], f[8 * q + 6], f[8 * q + 7]};
-    *reinterpret_cast<V*>(dst + 8 * q) = pack8<T, V>(lo, hi);
-}
-
-// Features f[0 .. 3], rounded to T, into an LDS row (8-byte aligned); the same
-// rounding as store8.
-template <typename T>
-__device__ inline void store4(T* dst, const float* f) {
-    if constexpr (sizeof(T) == 2 && !__is_same(T, _Float16)) {
-        uint2 r;
-        r.x = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{f[0], f[1]}, bf16x2));
-        r.y = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{f[2], f[3]}, bf16x2));
-        *reinterpret_cast<uint2*>(dst) = r;
-    } else {
-        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-        *reinterpret_cast<h4*>(dst) = __builtin_convertvector(f32x4{f[0], f[1], f[2], f[3]}, h4);
-    }
-}
-
 template <typename T, int PRESET>
 __device__ inline void store_reflectance(T* dst, const float* f, int fcol) {
     f32x4 r = f32x4{1.0f, 1.0f, 1.0f, 0.0f};
@@ -680,6 +594,12 @@ __device__ inline void store_reflectance(T* dst, const float* f, int fcol) {
     *reinterpret_cast<f32x4*>(dst + 64) = r;
 }
 
+// Encodes the lane's record x and stores its 64 features, rounded to T, at
+// dst (a 16-byte aligned LDS row), followed by the record's reflectance
+// factor alpha + beta (Sec. 5) as 3 floats in the row's 16 spare bytes: the
+// rounded diffuse plus the rounded specular albedo per channel, the same
+// arithmetic reflectance_operand does on the B operand, here in the lane that
+// holds the record instead of three shuffles per channel and column.
 template <typename T, int PRESET, int LAYOUT>
 __device__ inline void encode_to_lds(const float* x, T* dst, int fcol) {
     float f[64];
@@ -687,14 +607,6 @@ __device__ inline void encode_to_lds(const float* x, T* dst, int fcol) {
     #pragma unroll
     for (int q = 0; q < 8; ++q) store8<T>(dst, f, q);
     store_reflectance<T, PRESET>(dst, f, fcol);
-}
-
-// Orders a wave's LDS accesses: those before complete before those after,
-// across the wave's lanes.
-__device__ inline void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Fused raw -> encode -> network inference for a depth fixed at compile time
@@ -824,35 +736,6 @@ __global__ __launch_bounds__(64 * NW) void k_fwd_raw_mfma_fixed(const T* __restr
     }
 }
 
-// The lane's record x (its four lane groups hold the same one) encoded into the
-// LDS row h0, a share of the features per group: groups 0..2 the frequency
-// encoding of position coordinate g (the same code for the three, features
-// 12g .. 12g + 11), group 3 the rest (36 .. 63).  valid = false: a row of zeros.
-template <typename T, int PRESET, int LAYOUT, int RW>
-__device__ inline void encode_shared(const float (&x)[RW], T* h0, int g, bool valid) {
-    float f[64];
-    if (g < 3) {
-        float xc[RW];
-        xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
-        encode_part<PRESET, LAYOUT, 0>(xc, f);
-        if (!valid) {
-            #pragma unroll
-            for (int k = 0; k < 12; ++k) f[k] = 0.0f;
-        }
-        #pragma unroll
-        for (int q = 0; q < 3; ++q) store4<T>(h0 + 12 * g + 4 * q, f + 4 * q);
-    } else {
-        encode_part<PRESET, LAYOUT, 3>(x, f);
-        encode_part<PRESET, LAYOUT, 4>(x, f);
-        if (!valid) {
-            #pragma unroll
-            for (int k = 36; k < 64; ++k) f[k] = 0.0f;
-        }
-        #pragma unroll
-        for (int q = 9; q < 16; ++q) store4<T>(h0 + 4 * q, f + 4 * q);
-    }
-}
-
 // Inference over few records (width 64, any depth): four waves share a 64-record
 // tile, 16 records (one operand column block) each, so a tile's chain of layers
 // is a quarter as long as in the kernels above and a small batch reaches four
@@ -948,31 +831,30 @@ __global__ __launch_bounds__(256) void k_fwd_small(const T* __restrict__ ffr, in
 // ---------------------------------------------------------------------------
 // Training: forward + loss gradient + data backward + per-tile weight gradient
 // ---------------------------------------------------------------------------
-// Records per workgroup: 64 at width 64 (4 chain waves), 32 at width 128 (2
-// chain waves), so that every layer's activations and deltas of the tile fit
-// in LDS; as many weight-gradient waves again.
-template <int W> struct TrainShape {
-    static constexpr int TS = W == 64 ? 64 : 32;   // records per tile
+// One 64-record tile per workgroup: 4 chain waves, and as many weight-gradient
+// waves beside them.
+struct TrainShape {
+    static constexpr int TS = 64;                  // records per tile
     static constexpr int NW = TS / 16;             // chain waves per workgroup
     static constexpr int LDT = TS + 8;             // row stride of dL/dy, elements
-    static constexpr int LDR = W == 64 ? 72 : 144; // record row stride of h_l, delta_l
+    static constexpr int LDR = 72;                 // record row stride of h_l, delta_l
 };
-// LDS bytes of one training workgroup: h_0 [record][64 + 8], h_1..h_H and
-// delta_1..delta_H [record][LDR], then dL/dy [3 (16) rows][record].
-__host__ __device__ constexpr int train_lds_bytes(int W, int H) {
-    return ((W == 64 ? 64 : 32) * (72 + 2 * H * (W == 64 ? 72 : 144)) + 16 * (W == 64 ? 72 : 40)) * 2;
+// LDS bytes of one training workgroup: h_0 .. h_H [record][72], delta_1 ..
+// delta_H [record][72], then dL/dy [3 (16) rows][record]; the forward-only form
+// holds the activations alone, which leaves room for two workgroups per CU.
+__host__ __device__ constexpr int train_lds_bytes(int H, bool store = false) {
+    return (64 * 72 * (store ? 1 + H : 1 + 2 * H) + (store ? 0 : 16 * 72)) * 2;
 }
 
-// Activation buffer of the autograd form (ACT): per tile, h_1 .. h_H as
-// [layer][record][feature] at the operand precision (the LDS rows without
-// their padding), then, after every tile's block, the network output
-// [tile * TS + record][4] (FP32).  kActNone: no buffer; kActStore: forward only,
-// writes the buffer and rgb, then exits; kActLoad: the forward pass is read
-// from the buffer instead of recomputed.
+// Activation buffer of the autograd form (ACT): h_1 .. h_H as
+// [record][layer][feature] at the operand precision, then, past the last tile's
+// records, the network output [record][4] (FP32).  kActNone: no buffer;
+// kActStore: forward only, writes the buffer and rgb, then exits; kActLoad: the
+// forward pass is read from the buffer instead of recomputed.
 constexpr int kActNone = 0, kActStore = 1, kActLoad = 2;
 
 // Weight-gradient waves beside the chain waves (none in the forward-only form).
-template <int W, int ACT> constexpr int train_helpers() { return ACT == kActStore ? 0 : TrainShape<W>::NW; }
+template <int ACT> constexpr int train_helpers() { return ACT == kActStore ? 0 : TrainShape::NW; }
 
 // Training records given raw (RAWL = their layout, PRESET = the cache's
 // encoding; RAWL < 0: encoded rows): the kernel's enc argument then points at
@@ -980,8 +862,7 @@ template <int W, int ACT> constexpr int train_helpers() { return ACT == kActStor
 // wave encode record j, a share of its features each, into the record's h_0
 // row, where the stand-alone encoding kernel would have written it, before the
 // wave reads its operands back.
-template <typename T, int W, bool UPSTREAM, bool GENC, int ACT = kActNone, int RAWL = -1,
-          int PRESET = NRC_PRESET_CONFIG>
+template <typename T, bool UPSTREAM, bool GENC, int ACT = kActNone, int RAWL = -1, int PRESET = NRC_PRESET_CONFIG>
 __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
                                                     const T* __restrict__ bfr,
                                                     const T* __restrict__ enc,
@@ -995,10 +876,10 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
                                                     T* __restrict__ act, float* __restrict__ rgb,
                                                     LcgGather lg) {
     using V = typename Vec8<T>::type;
-    using S = TrainShape<W>;
-    constexpr int MB = W / 16, KC = W / 32, TS = S::TS, NW = S::NW, LDT = S::LDT, TK = TS / 32;
+    using S = TrainShape;
+    constexpr int W = 64, MB = W / 16, KC = W / 32, TS = S::TS, NW = S::NW, LDT = S::LDT, TK = TS / 32;
     constexpr int LDR = S::LDR, LD0 = 72;
-    constexpr int NHW = train_helpers<W, ACT>();             // weight-gradient waves
+    constexpr int NHW = train_helpers<ACT>();                // weight-gradient waves
     constexpr int NT = 64 * (NW + NHW);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     __shared__ float wsum[4];
@@ -1100,24 +981,27 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
         #pragma unroll
         for (int c = 0; c < 3; ++c) tg[c] = tgt[src * 3 + c];
     }
-    // the tile's block of the activation buffer and its network outputs
+    // the tile's rows of the activation buffer (the buffer is sized for whole
+    // tiles) and its network outputs
     const int64_t n_tiles = gridDim.x;
     T* act_t = act + tile * (int64_t)(n_hidden * W * TS);
     float* act_y = reinterpret_cast<float*>(act + n_tiles * (int64_t)(n_hidden * W * TS));
-    // copy h_1 .. h_H between the LDS rows and the buffer, 16 bytes at a time
+    // copy h_1 .. h_H between the LDS rows (layer, record) and the buffer's
+    // (record, layer), 16 bytes at a time
     auto copy_act = [&](bool to_lds) {
         constexpr int CPR = W * (int)sizeof(T) / 16;          // 16-byte chunks per record row
         const int rows = n_hidden * TS;
         for (int i = tid; i < rows * CPR; i += NT) {
             const int rr = i / CPR, q = i - rr * CPR;
+            const int rec = rr % TS, l0 = rr / TS;
             u32x4* l = reinterpret_cast<u32x4*>(hT + TS * LD0 + rr * LDR) + q;
-            u32x4* gp = reinterpret_cast<u32x4*>(act_t + rr * W) + q;
+            u32x4* gp = reinterpret_cast<u32x4*>(act_t + (rec * n_hidden + l0) * W) + q;
             if (to_lds) *l = *gp; else *gp = *l;
         }
     };
     const int n_fwd = (ACT == kActLoad || !chain) ? 0 : n_hidden;   // layers the forward pass computes
-    if constexpr (W == 64 && SPLIT) {
-        // BF16 at width 64: every layer has the same 8 fragments (4 row blocks
+    if constexpr (SPLIT) {
+        // BF16: every layer has the same 8 fragments (4 row blocks
         // x 2 K chunks) and their lo parts.  The next layer's 16 load into
         // registers while this layer computes, so no layer waits for its
         // weights (measured: 15.9 -> 14.9 us per step; FP16, with half the
@@ -1442,21 +1326,24 @@ hipError_t fwd_fixed_launch(const void* ffr, const Src& src, int64_t tiles, int 
 // slower or equal (52.9 to 54.8 at 500,003).
 constexpr int kWideTilesPerCu = 6;
 
-template <typename T, int COLS, typename Src>
-hipError_t fwd_wide_launch(const Geo& d, const void* ffr, const Src& src, int64_t tiles, hipStream_t s) {
+template <typename T, int COLS, bool ACT, typename Src>
+hipError_t fwd_wide_launch(const Geo& d, const void* ffr, const Src& src, int64_t tiles, hipStream_t s, void* act,
+                           float* act_y) {
     const size_t lds = (size_t)d.n_fwd_frags() * 1024;
     int64_t blocks = tiles * (4 / COLS);
     if (blocks > device_cu_count()) blocks = device_cu_count();
-    auto k = k_fwd_wide<T, COLS, Src>;
+    auto k = k_fwd_wide<T, COLS, ACT, Src>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kWideWaves), lds, s, (const T*)ffr, d.n_fwd_frags(), src, d.H,
-                       d.F);
+                       d.F, (T*)act, act_y);
     return hipGetLastError();
 }
-template <typename T, typename Src>
-hipError_t fwd_wide(const Geo& d, const void* ffr, const Src& src, int64_t tiles, hipStream_t s) {
-    if (tiles <= (int64_t)kWideTilesPerCu * device_cu_count()) return fwd_wide_launch<T, 1>(d, ffr, src, tiles, s);
-    return fwd_wide_launch<T, 2>(d, ffr, src, tiles, s);
+template <typename T, bool ACT = false, typename Src>
+hipError_t fwd_wide(const Geo& d, const void* ffr, const Src& src, int64_t tiles, hipStream_t s, void* act = nullptr,
+                    float* act_y = nullptr) {
+    if (tiles <= (int64_t)kWideTilesPerCu * device_cu_count())
+        return fwd_wide_launch<T, 1, ACT>(d, ffr, src, tiles, s, act, act_y);
+    return fwd_wide_launch<T, 2, ACT>(d, ffr, src, tiles, s, act, act_y);
 }
 
 template <typename T, int W>
@@ -1579,42 +1466,42 @@ hipError_t fwd_raw_dispatch(const Geo& d, int preset, int layout, const void* ff
                                : fwd_raw_generic<T, W, NRC_PRESET_CONFIG, NRC_RAW16>(d, ffr, raw, n, rgb, s);
 }
 
-template <typename T, int W, bool UP, bool GE, int ACT = kActNone, int RAWL = -1, int PRESET = NRC_PRESET_CONFIG>
+template <typename T, bool UP, bool GE, int ACT = kActNone, int RAWL = -1, int PRESET = NRC_PRESET_CONFIG>
 hipError_t train_launch(const Geo& d, const void* ffr, const void* bfr, const void* enc,
                         const float* tgt, const int32_t* idx, int64_t n, float loss_eps, float grad_scale,
                         float* partials, float* loss_part, int32_t* tile_bad, float* genc,
                         hipStream_t s, void* act = nullptr, float* rgb = nullptr, LcgGather lg = LcgGather{}) {
-    using S = TrainShape<W>;
+    using S = TrainShape;
     const int64_t tiles = (n + S::TS - 1) / S::TS;
     if (tiles == 0) return hipSuccess;
-    const size_t lds = (size_t)train_lds_bytes(W, d.H);
-    auto k = k_train_mfma<T, W, UP, GE, ACT, RAWL, PRESET>;
+    const size_t lds = (size_t)train_lds_bytes(d.H, ACT == kActStore);
+    auto k = k_train_mfma<T, UP, GE, ACT, RAWL, PRESET>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(64 * (S::NW + train_helpers<W, ACT>())), lds, s, (const T*)ffr, (const T*)bfr,
+    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(64 * (S::NW + train_helpers<ACT>())), lds, s, (const T*)ffr, (const T*)bfr,
                        (const T*)enc, tgt, idx, n, d.H, loss_eps, grad_scale, partials, loss_part, tile_bad,
                        genc, d.F, (T*)act, rgb, lg);
     return hipGetLastError();
 }
 
-template <typename T, int W>
+template <typename T>
 hipError_t train_dispatch(const Geo& d, const void* ffr, const void* bfr, const void* enc,
                           const float* tgt, const int32_t* idx, int64_t n, bool upstream, float loss_eps,
                           float grad_scale, float* partials, float* loss_part, int32_t* tile_bad,
                           float* genc, hipStream_t s, const void* act, LcgGather lg) {
     if (!upstream)
-        return train_launch<T, W, false, false>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
+        return train_launch<T, false, false>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
                                                 partials, loss_part, tile_bad, genc, s, nullptr, nullptr, lg);
     if (act) {
         if (genc)
-            return train_launch<T, W, true, true, kActLoad>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
+            return train_launch<T, true, true, kActLoad>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
                                                             partials, loss_part, tile_bad, genc, s, (void*)act);
-        return train_launch<T, W, true, false, kActLoad>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
+        return train_launch<T, true, false, kActLoad>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
                                                          partials, loss_part, tile_bad, genc, s, (void*)act);
     }
     if (genc)
-        return train_launch<T, W, true, true>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
+        return train_launch<T, true, true>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
                                               partials, loss_part, tile_bad, genc, s);
-    return train_launch<T, W, true, false>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
+    return train_launch<T, true, false>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
                                            partials, loss_part, tile_bad, genc, s);
 }
 
@@ -1625,7 +1512,7 @@ hipError_t train_raw_dispatch(const Geo& d, int preset, int layout, const void* 
                               float grad_scale, float* partials, float* loss_part, int32_t* tile_bad,
                               hipStream_t s, LcgGather lg) {
 #define NRC_TRAIN_RAW(PR, LA)                                                                                 \
-    return train_launch<T, 64, false, false, kActNone, LA, PR>(d, ffr, bfr, raw, tgt, idx, n, loss_eps,      \
+    return train_launch<T, false, false, kActNone, LA, PR>(d, ffr, bfr, raw, tgt, idx, n, loss_eps,      \
                                                                grad_scale, partials, loss_part, tile_bad,     \
                                                                nullptr, s, nullptr, nullptr, lg)
     const bool r14 = layout == NRC_RAW14;
@@ -1658,13 +1545,6 @@ int device_cu_count() {
     return cus;
 }
 
-size_t mfma_train_lds_bytes(int width, int n_hidden) {
-    return (size_t)train_lds_bytes(width, n_hidden) + 16;
-}
-size_t mfma_fwd_lds_bytes(int width, int n_hidden) {
-    return (size_t)Geo(width, n_hidden).n_fwd_frags() * 64 * 16;
-}
-
 hipError_t launch_fwd_mfma(int precision, const Geo& d, const void* ffr, const void* enc,
                            int64_t n, float* rgb, hipStream_t s) {
     if (precision == NRC_FP16)
@@ -1692,20 +1572,25 @@ hipError_t launch_fwd_raw_mfma(int precision, const Geo& d, int preset, int layo
     return fwd_raw_dispatch<__bf16, 64>(d, preset, layout, ffr, raw, n, rgb, s);
 }
 
+// Where the activation buffer's network outputs start: past the rows of its last
+// 64-record (width 128: 32-record) tile.
+static float* act_outputs(const Geo& d, const void* act, int64_t n) {
+    const int64_t ts = train_tile(NRC_FP16, d.W), rows = (n + ts - 1) / ts * ts;
+    return act ? (float*)((char*)act + rows * d.H * d.W * 2) : nullptr;
+}
+
 hipError_t launch_train_mfma(int precision, const Geo& d, const void* ffr, const void* bfr,
                              const void* enc, const float* tgt, const int32_t* idx, int64_t n, bool upstream,
                              float loss_eps, float grad_scale, float* partials, float* loss_part,
                              int32_t* tile_bad, float* genc, hipStream_t s, const void* act, LcgGather lg) {
+    if (train_in_tiles(d, n))
+        return launch_train_tiles(precision, d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps, grad_scale, partials,
+                                  loss_part, tile_bad, genc, s, act, act_outputs(d, act, n), lg);
     if (precision == NRC_FP16)
-        return d.W == 64 ? train_dispatch<_Float16, 64>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps,
-                                                        grad_scale, partials, loss_part, tile_bad, genc, s, act, lg)
-                         : train_dispatch<_Float16, 128>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps,
-                                                         grad_scale, partials, loss_part, tile_bad, genc, s, act,
-                                                         lg);
-    return d.W == 64 ? train_dispatch<__bf16, 64>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps,
-                                                  grad_scale, partials, loss_part, tile_bad, genc, s, act, lg)
-                     : train_dispatch<__bf16, 128>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps,
-                                                   grad_scale, partials, loss_part, tile_bad, genc, s, act, lg);
+        return train_dispatch<_Float16>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps, grad_scale, partials,
+                                        loss_part, tile_bad, genc, s, act, lg);
+    return train_dispatch<__bf16>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps, grad_scale, partials,
+                                  loss_part, tile_bad, genc, s, act, lg);
 }
 
 hipError_t launch_train_mfma_raw(int precision, const Geo& d, int preset, int layout, const void* ffr,
@@ -1713,6 +1598,9 @@ hipError_t launch_train_mfma_raw(int precision, const Geo& d, int preset, int la
                                  int64_t n, float loss_eps, float grad_scale, float* partials, float* loss_part,
                                  int32_t* tile_bad, hipStream_t s, LcgGather lg) {
     if (d.W != 64) return hipErrorInvalidValue;
+    if (train_in_tiles(d, n))
+        return launch_train_tiles_raw(precision, d, preset, layout, ffr, bfr, raw, tgt, idx, n, loss_eps, grad_scale,
+                                      partials, loss_part, tile_bad, s, lg);
     if (precision == NRC_FP16)
         return train_raw_dispatch<_Float16>(d, preset, layout, ffr, bfr, raw, tgt, idx, n, loss_eps, grad_scale,
                                             partials, loss_part, tile_bad, s, lg);
@@ -1720,20 +1608,23 @@ hipError_t launch_train_mfma_raw(int precision, const Geo& d, int preset, int la
                                       partials, loss_part, tile_bad, s, lg);
 }
 
-template <typename T, int W>
+template <typename T>
 hipError_t fwd_train_dispatch(const Geo& d, const void* ffr, const void* enc, int64_t n, void* act, float* rgb,
                               hipStream_t s) {
-    return train_launch<T, W, true, false, kActStore>(d, ffr, nullptr, enc, nullptr, nullptr, n, 0.0f, 1.0f,
-                                                      nullptr, nullptr, nullptr, nullptr, s, act, rgb);
+    if (d.W == 128) {
+        if constexpr (__is_same(T, __bf16))
+            return launch_fwd_train_tiles_bf16(d, ffr, enc, n, act, act_outputs(d, act, n), rgb, s);
+        else
+            return fwd_wide<T, true>(d, ffr, EncBatch{enc, n, rgb}, (n + 63) / 64, s, act, act_outputs(d, act, n));
+    }
+    return train_launch<T, true, false, kActStore>(d, ffr, nullptr, enc, nullptr, nullptr, n, 0.0f, 1.0f,
+                                                   nullptr, nullptr, nullptr, nullptr, s, act, rgb);
 }
 
 hipError_t launch_fwd_train_mfma(int precision, const Geo& d, const void* ffr, const void* enc, int64_t n,
                                  void* act, float* rgb, hipStream_t s) {
-    if (precision == NRC_FP16)
-        return d.W == 64 ? fwd_train_dispatch<_Float16, 64>(d, ffr, enc, n, act, rgb, s)
-                         : fwd_train_dispatch<_Float16, 128>(d, ffr, enc, n, act, rgb, s);
-    return d.W == 64 ? fwd_train_dispatch<__bf16, 64>(d, ffr, enc, n, act, rgb, s)
-                     : fwd_train_dispatch<__bf16, 128>(d, ffr, enc, n, act, rgb, s);
+    if (precision == NRC_FP16) return fwd_train_dispatch<_Float16>(d, ffr, enc, n, act, rgb, s);
+    return fwd_train_dispatch<__bf16>(d, ffr, enc, n, act, rgb, s);
 }
 
 }  // namespace nrc

@@ -137,6 +137,12 @@ Geo kernel_geo(const nrc_config& c) {
     return d;
 }
 
+// Weight-gradient partials a step over n records writes: one per tile, or one
+// per workgroup where workgroups take several tiles.
+static int64_t step_parts(const nrc_config& c, const Geo& d, int64_t n, const ScratchLayout& sl) {
+    return !fp32_form(c.precision) && train_in_tiles(d, n) ? train_parts(d, n) : sl.tiles;
+}
+
 // Enqueue one training step (forward, loss, backward, reduction, Adam) on s.
 int enqueue_train_step(nrc_cache* c, const void* enc, const float* target, const int32_t* idx,
                        int64_t n, char* scratch, float* loss_dev, int32_t* skipped_dev, hipStream_t s,
@@ -175,8 +181,8 @@ int enqueue_train_step(nrc_cache* c, const void* enc, const float* target, const
     int32_t* skipped_out = skipped_dev ? skipped_dev : (int32_t*)(scratch + sl.skipped);
     const AdamHyper hp{cfg.lr, cfg.beta1, cfg.beta2, cfg.adam_eps};
     const EmaArgs ema{c->ema() ? cfg.ema_alpha : 0.0f, c->e(), c->wbar(), c->effr()};
-    e = launch_reduce_adam(cfg.precision, d, !fp32_form(cfg.precision), partials, (int)sl.tiles,
-                           tile_bad, loss_part, (float)(1.0 / (3.0 * (double)n)), loss_out,
+    e = launch_reduce_adam(cfg.precision, d, !fp32_form(cfg.precision), partials, (int)step_parts(cfg, d, n, sl),
+                           tile_bad, loss_part, (int)((n + 63) / 64), (float)(1.0 / (3.0 * (double)n)), loss_out,
                            1.0f / scale, c->w(), c->m(), c->v(), c->tslots(), c->parity, hp, ema,
                            skipped_out, c->ffr(), c->bfr(), s);
     if (e != hipSuccess) return device_fail(e, "gradient reduction / Adam launch");
@@ -554,8 +560,7 @@ int nrc_backward(nrc_cache* cache, const void* enc, const void* act_ws, const fl
         e = launch_train_mfma(cfg.precision, d, cache->ffr(), cache->bfr(), enc, grad_rgb, nullptr, n, true,
                               cfg.loss_eps, scale, partials, loss_part, tile_bad, grad_enc, s, act_ws);
     if (e != hipSuccess) return device_fail(e, "backward kernel launch");
-    e = launch_reduce(d, !fp32_form(cfg.precision), partials, (int)sl.tiles, 1.0f / scale, grad_w, loss_part,
-                      1.0f, nullptr, s);
+    e = launch_reduce(d, !fp32_form(cfg.precision), partials, (int)step_parts(cfg, d, n, sl), 1.0f / scale, grad_w, s);
     if (e != hipSuccess) return device_fail(e, "gradient reduction launch");
     return ok();
 }

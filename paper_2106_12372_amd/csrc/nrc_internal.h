@@ -277,18 +277,34 @@ hipError_t launch_train_mfma(int precision, const Geo& d, const void* ffr, const
 // (act_bytes_mfma / act_bytes_fp32 bytes) for a later backward.
 hipError_t launch_fwd_train_mfma(int precision, const Geo& d, const void* ffr, const void* enc, int64_t n,
                                  void* act, float* rgb, hipStream_t s);
+// train_tiles.hip: the FP16/BF16 trainer over more tiles than compute units
+// (and always at width 128).  It writes train_parts(d, n) partials and flags,
+// and a loss term for each 64 records.  Arguments as launch_train_mfma and
+// launch_train_mfma_raw; act_y: the network outputs of the activation buffer.
+bool train_in_tiles(const Geo& d, int64_t n);
+int64_t train_parts(const Geo& d, int64_t n);
+hipError_t launch_train_tiles(int precision, const Geo& d, const void* ffr, const void* bfr, const void* enc,
+                              const float* tgt, const int32_t* idx, int64_t n, bool upstream, float loss_eps,
+                              float grad_scale, float* partials, float* loss_part, int32_t* part_bad, float* genc,
+                              hipStream_t s, const void* act, const float* act_y, LcgGather lg);
+// The forward pass of the autograd form for BF16 at width 128: the training
+// weights are pairs (hi, lo), whose fragments do not fit in LDS together.
+hipError_t launch_fwd_train_tiles_bf16(const Geo& d, const void* ffr, const void* enc, int64_t n, void* act,
+                                       float* act_y, float* rgb, hipStream_t s);
+hipError_t launch_train_tiles_raw(int precision, const Geo& d, int preset, int layout, const void* ffr,
+                                  const void* bfr, const float* raw, const float* tgt, const int32_t* idx, int64_t n,
+                                  float loss_eps, float grad_scale, float* partials, float* loss_part,
+                                  int32_t* part_bad, hipStream_t s, LcgGather lg);
 size_t fp32_train_lds_bytes(int n_hidden);
-size_t mfma_train_lds_bytes(int width, int n_hidden);
-size_t mfma_fwd_lds_bytes(int width, int n_hidden);
 // optim.hip
 int reduce_blocks(int n_params);
 // `native`: the partials use the matrix-core accumulator layout (see
 // k_train_mfma) instead of row-major [out][in].
-hipError_t launch_reduce(const Geo& d, bool native, const float* partials, int n_tiles,
-                         float inv_scale, float* grad, const float* loss_part, float inv_count,
-                         float* loss_out, hipStream_t s);
-hipError_t launch_reduce_adam(int precision, const Geo& d, bool native, const float* partials, int n_tiles,
-                              const int32_t* tile_bad, const float* loss_part, float inv_count,
+// n_parts partials (and flags), n_loss loss terms.
+hipError_t launch_reduce(const Geo& d, bool native, const float* partials, int n_parts,
+                         float inv_scale, float* grad, hipStream_t s);
+hipError_t launch_reduce_adam(int precision, const Geo& d, bool native, const float* partials, int n_parts,
+                              const int32_t* tile_bad, const float* loss_part, int n_loss, float inv_count,
                               float* loss_out, float inv_scale, float* w, float* m, float* v,
                               int32_t* tslots, int parity, AdamHyper hp, EmaArgs ema,
                               int32_t* skipped_out, void* ffr, void* bfr, hipStream_t s);

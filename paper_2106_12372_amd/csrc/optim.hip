@@ -92,8 +92,8 @@ constexpr int kRedGroups = 8;    // tile groups per workgroup
 template <typename T, bool ADAM, bool NATIVE>
 __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partials, int n_tiles,
                                                 const int32_t* __restrict__ tile_bad,
-                                                const float* __restrict__ loss_part, float inv_count,
-                                                float* __restrict__ loss_out, float inv_scale,
+                                                const float* __restrict__ loss_part, int n_loss,
+                                                float inv_count, float* __restrict__ loss_out, float inv_scale,
                                                 float* __restrict__ grad_out, float* __restrict__ w,
                                                 float* __restrict__ m, float* __restrict__ v,
                                                 int32_t* __restrict__ tslots, int parity, AdamHyper hp,
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
     if (loss_wave) {
         #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (lane + 64 * u < n_tiles) lv[u] = loss_part[lane + 64 * u];
+            if (lane + 64 * u < n_loss) lv[u] = loss_part[lane + 64 * u];
     }
     // Bias corrections of the step this update would make (a skipped step
     // updates nothing) and the weight's fragment slots, evaluated while the
@@ -191,8 +191,8 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
         float ls = 0.0f, lc = 0.0f;
         #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (lane + 64 * u < n_tiles) neumaier_add(ls, lc, lv[u]);
-        for (int t = lane + 256; t < n_tiles; t += 64) neumaier_add(ls, lc, loss_part[t]);
+            if (lane + 64 * u < n_loss) neumaier_add(ls, lc, lv[u]);
+        for (int t = lane + 256; t < n_loss; t += 64) neumaier_add(ls, lc, loss_part[t]);
         #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
             const float os = __shfl_xor(ls, off, 64), oc = __shfl_xor(lc, off, 64);
@@ -295,33 +295,32 @@ __global__ __launch_bounds__(256) void k_install(const float* src, float* w, flo
 
 int reduce_blocks(int n_params) { return (n_params + kRedParams - 1) / kRedParams; }
 
-hipError_t launch_reduce(const Geo& d, bool native, const float* partials, int n_tiles,
-                         float inv_scale, float* grad, const float* loss_part, float inv_count,
-                         float* loss_out, hipStream_t s) {
+hipError_t launch_reduce(const Geo& d, bool native, const float* partials, int n_parts,
+                         float inv_scale, float* grad, hipStream_t s) {
     const dim3 grid(reduce_blocks(d.n_params())), block(256);
     auto k = native ? k_reduce<_Float16, false, true> : k_reduce<_Float16, false, false>;
-    hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_tiles, (const int32_t*)nullptr, loss_part,
-                       inv_count, loss_out, inv_scale, grad, (float*)nullptr, (float*)nullptr,
+    hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_parts, (const int32_t*)nullptr,
+                       (const float*)nullptr, 0, 1.0f, (float*)nullptr, inv_scale, grad, (float*)nullptr, (float*)nullptr,
                        (float*)nullptr, (int32_t*)nullptr, 0, AdamHyper{}, EmaArgs{},
                        (int32_t*)nullptr, (_Float16*)nullptr, (_Float16*)nullptr, d.W, d.H);
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_adam(int precision, const Geo& d, bool native, const float* partials,
-                              int n_tiles, const int32_t* tile_bad, const float* loss_part,
+                              int n_parts, const int32_t* tile_bad, const float* loss_part, int n_loss,
                               float inv_count, float* loss_out, float inv_scale, float* w, float* m,
                               float* v, int32_t* tslots, int parity, AdamHyper hp, EmaArgs ema,
                               int32_t* skipped_out, void* ffr, void* bfr, hipStream_t s) {
     const dim3 grid(reduce_blocks(d.n_params())), block(256);
     if (precision == NRC_BF16) {
         auto k = native ? k_reduce<__bf16, true, true> : k_reduce<__bf16, true, false>;
-        hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_tiles, tile_bad, loss_part, inv_count,
+        hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_parts, tile_bad, loss_part, n_loss, inv_count,
                            loss_out, inv_scale, (float*)nullptr, w, m, v, tslots, parity, hp, ema,
                            skipped_out, (__bf16*)ffr, (__bf16*)bfr, d.W, d.H);
     } else {
         // FP32 caches have no reduced-precision copies (ffr, bfr, ema.effr are NULL).
         auto k = native ? k_reduce<_Float16, true, true> : k_reduce<_Float16, true, false>;
-        hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_tiles, tile_bad, loss_part, inv_count,
+        hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_parts, tile_bad, loss_part, n_loss, inv_count,
                            loss_out, inv_scale, (float*)nullptr, w, m, v, tslots, parity, hp, ema,
                            skipped_out, (_Float16*)ffr, (_Float16*)bfr, d.W, d.H);
     }

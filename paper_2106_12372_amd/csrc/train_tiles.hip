@@ -1,0 +1,616 @@
+// Training over many records in the FP16/BF16 matrix-core forms: forward pass,
+// loss gradient of Eq. 5 (or an upstream gradient), data backward pass and
+// weight gradients, with the weight gradients of all a workgroup's tiles summed
+// in registers.
+//
+// A workgroup of 8 waves takes 64-record tiles one after another.  In every
+// layer a wave owns one 16-row block of the output for NC of the tile's four
+// 16-record columns, so a weight fragment is read by one wave per tile (two at
+// width 64; every wave that holds records in k_train_mfma) and goes from L2 to
+// registers while the wave waits for the layer before.  Activations and deltas pass between the waves
+// through LDS, record-major, each 32-feature chunk of a row in the order of the
+// operand slots ("chained" order, nrc_internal.h): the B operand of the next
+// product is one 16-byte read.  Only two layers' deltas are held.  While the
+// waves form delta_l they also form dW_l = delta_{l+1} h_l^T over the tile's 64
+// records, the record index along K by LDS transpose reads, into accumulators
+// that stay in registers from tile to tile.  Each workgroup writes its sums
+// once, in the accumulator layout the reduction expects, so the partials no
+// longer grow with the batch.
+//
+// Every record's forward pass, loss and deltas go through the same products in
+// the same order as in k_train_mfma; only the grouping of the records' weight
+// gradients differs.
+//
+// Bound by LDS traffic and the barrier between layers.  Cycle stamps of a tile:
+// width 128 (FP16) 28k cycles, 1.9k per forward layer, 3.2k per backward layer
+// with its weight gradient; width 64, two workgroups per CU, 15k, 0.9k and 1.4k.
+// The partials' one write takes 27k cycles at width 128 (76 MB over the chip, at
+// the rate of a copy).  Whole training steps, us, k_train_mfma before and now:
+// width 64 FP16 65,536 records 48 / 34, 262,144 183 / 88, BF16 262,144 232 / 96;
+// width 128 FP16 1,000 records 53 / 28, 16,384 97 / 45, 65,536 306 / 78, BF16
+// 65,536 438 / 100.  At width 128 a wave with two row blocks and two columns
+// instead of one and four was slower (83 and 134 us: its fragments spill).
+#include "mfma_ops.h"
+#include "nrc_internal.h"
+
+namespace nrc {
+namespace {
+
+constexpr int kTS = 64;           // records per tile
+constexpr int kWaves = 8;
+constexpr int kLd0 = 72;          // LDS row strides, elements: h_0
+constexpr int kLdT = 72;          // dL/dy, feature-major
+
+__host__ __device__ constexpr int row_stride(int W) { return W + 8; }
+// LDS bytes: h_0 [64][72], h_1 .. h_H and two deltas [64][W + 8], dL/dy
+// feature-major [3][72] and record-major [64][4], network outputs [64][4] (FP32).
+__host__ __device__ constexpr int tiles_lds_bytes(int W, int H) {
+    return (kTS * (kLd0 + (H + 2) * row_stride(W)) + 3 * kLdT + kTS * 4) * 2 + kTS * 16;
+}
+
+// UPSTREAM, GENC, RAWL, PRESET as in k_train_mfma.  ACT: kActLoad reads the
+// forward pass from the activation buffer ([record][layer][feature], and the
+// network outputs [record][4]) instead of computing it; kActStore computes it,
+// writes the buffer and the predictions (to out) and stops there.  out: dL/d(input)
+// in the GENC forms.  MAXH: the most hidden layers the accumulators hold.
+constexpr int kActNone = 0, kActStore = 1, kActLoad = 2;
+
+template <typename T, int W, int MAXH, bool UPSTREAM, bool GENC, int ACT, int RAWL, int PRESET>
+__global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_train_tiles(const T* __restrict__ ffr, const T* __restrict__ bfr,
+                                                             const T* __restrict__ enc,
+                                                             const float* __restrict__ tgt,
+                                                             const int32_t* __restrict__ idx, int64_t n, int n_hidden,
+                                                             float loss_eps, float grad_scale,
+                                                             float* __restrict__ partials,
+                                                             float* __restrict__ loss_part,
+                                                             int32_t* __restrict__ part_bad,
+                                                             float* __restrict__ out, int fcol,
+                                                             T* __restrict__ act, float* __restrict__ act_y,
+                                                             LcgGather lg) {
+    using V = typename Vec8<T>::type;
+    typedef T t4 __attribute__((ext_vector_type(4)));
+    constexpr bool SPLIT = __is_same(T, __bf16);
+    constexpr int MB = W / 16, KC = W / 32, LDR = row_stride(W);
+    constexpr int RG = W / 16, NC = W / 32;                  // waves: RG row blocks x (8 / RG) groups of NC columns
+    constexpr int NTH = 64 * kWaves;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    __shared__ float wsum[4];
+    // every region at a fixed offset, the activations last
+    T* h0 = reinterpret_cast<T*>(smem_raw);
+    T* dO = h0 + kTS * kLd0;                                 // dL/dy [3][kLdT]
+    T* dR = dO + 3 * kLdT;                                   // dL/dy [64][4]
+    float* fy = reinterpret_cast<float*>(dR + kTS * 4);      // network outputs [64][4]
+    T* ds = reinterpret_cast<T*>(fy + kTS * 4);              // delta_l in block l & 1
+    T* hs = ds + 2 * kTS * LDR;                              // h_1 .. h_H
+    auto hrow = [&](int l) { return hs + (l - 1) * kTS * LDR; };
+    auto drow = [&](int l) { return ds + (l & 1) * kTS * LDR; };
+
+    const Geo geo(W, n_hidden);
+    const int P = geo.n_params();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, ln = lane & 15;
+    const int rb = wave % RG, col0 = (wave / RG) * NC;
+    const int lo_f = geo.n_fwd_frags() * 64, lo_b = geo.n_bwd_frags() * 64;
+
+    // A product's weight operand, hi part and (BF16) lo part.
+    struct Frag { V hi, lo; };
+    auto ld = [&](const V* f, int lo) {
+        Frag r;
+        r.hi = *f;
+        if (SPLIT) r.lo = f[lo];
+        return r;
+    };
+    auto mm = [&](const Frag& a, const V& b, f32x4 c) {
+        c = mfma(a.hi, b, c);
+        if (SPLIT) c = mfma(a.lo, b, c);
+        return c;
+    };
+    const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+    // This wave's fragments of a layer, loaded while the layer before finishes.
+    Frag fr[KC];
+    auto load_frags = [&](const V* base, int kc, int row, int lo) {
+        #pragma unroll
+        for (int c = 0; c < KC; ++c)
+            if (c < kc) fr[c] = ld(base + (row * kc + c) * 64, lo);
+    };
+    // The four values of this wave's row block a lane holds of column col, into a
+    // row store.
+    auto put = [&](T* rows, int col, f32x4 v, bool relu_it) {
+        T* dst = rows + (16 * col + ln) * LDR + 32 * (rb >> 1) + 8 * g + 4 * (rb & 1);
+        const V p = pack8<T, V>(v, v);
+        const V q = relu_it ? relu_packed(p) : p;
+        *reinterpret_cast<t4*>(dst) = __builtin_shufflevector(q, q, 0, 1, 2, 3);
+    };
+    // B operand chunk c of column col from a row store in slot order.
+    auto get = [&](const T* rows, int stride, int col, int c) {
+        return *reinterpret_cast<const V*>(rows + (16 * col + ln) * stride + 32 * c + 8 * g);
+    };
+    // Operand of records 32 kc + 8 g .. +7 for row positions 16 blk + ln of a
+    // record-major store (the transpose read of k_train_mfma).
+    auto gather = [&](const T* base, int stride, int blk, int kc) {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const T* p = base + (32 * kc + 8 * g + (ln >> 2)) * stride + 16 * blk + 4 * (ln & 3);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * stride));
+        return __builtin_bit_cast(V, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+
+    // Weight-gradient accumulators.  Layer l >= 1: row blocks MW (wave >> 2) ..,
+    // column blocks NW (wave & 3) ..; layer 0 (64 columns): one column block,
+    // wave & 3; output layer: column blocks wave, wave + 8 (waves 0 .. MB - 1).
+    constexpr int MW = MB / 2, NW = MB / 4;
+    const int mw0 = (wave >> 2) * MW, nw0 = (wave & 3) * NW;
+    f32x4 acc0[MW], accw[MAXH > 1 ? MAXH - 1 : 1][MW][NW], acco = zero;
+    #pragma unroll
+    for (int i = 0; i < MW; ++i) {
+        acc0[i] = zero;
+        #pragma unroll
+        for (int l = 0; l < MAXH - 1; ++l)
+            #pragma unroll
+            for (int j = 0; j < NW; ++j) accw[l][i][j] = zero;
+    }
+
+    // The weights are read anew for each tile, and what only a part of the tile
+    // needs is computed there: held in registers across the tiles (their loads and
+    // addresses are loop-invariant) they would spill the accumulators.
+    auto anew = [](int v) {
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+    // Encoded rows: a thread moves 16 bytes of record tid / 8, and the output lanes
+    // their record's targets; both are loaded during the tile before.
+    const int64_t n_tiles = (n + kTS - 1) / kTS;
+    V in_v = zero8<V>();
+    float tg[3] = {0.f, 0.f, 0.f};
+    int src_e = -1, src_t = -1;              // n <= 2^31
+    auto find = [&](int64_t t) {             // the records behind tile t's slots (-1: none)
+        const int ft = anew(tid);
+        const int64_t re = t * kTS + (ft >> 3), rt = t * kTS + 16 * wave + (ft & 15);
+        src_e = re < n ? (int)gather_row(idx, lg, re) : -1;
+        src_t = wave < 4 && g == 0 && rt < n ? (int)gather_row(idx, lg, rt) : -1;
+    };
+    auto fetch = [&] {
+        in_v = zero8<V>();
+        if (src_e >= 0) in_v = *reinterpret_cast<const V*>(enc + (int64_t)src_e * kEncWidth + 8 * (anew(tid) & 7));
+        #pragma unroll
+        for (int c = 0; c < 3; ++c) tg[c] = ACT != kActStore && src_t >= 0 ? tgt[(int64_t)src_t * 3 + c] : 0.0f;
+    };
+    if constexpr (RAWL < 0) {
+        find(blockIdx.x);
+        fetch();
+    }
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const int fresh = anew(lane);
+        const V* gf = reinterpret_cast<const V*>(ffr) + fresh;
+        const V* gb = reinterpret_cast<const V*>(bfr) + fresh;
+        // ---- h_0, targets ------------------------------------------------------
+        const bool out_wave = wave < 4;                      // holds the outputs of records 16 wave ..
+        const int sl = 16 * (wave & 3) + ln;
+        const int64_t row = tile * kTS + sl;
+        const bool valid = row < n;
+        if constexpr (RAWL >= 0) {
+            constexpr int RW = RAWL == NRC_RAW14 ? 14 : 16;
+            if (out_wave) {
+                const int64_t src = valid ? gather_row(idx, lg, row) : 0;
+                float x[RW];
+                const float* rr = reinterpret_cast<const float*>(enc) + src * RW;
+                #pragma unroll
+                for (int k = 0; k < RW; ++k) x[k] = valid ? rr[k] : 0.0f;
+                if (g == 0 && valid) {
+                    #pragma unroll
+                    for (int c = 0; c < 3; ++c) tg[c] = tgt[src * 3 + c];
+                }
+                encode_shared<T, PRESET, RAWL>(x, h0 + sl * kLd0, g, valid);
+            }
+        } else {
+            const int ft = anew(tid);
+            *reinterpret_cast<V*>(h0 + (ft >> 3) * kLd0 + 8 * (ft & 7)) = in_v;
+            find(tile + gridDim.x);
+        }
+        f32x4 y = zero;
+        if constexpr (ACT == kActLoad) {
+            // a thread moves 16 bytes (8 consecutive features: two operand-slot
+            // groups of 4) of NR records per layer, a batch of layers' loads in flight
+            constexpr int CPR = W / 8, NR = kTS * CPR / NTH;
+            const int ft = anew(tid), q = ft % CPR, rec0 = ft / CPR;
+            // features 8q .. +3 and +4 .. +7 sit in slots (g', i') and (g' + 1, i')
+            const int rq = (8 * q) & 31, gq = (rq & 15) >> 2, iq = rq < 16 ? 0 : 4;
+            constexpr int LB = W == 128 ? 2 : MAXH;          // layers per batch of loads
+            #pragma unroll
+            for (int lb = 0; lb < MAXH; lb += LB) {
+                V v[LB][NR];
+                #pragma unroll
+                for (int u = 0; u < LB; ++u)
+                    #pragma unroll
+                    for (int k = 0; k < NR; ++k) {
+                        const int64_t ar = tile * kTS + rec0 + k * (NTH / CPR);
+                        v[u][k] = zero8<V>();
+                        if (lb + u < n_hidden && ar < n)
+                            v[u][k] = *reinterpret_cast<const V*>(act + (ar * n_hidden + lb + u) * W + 8 * q);
+                    }
+                #pragma unroll
+                for (int u = 0; u < LB; ++u)
+                    #pragma unroll
+                    for (int k = 0; k < NR; ++k)
+                        if (lb + u < n_hidden) {
+                            const V x = v[u][k];
+                            T* dst = hrow(lb + u + 1) + (rec0 + k * (NTH / CPR)) * LDR + 32 * (q >> 2) + 8 * gq + iq;
+                            *reinterpret_cast<t4*>(dst) = __builtin_shufflevector(x, x, 0, 1, 2, 3);
+                            *reinterpret_cast<t4*>(dst + 8) = __builtin_shufflevector(x, x, 4, 5, 6, 7);
+                        }
+            }
+            if (out_wave && g == 0 && valid) {
+                #pragma unroll
+                for (int c = 0; c < 3; ++c) y[c] = act_y[row * 4 + c];
+            }
+            __syncthreads();
+        } else {
+            // ---- forward -------------------------------------------------------
+            load_frags(gf, 2, rb, lo_f);
+            __syncthreads();                                 // h_0 is in LDS
+            auto layer = [&](const T* in, int stride, auto kc_, int l) {
+                constexpr int kc = decltype(kc_)::value;
+                f32x4 a[NC];
+                #pragma unroll
+                for (int c = 0; c < kc; ++c)
+                    #pragma unroll
+                    for (int col = 0; col < NC; ++col)
+                        a[col] = mm(fr[c], get(in, stride, col0 + col, c), c == 0 ? zero : a[col]);
+                // the next layer's weights are on their way before the barrier
+                if (l + 1 < n_hidden)
+                    load_frags(gf + geo.fwd_base(l + 1) * 64, KC, rb, lo_f);
+                else if (out_wave)
+                    load_frags(gf + geo.fwd_base(n_hidden) * 64, KC, 0, lo_f);
+                #pragma unroll
+                for (int col = 0; col < NC; ++col) put(hrow(l + 1), col0 + col, a[col], true);
+                __syncthreads();                             // h_{l+1} is in LDS
+            };
+            layer(h0, kLd0, IntC<2>{}, 0);
+            for (int l = 1; l < n_hidden; ++l) layer(hrow(l), LDR, IntC<KC>{}, l);
+            if (out_wave) {
+                #pragma unroll
+                for (int c = 0; c < KC; ++c) y = mm(fr[c], get(hrow(n_hidden), LDR, wave, c), y);
+            }
+        }
+        if constexpr (ACT == kActStore) {
+            fetch();                                         // the next tile's rows
+            if (out_wave) {
+                float r[3];
+                reflectance_operand(*reinterpret_cast<const V*>(h0 + sl * kLd0 + 32 + 8 * g), fcol, ln, r);
+                if (g == 0 && valid) {
+                    #pragma unroll
+                    for (int c = 0; c < 3; ++c) out[row * 3 + c] = y[c] * r[c];
+                    *reinterpret_cast<f32x4*>(act_y + row * 4) = f32x4{y[0], y[1], y[2], 0.0f};
+                }
+            }
+            // 16 bytes (8 consecutive features) of a record's layer per thread
+            constexpr int CPR = W / 8;
+            const int q = tid % CPR, rq = (8 * q) & 31, gq = (rq & 15) >> 2, iq = rq < 16 ? 0 : 4;
+            for (int l = 0; l < n_hidden; ++l)
+                #pragma unroll
+                for (int rec = tid / CPR; rec < kTS; rec += NTH / CPR) {
+                    const int64_t ar = tile * kTS + rec;
+                    const T* p = hrow(l + 1) + rec * LDR + 32 * (q >> 2) + 8 * gq + iq;
+                    const t4 a = *reinterpret_cast<const t4*>(p), b = *reinterpret_cast<const t4*>(p + 8);
+                    if (ar < n)
+                        *reinterpret_cast<V*>(act + (ar * n_hidden + l) * W + 8 * q) =
+                            __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+                }
+            __syncthreads();                                 // h_0 .. h_H have been read
+            continue;
+        }
+        // delta_H's weights: K = 32, one fragment per row block
+        fr[0] = ld(gb + (geo.bwd_base(n_hidden) + rb) * 64, lo_b);
+
+        // ---- loss gradient (Eq. 5) in lanes 0 .. 15 of waves 0 .. 3 --------------
+        float lterm = 0.0f;
+        if (out_wave) {
+            float r[3];
+            reflectance_operand(*reinterpret_cast<const V*>(h0 + sl * kLd0 + 32 + 8 * g), fcol, ln, r);
+            float d0 = 0.f, d1 = 0.f, d2 = 0.f;
+            if (g == 0 && valid) {
+                if (UPSTREAM) {
+                    d0 = tg[0] * grad_scale * r[0];
+                    d1 = tg[1] * grad_scale * r[1];
+                    d2 = tg[2] * grad_scale * r[2];
+                } else {
+                    const float p0 = y[0] * r[0], p1 = y[1] * r[1], p2 = y[2] * r[2];
+                    const float lum = (p0 + p1 + p2) * (1.0f / 3.0f);
+                    const float inv_den = 1.0f / fmaf(lum, lum, loss_eps);
+                    const float e0 = p0 - tg[0];
+                    const float e1 = p1 - tg[1];
+                    const float e2 = p2 - tg[2];
+                    lterm = fmaf(e2, e2, fmaf(e1, e1, e0 * e0)) * inv_den;
+                    d0 = 2.0f * e0 * inv_den * grad_scale * r[0];
+                    d1 = 2.0f * e1 * inv_den * grad_scale * r[1];
+                    d2 = 2.0f * e2 * inv_den * grad_scale * r[2];
+                }
+            }
+            if (g == 0) {
+                const t4 d = t4{to_t<T>(d0), to_t<T>(d1), to_t<T>(d2), (T)0};
+                dO[0 * kLdT + sl] = d[0];
+                dO[1 * kLdT + sl] = d[1];
+                dO[2 * kLdT + sl] = d[2];
+                *reinterpret_cast<t4*>(dR + sl * 4) = d;
+                if (GENC) *reinterpret_cast<f32x4*>(fy + sl * 4) = y;
+            }
+        }
+        __syncthreads();                                     // dL/dy is in LDS
+        if constexpr (RAWL < 0) fetch();                     // the next tile's rows and targets
+
+        // ---- data backward and weight gradients --------------------------------
+        // delta_l masked by ReLU'(z_l) into its row store
+        auto put_delta = [&](int l, const f32x4 (&a)[NC]) {
+            #pragma unroll
+            for (int col = 0; col < NC; ++col) {
+                const t4 hv = *reinterpret_cast<const t4*>(hrow(l) + (16 * (col0 + col) + ln) * LDR + 32 * (rb >> 1) +
+                                                           8 * g + 4 * (rb & 1));
+                f32x4 v;
+                #pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = (float)hv[j] > 0.0f ? a[col][j] : 0.0f;
+                put(drow(l), col0 + col, v, false);
+            }
+        };
+        {
+            f32x4 a[NC];
+            #pragma unroll
+            for (int col = 0; col < NC; ++col) {
+                V bd = zero8<V>();
+                const t4 d = *reinterpret_cast<const t4*>(dR + (16 * (col0 + col) + ln) * 4);
+                if (g == 0) { bd[0] = d[0]; bd[1] = d[1]; bd[2] = d[2]; }
+                a[col] = mm(fr[0], bd, zero);
+            }
+            if (n_hidden > 1) load_frags(gb + geo.bwd_base(n_hidden - 1) * 64, KC, rb, lo_b);
+            put_delta(n_hidden, a);
+            if (wave < MB) {
+                #pragma unroll
+                for (int kc = 0; kc < 2; ++kc) {
+                    const V av = ln < kNOut ? *reinterpret_cast<const V*>(dO + ln * kLdT + 32 * kc + 8 * g) : zero8<V>();
+                    acco = mfma(av, gather(hrow(n_hidden), LDR, wave, kc), acco);
+                }
+            }
+        }
+        __syncthreads();                                     // delta_H is in LDS
+        #pragma unroll
+        for (int l = MAXH - 1; l >= 1; --l) {
+            if (l < n_hidden) {
+                f32x4 a[NC];
+                #pragma unroll
+                for (int c = 0; c < KC; ++c)
+                    #pragma unroll
+                    for (int col = 0; col < NC; ++col)
+                        a[col] = mm(fr[c], get(drow(l + 1), LDR, col0 + col, c), c == 0 ? zero : a[col]);
+                if (l > 1) load_frags(gb + geo.bwd_base(l - 1) * 64, KC, rb, lo_b);
+                put_delta(l, a);
+                #pragma unroll
+                for (int kc = 0; kc < 2; ++kc) {
+                    V bw[NW];
+                    #pragma unroll
+                    for (int j = 0; j < NW; ++j) bw[j] = gather(hrow(l), LDR, nw0 + j, kc);
+                    #pragma unroll
+                    for (int i = 0; i < MW; ++i) {
+                        const V aw = gather(drow(l + 1), LDR, mw0 + i, kc);
+                        #pragma unroll
+                        for (int j = 0; j < NW; ++j) accw[l - 1][i][j] = mfma(aw, bw[j], accw[l - 1][i][j]);
+                    }
+                }
+                __syncthreads();                             // delta_l is in LDS, delta_{l+1} has been read
+            }
+        }
+        #pragma unroll
+        for (int kc = 0; kc < 2; ++kc) {
+            const V bw = gather(h0, kLd0, wave & 3, kc);
+            #pragma unroll
+            for (int i = 0; i < MW; ++i) acc0[i] = mfma(gather(drow(1), LDR, mw0 + i, kc), bw, acc0[i]);
+        }
+        if constexpr (GENC) {
+            // dL/dh_0 = W_0^T delta_1, row block wave & 3 of two columns, with the
+            // loss scale of the upstream gradient divided out
+            const int rg = wave & 3, cg = 2 * (wave >> 2);
+            const int fl = anew(lane), fg = fl >> 4, fn = fl & 15;
+            const float inv_scale = 1.0f / grad_scale;
+            f32x4 a[2];
+            #pragma unroll
+            for (int c = 0; c < KC; ++c) {
+                const Frag w0 = ld(gb + (rg * KC + c) * 64, lo_b);
+                #pragma unroll
+                for (int col = 0; col < 2; ++col)
+                    a[col] = mm(w0, get(drow(1), LDR, cg + col, c), c == 0 ? zero : a[col]);
+            }
+            #pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                const int rec = 16 * (cg + col) + fn;
+                const int64_t gr = tile * kTS + rec;
+                #pragma unroll
+                for (int j = 0; j < 4; ++j) a[col][j] *= inv_scale;
+                if (gr < n) {
+                    if (fcol) {
+                        // d(f_c R_c)/d(albedo column) = f_c
+                        #pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            int c = 16 * rg + 4 * fg + j - fcol;
+                            if (c >= 0 && c < 6) {
+                                c = c >= 3 ? c - 3 : c;
+                                a[col][j] = fmaf(tgt[gr * 3 + c], fy[rec * 4 + c], a[col][j]);
+                            }
+                        }
+                    }
+                    *reinterpret_cast<float4*>(out + gr * kEncWidth + 16 * rg + 4 * fg) =
+                        make_float4(a[col][0], a[col][1], a[col][2], a[col][3]);
+                }
+            }
+        }
+        if (!UPSTREAM && out_wave) {
+            const float wl = wave_sum_compensated(lterm);
+            if (lane == 0) wsum[wave] = wl;
+        }
+        __syncthreads();                                     // h_0 and delta_1 have been read
+        if (!UPSTREAM && tid == NTH - 1) {
+            // compensated combine of the waves' sums, in wave order
+            float t = 0.0f, c = 0.0f;
+            for (int w = 0; w < 4; ++w) {
+                const float x = wsum[w], u = t + x;
+                c += fabsf(t) >= fabsf(x) ? (t - u) + x : (x - u) + t;
+                t = u;
+            }
+            loss_part[tile] = t + c;
+        }
+    }
+
+    if constexpr (ACT == kActStore) return;
+    // ---- the workgroup's sums, in the layout of k_train_mfma's partials ---------
+    // Slot w_off + ((mb * NB + nb) * 64 + 16 g' + ln') * 4 + j holds
+    // dW[16 mb + 4 g' + j][16 nb + ln'].  Rows (and, past layer 0, columns) sit in
+    // slot order here: row positions 16 mbp + 4 g + j of a chunk are features
+    // 16 (g & 1) + 4 (2 (mbp & 1) + (g >> 1)) + j, column position 16 nbp + ln
+    // feature 16 ((ln >> 2) & 1) + 4 (2 (nbp & 1) + (ln >> 3)) + (ln & 3).
+    float* part = partials + (int64_t)blockIdx.x * P;
+    bool bad = false;
+    auto flush = [&](int l, int mbp, int nbp, const f32x4& a) {
+        const int NB = l == 0 ? 4 : MB;
+        const int mb = (mbp & ~1) + (g & 1), gq = 2 * (mbp & 1) + (g >> 1);
+        const int nb = l == 0 ? nbp : (nbp & ~1) + ((ln >> 2) & 1);
+        const int lq = l == 0 ? ln : 4 * (2 * (nbp & 1) + (ln >> 3)) + (ln & 3);
+        __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(part + geo.w_off(l) + ((mb * NB + nb) * 64 + 16 * gq + lq) * 4));
+        #pragma unroll
+        for (int j = 0; j < 4; ++j) bad |= !isfinite(a[j]);
+    };
+    #pragma unroll
+    for (int i = 0; i < MW; ++i) flush(0, mw0 + i, wave & 3, acc0[i]);
+    #pragma unroll
+    for (int l = 1; l < MAXH; ++l)
+        if (l < n_hidden) {
+            #pragma unroll
+            for (int i = 0; i < MW; ++i)
+                #pragma unroll
+                for (int j = 0; j < NW; ++j) flush(l, mw0 + i, nw0 + j, accw[l - 1][i][j]);
+        }
+    if (wave < MB && g == 0) {
+        const int f = 32 * (wave >> 1) + 16 * ((ln >> 2) & 1) + 4 * (2 * (wave & 1) + (ln >> 3)) + (ln & 3);
+        #pragma unroll
+        for (int j = 0; j < kNOut; ++j) {
+            part[geo.w_off(n_hidden) + j * W + f] = acco[j];
+            bad |= !isfinite(acco[j]);
+        }
+    }
+    const int any_bad = __syncthreads_or(bad ? 1 : 0);
+    if (tid == 0 && part_bad) part_bad[blockIdx.x] = any_bad ? 1 : 0;
+}
+
+template <typename T, int W, int MAXH, bool UP, bool GE, int ACT, int RAWL, int PRESET>
+hipError_t tiles_launch(const Geo& d, const void* ffr, const void* bfr, const void* enc, const float* tgt,
+                        const int32_t* idx, int64_t n, float loss_eps, float grad_scale, float* partials,
+                        float* loss_part, int32_t* part_bad, float* out, hipStream_t s, void* act, float* act_y,
+                        LcgGather lg) {
+    const size_t lds = (size_t)tiles_lds_bytes(W, d.H);
+    auto k = k_train_tiles<T, W, MAXH, UP, GE, ACT, RAWL, PRESET>;
+    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3((unsigned)train_parts(d, n)), dim3(64 * kWaves), lds, s, (const T*)ffr, (const T*)bfr,
+                       (const T*)enc, tgt, idx, n, d.H, loss_eps, grad_scale, partials, loss_part, part_bad, out,
+                       d.F, (T*)act, act_y, lg);
+    return hipGetLastError();
+}
+
+template <typename T, int W, int MAXH>
+hipError_t tiles_dispatch(const Geo& d, const void* ffr, const void* bfr, const void* enc, const float* tgt,
+                          const int32_t* idx, int64_t n, bool upstream, float loss_eps, float grad_scale,
+                          float* partials, float* loss_part, int32_t* part_bad, float* genc, hipStream_t s,
+                          void* act, float* act_y, LcgGather lg) {
+#define NRC_TILES(UP, GE, ACT)                                                                                    \
+    return tiles_launch<T, W, MAXH, UP, GE, ACT, -1,  NRC_PRESET_CONFIG>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, \
+                                                                         grad_scale, partials, loss_part,         \
+                                                                         part_bad, genc, s, act, act_y, lg)
+    if (!upstream) NRC_TILES(false, false, kActNone);
+    if (act) {
+        if (genc) NRC_TILES(true, true, kActLoad);
+        NRC_TILES(true, false, kActLoad);
+    }
+    if (genc) NRC_TILES(true, true, kActNone);
+    NRC_TILES(true, false, kActNone);
+#undef NRC_TILES
+}
+
+template <typename T, int MAXH>
+hipError_t tiles_raw_dispatch(const Geo& d, int preset, int layout, const void* ffr, const void* bfr,
+                              const float* raw, const float* tgt, const int32_t* idx, int64_t n, float loss_eps,
+                              float grad_scale, float* partials, float* loss_part, int32_t* part_bad, hipStream_t s,
+                              LcgGather lg) {
+#define NRC_TILES(PR)                                                                                            \
+    return layout == NRC_RAW14                                                                                   \
+               ? tiles_launch<T, 64, MAXH, false, false, kActNone, NRC_RAW14, PR>(d, ffr, bfr, raw, tgt, idx, n,    \
+                                                                               loss_eps, grad_scale, partials,   \
+                                                                               loss_part, part_bad, nullptr, s,  \
+                                                                               nullptr, nullptr, lg)             \
+               : tiles_launch<T, 64, MAXH, false, false, kActNone, NRC_RAW16, PR>(d, ffr, bfr, raw, tgt, idx, n,    \
+                                                                               loss_eps, grad_scale, partials,   \
+                                                                               loss_part, part_bad, nullptr, s,  \
+                                                                               nullptr, nullptr, lg)
+    if (preset == NRC_PRESET_PAPER_GAUSS) NRC_TILES(NRC_PRESET_PAPER_GAUSS);
+    if (preset == NRC_PRESET_PAPER_TRI) NRC_TILES(NRC_PRESET_PAPER_TRI);
+    if (preset == NRC_PRESET_PAPER) NRC_TILES(NRC_PRESET_PAPER);
+    NRC_TILES(NRC_PRESET_CONFIG);
+#undef NRC_TILES
+}
+
+}  // namespace
+
+bool train_in_tiles(const Geo& d, int64_t n) {
+    return d.W == 128 || (n + kTS - 1) / kTS > device_cu_count();
+}
+
+// Workgroups, each with one partial.  Two fit a CU at width 64 up to depth 5, but
+// up to three tiles per CU one is better: the second partial per CU costs the
+// reduction more than the overlap saves (us per FP16 step, one / two per CU:
+// 20,000 records 23.0 / 25.3, 32,768 23.6 / 25.7, 49,152 28.6 / 29.0, 65,536 35.6
+// / 35.2, 262,144 108.8 / 88.8).
+int64_t train_parts(const Geo& d, int64_t n) {
+    const int64_t tiles = (n + kTS - 1) / kTS, cus = device_cu_count();
+    const bool two = 2 * tiles_lds_bytes(d.W, d.H) <= 160 * 1024 && tiles > 3 * cus;
+    const int64_t wgs = two ? 2 * cus : cus;
+    return tiles < wgs ? tiles : wgs;
+}
+
+hipError_t launch_train_tiles(int precision, const Geo& d, const void* ffr, const void* bfr, const void* enc,
+                              const float* tgt, const int32_t* idx, int64_t n, bool upstream, float loss_eps,
+                              float grad_scale, float* partials, float* loss_part, int32_t* part_bad, float* genc,
+                              hipStream_t s, const void* act, const float* act_y, LcgGather lg) {
+#define NRC_TILES(T, W, MAXH)                                                                                      \
+    return tiles_dispatch<T, W, MAXH>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps, grad_scale, partials,    \
+                                      loss_part, part_bad, genc, s, (void*)act, (float*)act_y, lg)
+    if (precision == NRC_FP16) {
+        if (d.W == 128) NRC_TILES(_Float16, 128, 5);
+        if (d.H <= 5) NRC_TILES(_Float16, 64, 5);
+        NRC_TILES(_Float16, 64, 8);
+    }
+    if (d.W == 128) NRC_TILES(__bf16, 128, 5);
+    if (d.H <= 5) NRC_TILES(__bf16, 64, 5);
+    NRC_TILES(__bf16, 64, 8);
+#undef NRC_TILES
+}
+
+hipError_t launch_train_tiles_raw(int precision, const Geo& d, int preset, int layout, const void* ffr,
+                                  const void* bfr, const float* raw, const float* tgt, const int32_t* idx, int64_t n,
+                                  float loss_eps, float grad_scale, float* partials, float* loss_part,
+                                  int32_t* part_bad, hipStream_t s, LcgGather lg) {
+#define NRC_TILES(T, MAXH)                                                                                      \
+    return tiles_raw_dispatch<T, MAXH>(d, preset, layout, ffr, bfr, raw, tgt, idx, n, loss_eps, grad_scale,    \
+                                       partials, loss_part, part_bad, s, lg)
+    if (precision == NRC_FP16) {
+        if (d.H <= 5) NRC_TILES(_Float16, 5);
+        NRC_TILES(_Float16, 8);
+    }
+    if (d.H <= 5) NRC_TILES(__bf16, 5);
+    NRC_TILES(__bf16, 8);
+#undef NRC_TILES
+}
+
+hipError_t launch_fwd_train_tiles_bf16(const Geo& d, const void* ffr, const void* enc, int64_t n, void* act,
+                                       float* act_y, float* rgb, hipStream_t s) {
+    return tiles_launch<__bf16, 128, 5, true, false, kActStore, -1, NRC_PRESET_CONFIG>(
+        d, ffr, nullptr, enc, nullptr, nullptr, n, 0.0f, 1.0f, nullptr, nullptr, nullptr, rgb, s, act, act_y,
+        LcgGather{});
+}
+
+}  // namespace nrc

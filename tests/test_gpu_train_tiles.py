@@ -1,0 +1,106 @@
+"""The FP16/BF16 trainer over many tiles (weight gradients summed in registers).
+
+A record's forward pass and deltas do not depend on its batch, so dL/d(input) of
+a large batch equals that of its slices bit for bit.  The weight gradients are
+FP32 sums of the same products in another order.  With non-negative weights,
+inputs and upstream gradients every product is non-negative, so each sum's
+relative error is at most its number of roundings times 2^-24: at most 64 per
+tile that a workgroup takes and one per partial, on either side.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synthdata as sd
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def N():
+    from paper_2106_12372_amd import nrc
+    return nrc
+
+
+def _cus():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+# tiles per compute unit, records past the last whole tile: one workgroup per CU
+# with one or two tiles, two workgroups per CU, and ragged ends
+SIZES = [(1, 1), (1, 64), (2, -63), (3, 5), (4, 0)]
+
+
+@pytest.mark.parametrize("prec,width,n_hidden", [("fp16", 64, 5), ("bf16", 64, 5), ("fp16", 64, 1), ("bf16", 64, 2),
+                                                 ("fp16", 64, 6), ("bf16", 64, 8), ("fp16", 128, 5), ("bf16", 128, 5),
+                                                 ("fp16", 128, 1), ("bf16", 128, 3)])
+@pytest.mark.parametrize("per_cu,rest", SIZES)
+def test_gradients_of_a_large_batch_and_of_its_slices(N, prec, width, n_hidden, per_cu, rest):
+    tiles = per_cu * _cus()
+    n = 64 * tiles + rest
+    fact = n_hidden in (2, 5)
+    cfg = N.make_config(width=width, n_hidden=n_hidden, precision=prec, factorize=fact)
+    c = N.Cache(cfg)
+    c.set_weights(np.abs(sd.glorot_weights(width, n_hidden, seed=2)) / np.float32(width ** 0.5))
+    enc = torch.from_numpy(sd.uniform_features(n, 64, 11)).cuda().to(c.enc_dtype)
+    up = torch.rand(n, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(4)) * 0.5 + 0.5
+    rgb, act = N.nrc_forward_train(c, enc)
+    got_w, got_x = N.nrc_backward(c, enc, up, act=act)
+    again_w, again_x = N.nrc_backward(c, enc, up)           # the forward pass recomputed
+    assert torch.equal(got_w, again_w) and torch.equal(got_x, again_x)
+    only_w, none = N.nrc_backward(c, enc, up, want_grad_enc=False, act=act)
+    assert none is None and torch.equal(only_w, got_w)
+    ref_w = torch.zeros_like(got_w, dtype=torch.float64)
+    step = 64 * (_cus() // 2) - 7
+    for lo in range(0, n, step):
+        e, u = enc[lo:lo + step].clone(), up[lo:lo + step].clone()
+        assert torch.equal(N.nrc_forward_train(c, e)[0], rgb[lo:lo + step])
+        w, x = N.nrc_backward(c, e, u)
+        assert torch.equal(x, got_x[lo:lo + step]), lo
+        ref_w += w.double()
+    bound = 2 * (64 * (per_cu + 1) + 2 * _cus()) * 2.0 ** -24
+    assert bool((ref_w >= 0).all())
+    assert bool(((got_w.double() - ref_w).abs() <= bound * ref_w).all())
+
+
+@pytest.mark.parametrize("prec,n_hidden", [("fp16", 5), ("bf16", 5), ("bf16", 8), ("fp16", 1)])
+@pytest.mark.parametrize("preset,layout", [(0, 0), (1, 1), (2, 0), (3, 1)])
+@pytest.mark.parametrize("past", [1, 64 * 300 + 9])
+def test_raw_encoded_and_indexed_steps_agree(N, prec, n_hidden, preset, layout, past):
+    """One step over a batch of more tiles than compute units: from raw records, from
+    encoded rows and through an index list, equal bit for bit."""
+    n = 64 * _cus() + past
+    cfg = N.make_config(n_hidden=n_hidden, precision=prec, enc_preset=preset, ema_alpha=0.9)
+    w = sd.glorot_weights(64, n_hidden, seed=6)
+    raw_np = sd.raw_records(n, 77, layout)
+    raw, y = torch.from_numpy(raw_np).cuda(), torch.from_numpy(sd.targets(raw_np)).cuda()
+    res = []
+    for form in ("raw", "encoded", "indexed"):
+        c = N.Cache(cfg)
+        c.set_weights(w)
+        if form == "raw":
+            loss, skipped = N.nrc_train_frame_raw(c, raw, y, layout, steps=1, batch=n, seed=5)
+        elif form == "encoded":
+            loss, skipped = N.nrc_train_frame(c, N.nrc_encode(c, raw, layout), y, steps=1, batch=n, seed=5)
+        else:
+            loss, skipped = N.nrc_train_step_indexed(c, N.nrc_encode(c, raw, layout), y, N.nrc_shuffle(n, 5))
+        assert int(skipped.item()) == 0
+        res.append((loss.clone(), c.ws.clone()))
+    for loss, ws in res[1:]:
+        assert torch.equal(loss, res[0][0]) and torch.equal(ws, res[0][1])
+
+
+def test_a_non_finite_gradient_in_any_tile_skips_the_step(N):
+    n = 64 * _cus() * 3 + 100
+    for prec, width in (("fp16", 64), ("bf16", 128)):
+        c = N.Cache(N.make_config(width=width, precision=prec))
+        w = sd.glorot_weights(width, 5, seed=8)
+        c.set_weights(w)
+        raw = sd.raw_records(n, 13)
+        enc, y = N.nrc_encode(c, torch.from_numpy(raw).cuda()), torch.from_numpy(sd.targets(raw)).cuda()
+        for at in (0, 64 * _cus() + 70, n - 1):
+            bad = y.clone()
+            bad[at, 1] = float("nan")
+            _, skipped = N.nrc_train_step(c, enc, bad)
+            assert int(skipped.item()) == 1
+            assert np.array_equal(c.get_weights(), w)
