@@ -86,6 +86,8 @@ __device__ inline void write_frags(const Geo& d, int p, float w, T* ffr, T* bfr,
     put_frags<T>(d, fi, bi, w, ffr, bfr, split);
 }
 
+template <int N> struct Count { static constexpr int value = N; };
+
 constexpr int kRedParams = 32;   // weights per workgroup
 constexpr int kRedGroups = 8;    // tile groups per workgroup
 
@@ -140,8 +142,8 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
             if (lane + 64 * u < n_loss) lv[u] = loss_part[lane + 64 * u];
     }
     // Bias corrections of the step this update would make (a skipped step
-    // updates nothing) and the weight's fragment slots, evaluated while the
-    // partials are in flight.
+    // updates nothing) and the weight's fragment slots, before the partials'
+    // loads (formed while those are in flight, the launch was 0.9 us slower).
     const float t_next = (float)(t_old + 1);
     float bc1 = 1.0f, bc2 = 1.0f, bce = 1.0f;
     int64_t fi = 0, bi = 0;
@@ -151,28 +153,36 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
         if (ema.alpha > 0.0f) bce = 1.0f - powf(ema.alpha, t_next);
         if (ffr != nullptr || ema.effr != nullptr) frag_slots(d, p, fi, bi);
     }
+    // The thread's partials, every kRedGroups-th, summed in order.  Rounds of 32
+    // loads in flight, then 16, 8, 4 and up to 3 (64 partials, 4,096 records: one
+    // round of 8 instead of 8 loads one after another, 2.4 us less per step).
     float s = 0.0f, c = 0.0f;
     if (sidx < P) {
-        // 32 (then 16) loads in flight per thread before the (order-preserving) sums
         int t = grp;
-        for (; t + 31 * kRedGroups < n_tiles; t += 32 * kRedGroups) {
-            float x[32];
+        auto load = [&](int u) {
+            return __builtin_nontemporal_load(&partials[(int64_t)(t + u * kRedGroups) * P + sidx]);
+        };
+        auto left = [&](int k) { return t + (k - 1) * kRedGroups < n_tiles; };   // k partials or more
+        auto round = [&](auto k_) {
+            constexpr int K = decltype(k_)::value;
+            float x[K];
             #pragma unroll
-            for (int u = 0; u < 32; ++u)
-                x[u] = __builtin_nontemporal_load(&partials[(int64_t)(t + u * kRedGroups) * P + sidx]);
+            for (int u = 0; u < K; ++u) x[u] = load(u);
             #pragma unroll
-            for (int u = 0; u < 32; ++u) neumaier_add(s, c, x[u]);
-        }
-        for (; t + 15 * kRedGroups < n_tiles; t += 16 * kRedGroups) {
-            float x[16];
-            #pragma unroll
-            for (int u = 0; u < 16; ++u)
-                x[u] = __builtin_nontemporal_load(&partials[(int64_t)(t + u * kRedGroups) * P + sidx]);
-            #pragma unroll
-            for (int u = 0; u < 16; ++u) neumaier_add(s, c, x[u]);
-        }
-        for (; t < n_tiles; t += kRedGroups)
-            neumaier_add(s, c, __builtin_nontemporal_load(&partials[(int64_t)t * P + sidx]));
+            for (int u = 0; u < K; ++u) neumaier_add(s, c, x[u]);
+            t += K * kRedGroups;
+        };
+        while (left(32)) round(Count<32>{});
+        if (left(16)) round(Count<16>{});
+        if (left(8)) round(Count<8>{});
+        if (left(4)) round(Count<4>{});
+        float x[3];
+        #pragma unroll
+        for (int u = 0; u < 3; ++u)
+            if (left(u + 1)) x[u] = load(u);
+        #pragma unroll
+        for (int u = 0; u < 3; ++u)
+            if (left(u + 1)) neumaier_add(s, c, x[u]);
     }
     if (ADAM && tid < 64) {
         int any = bad4[0] | bad4[1] | bad4[2] | bad4[3];
