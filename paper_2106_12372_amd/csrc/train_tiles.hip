@@ -159,6 +159,26 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
         asm volatile("" : "+v"(v));
         return v;
     };
+    // A block of the workgroup's sums, in the layout of k_train_mfma's partials:
+    // slot w_off + ((mb * NB + nb) * 64 + 16 g' + ln') * 4 + j holds
+    // dW[16 mb + 4 g' + j][16 nb + ln'].  Rows (and, past layer 0, columns) sit in
+    // slot order here: row positions 16 mbp + 4 g + j of a chunk are features
+    // 16 (g & 1) + 4 (2 (mbp & 1) + (g >> 1)) + j, column position 16 nbp + ln
+    // feature 16 ((ln >> 2) & 1) + 4 (2 (nbp & 1) + (ln >> 3)) + (ln & 3).  A layer's
+    // sums leave as soon as the last tile has added to them, beside the layers
+    // before it.
+    float* part = partials + (int64_t)blockIdx.x * P;
+    bool bad = false;
+    auto flush = [&](int l, int mbp, int nbp, const f32x4& a) {
+        const int fl = anew(lane), fg = fl >> 4, fn = fl & 15;
+        const int NB = l == 0 ? 4 : MB;
+        const int mb = (mbp & ~1) + (fg & 1), gq = 2 * (mbp & 1) + (fg >> 1);
+        const int nb = l == 0 ? nbp : (nbp & ~1) + ((fn >> 2) & 1);
+        const int lq = l == 0 ? fn : 4 * (2 * (nbp & 1) + (fn >> 3)) + (fn & 3);
+        __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(part + geo.w_off(l) + ((mb * NB + nb) * 64 + 16 * gq + lq) * 4));
+        #pragma unroll
+        for (int j = 0; j < 4; ++j) bad |= !isfinite(a[j]);
+    };
     // Encoded rows: a thread moves 16 bytes of record tid / 8, and the output lanes
     // their record's targets; both are loaded during the tile before.
     const int64_t n_tiles = (n + kTS - 1) / kTS;
@@ -183,6 +203,7 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
     }
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const int fresh = anew(lane);
+        const bool last = tile + gridDim.x >= n_tiles;       // the sums leave with this tile
         const V* gf = reinterpret_cast<const V*>(ffr) + fresh;
         const V* gb = reinterpret_cast<const V*>(bfr) + fresh;
         // ---- h_0, targets ------------------------------------------------------
@@ -362,13 +383,24 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
                 if (g == 0) { bd[0] = d[0]; bd[1] = d[1]; bd[2] = d[2]; }
                 a[col] = mm(fr[0], bd, zero);
             }
-            if (n_hidden > 1) load_frags(gb + geo.bwd_base(n_hidden - 1) * 64, KC, rb, lo_b);
+            if (n_hidden > 1)
+                load_frags(gb + geo.bwd_base(n_hidden - 1) * 64, KC, rb, lo_b);
+            else if (GENC)
+                load_frags(gb, KC, wave & 3, lo_b);
             put_delta(n_hidden, a);
             if (wave < MB) {
                 #pragma unroll
                 for (int kc = 0; kc < 2; ++kc) {
                     const V av = ln < kNOut ? *reinterpret_cast<const V*>(dO + ln * kLdT + 32 * kc + 8 * g) : zero8<V>();
                     acco = mfma(av, gather(hrow(n_hidden), LDR, wave, kc), acco);
+                }
+                if (last && g == 0) {
+                    const int f = 32 * (wave >> 1) + 16 * ((ln >> 2) & 1) + 4 * (2 * (wave & 1) + (ln >> 3)) + (ln & 3);
+                    #pragma unroll
+                    for (int j = 0; j < kNOut; ++j) {
+                        part[geo.w_off(n_hidden) + j * W + f] = acco[j];
+                        bad |= !isfinite(acco[j]);
+                    }
                 }
             }
         }
@@ -382,7 +414,10 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
                     #pragma unroll
                     for (int col = 0; col < NC; ++col)
                         a[col] = mm(fr[c], get(drow(l + 1), LDR, col0 + col, c), c == 0 ? zero : a[col]);
-                if (l > 1) load_frags(gb + geo.bwd_base(l - 1) * 64, KC, rb, lo_b);
+                if (l > 1)
+                    load_frags(gb + geo.bwd_base(l - 1) * 64, KC, rb, lo_b);
+                else if (GENC)
+                    load_frags(gb, KC, wave & 3, lo_b);
                 put_delta(l, a);
                 #pragma unroll
                 for (int kc = 0; kc < 2; ++kc) {
@@ -396,6 +431,12 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
                         for (int j = 0; j < NW; ++j) accw[l - 1][i][j] = mfma(aw, bw[j], accw[l - 1][i][j]);
                     }
                 }
+                if (last) {
+                    #pragma unroll
+                    for (int i = 0; i < MW; ++i)
+                        #pragma unroll
+                        for (int j = 0; j < NW; ++j) flush(l, mw0 + i, nw0 + j, accw[l - 1][i][j]);
+                }
                 __syncthreads();                             // delta_l is in LDS, delta_{l+1} has been read
             }
         }
@@ -405,6 +446,10 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
             #pragma unroll
             for (int i = 0; i < MW; ++i) acc0[i] = mfma(gather(drow(1), LDR, mw0 + i, kc), bw, acc0[i]);
         }
+        if (last) {
+            #pragma unroll
+            for (int i = 0; i < MW; ++i) flush(0, mw0 + i, wave & 3, acc0[i]);
+        }
         if constexpr (GENC) {
             // dL/dh_0 = W_0^T delta_1, row block wave & 3 of two columns, with the
             // loss scale of the upstream gradient divided out
@@ -413,12 +458,10 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
             const float inv_scale = 1.0f / grad_scale;
             f32x4 a[2];
             #pragma unroll
-            for (int c = 0; c < KC; ++c) {
-                const Frag w0 = ld(gb + (rg * KC + c) * 64, lo_b);
+            for (int c = 0; c < KC; ++c)
                 #pragma unroll
                 for (int col = 0; col < 2; ++col)
-                    a[col] = mm(w0, get(drow(1), LDR, cg + col, c), c == 0 ? zero : a[col]);
-            }
+                    a[col] = mm(fr[c], get(drow(1), LDR, cg + col, c), c == 0 ? zero : a[col]);
             #pragma unroll
             for (int col = 0; col < 2; ++col) {
                 const int rec = 16 * (cg + col) + fn;
@@ -460,41 +503,6 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
     }
 
     if constexpr (ACT == kActStore) return;
-    // ---- the workgroup's sums, in the layout of k_train_mfma's partials ---------
-    // Slot w_off + ((mb * NB + nb) * 64 + 16 g' + ln') * 4 + j holds
-    // dW[16 mb + 4 g' + j][16 nb + ln'].  Rows (and, past layer 0, columns) sit in
-    // slot order here: row positions 16 mbp + 4 g + j of a chunk are features
-    // 16 (g & 1) + 4 (2 (mbp & 1) + (g >> 1)) + j, column position 16 nbp + ln
-    // feature 16 ((ln >> 2) & 1) + 4 (2 (nbp & 1) + (ln >> 3)) + (ln & 3).
-    float* part = partials + (int64_t)blockIdx.x * P;
-    bool bad = false;
-    auto flush = [&](int l, int mbp, int nbp, const f32x4& a) {
-        const int NB = l == 0 ? 4 : MB;
-        const int mb = (mbp & ~1) + (g & 1), gq = 2 * (mbp & 1) + (g >> 1);
-        const int nb = l == 0 ? nbp : (nbp & ~1) + ((ln >> 2) & 1);
-        const int lq = l == 0 ? ln : 4 * (2 * (nbp & 1) + (ln >> 3)) + (ln & 3);
-        __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(part + geo.w_off(l) + ((mb * NB + nb) * 64 + 16 * gq + lq) * 4));
-        #pragma unroll
-        for (int j = 0; j < 4; ++j) bad |= !isfinite(a[j]);
-    };
-    #pragma unroll
-    for (int i = 0; i < MW; ++i) flush(0, mw0 + i, wave & 3, acc0[i]);
-    #pragma unroll
-    for (int l = 1; l < MAXH; ++l)
-        if (l < n_hidden) {
-            #pragma unroll
-            for (int i = 0; i < MW; ++i)
-                #pragma unroll
-                for (int j = 0; j < NW; ++j) flush(l, mw0 + i, nw0 + j, accw[l - 1][i][j]);
-        }
-    if (wave < MB && g == 0) {
-        const int f = 32 * (wave >> 1) + 16 * ((ln >> 2) & 1) + 4 * (2 * (wave & 1) + (ln >> 3)) + (ln & 3);
-        #pragma unroll
-        for (int j = 0; j < kNOut; ++j) {
-            part[geo.w_off(n_hidden) + j * W + f] = acco[j];
-            bad |= !isfinite(acco[j]);
-        }
-    }
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
     if (tid == 0 && part_bad) part_bad[blockIdx.x] = any_bad ? 1 : 0;
 }
