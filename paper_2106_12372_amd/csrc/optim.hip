@@ -154,35 +154,30 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
         if (ffr != nullptr || ema.effr != nullptr) frag_slots(d, p, fi, bi);
     }
     // The thread's partials, every kRedGroups-th, summed in order.  Rounds of 32
-    // loads in flight, then 16, 8, 4 and up to 3 (64 partials, 4,096 records: one
-    // round of 8 instead of 8 loads one after another, 2.4 us less per step).
+    // loads in flight, then 16, 8, 4, 2 and 1, the same for every group, and the
+    // last, which only some groups have (64 partials, 4,096 records: one round of 8
+    // instead of 8 loads one after another, 2.4 us less per step).
     float s = 0.0f, c = 0.0f;
     if (sidx < P) {
-        int t = grp;
-        auto load = [&](int u) {
-            return __builtin_nontemporal_load(&partials[(int64_t)(t + u * kRedGroups) * P + sidx]);
-        };
-        auto left = [&](int k) { return t + (k - 1) * kRedGroups < n_tiles; };   // k partials or more
+        const float* src = partials + (int64_t)grp * P + sidx;
+        const int64_t step = (int64_t)kRedGroups * P;
         auto round = [&](auto k_) {
             constexpr int K = decltype(k_)::value;
             float x[K];
             #pragma unroll
-            for (int u = 0; u < K; ++u) x[u] = load(u);
+            for (int u = 0; u < K; ++u) x[u] = __builtin_nontemporal_load(src + u * step);
+            src += K * step;
             #pragma unroll
             for (int u = 0; u < K; ++u) neumaier_add(s, c, x[u]);
-            t += K * kRedGroups;
         };
-        while (left(32)) round(Count<32>{});
-        if (left(16)) round(Count<16>{});
-        if (left(8)) round(Count<8>{});
-        if (left(4)) round(Count<4>{});
-        float x[3];
-        #pragma unroll
-        for (int u = 0; u < 3; ++u)
-            if (left(u + 1)) x[u] = load(u);
-        #pragma unroll
-        for (int u = 0; u < 3; ++u)
-            if (left(u + 1)) neumaier_add(s, c, x[u]);
+        int k = n_tiles / kRedGroups;
+        for (; k >= 32; k -= 32) round(Count<32>{});
+        if (k & 16) round(Count<16>{});
+        if (k & 8) round(Count<8>{});
+        if (k & 4) round(Count<4>{});
+        if (k & 2) round(Count<2>{});
+        if (k & 1) round(Count<1>{});
+        if (grp < n_tiles % kRedGroups) round(Count<1>{});
     }
     if (ADAM && tid < 64) {
         int any = bad4[0] | bad4[1] | bad4[2] | bad4[3];
