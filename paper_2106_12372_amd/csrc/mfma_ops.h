@@ -157,5 +157,64 @@ __device__ inline void encode_shared(const float (&x)[RW], T* h0, int g, bool va
     }
 }
 
+
+// A record at rr (14 or 16 floats) encoded into the LDS row h0 by eight lanes, two
+// of each of four lane groups: first (half 0) the frequency encodings, position
+// coordinate g per group, then (half 1) the one-blob of angle g and a quarter of
+// the rest.  Both halves of a record run at once, in different waves, and neither
+// diverges far.  valid = false: zeros.  The same arithmetic as encode_part.
+template <typename T, int PRESET, int LAYOUT>
+__device__ inline void encode_half(const float* __restrict__ rr, T* h0, int half, int g, bool valid) {
+    constexpr bool paper = PRESET != NRC_PRESET_CONFIG, gauss = PRESET == NRC_PRESET_PAPER_GAUSS;
+    if (half == 0) {
+        if (g < 3) {
+            float x[1] = {valid ? rr[g] : 0.0f}, f[64];
+            encode_part<PRESET, LAYOUT, 0>(x, f);
+            #pragma unroll
+            for (int k = 0; k < 12; ++k) f[k] = valid ? f[k] : 0.0f;
+            #pragma unroll
+            for (int q = 0; q < 3; ++q) store4<T>(h0 + 12 * g + 4 * q, f + 4 * q);
+        }
+        return;
+    }
+    const float* rest = rr + (LAYOUT == NRC_RAW14 ? 7 : 9);
+    float v[7], s = 0.0f;
+    #pragma unroll
+    for (int j = 0; j < 7; ++j) v[j] = valid ? rest[j] : 0.0f;
+    if (LAYOUT == NRC_RAW14) {
+        if (valid) s = rr[3 + g];
+    } else if (valid) {
+        const float* d = rr + 3 + 3 * (g >> 1);
+        float u, w;
+        sph(d[0], d[1], d[2], u, w);
+        s = g & 1 ? w : u;
+    }
+    float e[4];
+    if (gauss) one_blob4_gauss(s, e); else one_blob4(s, e);
+    #pragma unroll
+    for (int k = 0; k < 4; ++k) e[k] = valid ? e[k] : 0.0f;
+    store4<T>(h0 + 36 + 4 * g, e);
+    if (g == 3) return;
+    if (paper) {
+        const float one = valid ? 1.0f : 0.0f;
+        if (g == 0) {
+            if (gauss) one_blob4_gauss(1.0f - expf(-v[0]), e); else one_blob4(1.0f - expf(-v[0]), e);
+            #pragma unroll
+            for (int k = 0; k < 4; ++k) e[k] = valid ? e[k] : 0.0f;
+        } else {
+            e[0] = g == 1 ? v[1] : v[5];
+            e[1] = g == 1 ? v[2] : v[6];
+            e[2] = g == 1 ? v[3] : one;
+            e[3] = g == 1 ? v[4] : one;
+        }
+    } else {
+        e[0] = g == 0 ? v[0] : g == 1 ? v[4] : 0.0f;
+        e[1] = g == 0 ? v[1] : g == 1 ? v[5] : 0.0f;
+        e[2] = g == 0 ? v[2] : g == 1 ? v[6] : 0.0f;
+        e[3] = g == 0 ? v[3] : 0.0f;
+    }
+    store4<T>(h0 + 52 + 4 * g, e);
+}
+
 }  // namespace
 }  // namespace nrc

@@ -14,16 +14,18 @@
 // loads of the encoded rows, H+1 chained layers of MFMA, and a 12-byte RGB
 // store per query.  HBM is touched only for the encoded input and the output.
 //
-// Training: a workgroup owns 64 records; its 4 chain waves hold 16 records
-// each (wave w: records 16w..16w+15).  The forward pass also writes every
-// layer's activations to LDS, record-major; the loss gradient of Eq. 5 is
-// formed in the output lanes; the data backward pass chains W_l^T products
-// through VGPRs the same way as the forward pass, storing each delta_l.  Four
-// more waves form the weight gradients: dW_l, a contraction over the tile's
-// 64 records, as soon as delta_{l+1} is in LDS, beside the chain's next
-// layer, reading delta and h with LDS transpose loads so that the record
-// index runs along K.  Each tile writes its weight-gradient partial sums; a
-// fixed-order reduction follows (no atomics).
+// Training: k_train_tiles (train_tiles.hip) runs the training steps and most
+// backward passes.  k_train_mfma here keeps two calls of the autograd form: the
+// forward pass that fills the activation buffer, and the FP16 backward pass of a
+// batch of at most one tile per compute unit.  A workgroup owns 64 records; its 4
+// chain waves hold 16 records each (wave w: records 16w..16w+15).  The forward
+// pass also writes every layer's activations to LDS, record-major; the data
+// backward pass chains W_l^T products through VGPRs the same way as the forward
+// pass, storing each delta_l.  Four more waves form the weight gradients: dW_l, a
+// contraction over the tile's 64 records, as soon as delta_{l+1} is in LDS,
+// beside the chain's next layer, reading delta and h with LDS transpose loads so
+// that the record index runs along K.  Each tile writes its weight-gradient
+// partial sums; a fixed-order reduction follows (no atomics).
 #include <atomic>
 
 #include "encode_impl.h"
@@ -856,25 +858,17 @@ constexpr int kActNone = 0, kActStore = 1, kActLoad = 2;
 // Weight-gradient waves beside the chain waves (none in the forward-only form).
 template <int ACT> constexpr int train_helpers() { return ACT == kActStore ? 0 : TrainShape::NW; }
 
-// Training records given raw (RAWL = their layout, PRESET = the cache's
-// encoding; RAWL < 0: encoded rows): the kernel's enc argument then points at
-// the raw records, FP32 [n][14 or 16], and the four lanes (g, j) of each chain
-// wave encode record j, a share of its features each, into the record's h_0
-// row, where the stand-alone encoding kernel would have written it, before the
-// wave reads its operands back.
-template <typename T, bool UPSTREAM, bool GENC, int ACT = kActNone, int RAWL = -1, int PRESET = NRC_PRESET_CONFIG>
+// tgt: the upstream gradient dL/d(prediction) of each record.
+template <typename T, bool GENC, int ACT>
 __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
                                                     const T* __restrict__ bfr,
                                                     const T* __restrict__ enc,
-                                                    const float* __restrict__ tgt,
-                                                    const int32_t* __restrict__ idx, int64_t n,
-                                                    int n_hidden, float loss_eps, float grad_scale,
+                                                    const float* __restrict__ tgt, int64_t n,
+                                                    int n_hidden, float grad_scale,
                                                     float* __restrict__ partials,
-                                                    float* __restrict__ loss_part,
                                                     int32_t* __restrict__ tile_bad,
                                                     float* __restrict__ genc, int fcol,
-                                                    T* __restrict__ act, float* __restrict__ rgb,
-                                                    LcgGather lg) {
+                                                    T* __restrict__ act, float* __restrict__ rgb) {
     using V = typename Vec8<T>::type;
     using S = TrainShape;
     constexpr int W = 64, MB = W / 16, KC = W / 32, TS = S::TS, NW = S::NW, LDT = S::LDT, TK = TS / 32;
@@ -882,7 +876,6 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
     constexpr int NHW = train_helpers<ACT>();                // weight-gradient waves
     constexpr int NT = 64 * (NW + NHW);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    __shared__ float wsum[4];
     const Geo geo(W, n_hidden);
     // h_l and delta_l record-major (a record's features contiguous, so the
     // chain waves store and read them 8 bytes at a time); dL/dy feature-major.
@@ -902,8 +895,7 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
     const int sl = 16 * (chain ? wave : 0) + ln;             // record within the tile
     const int64_t row = tile * TS + sl;
     const bool valid = chain && row < n;
-    // record read for this slot: idx[row] or the LCG orbit for a gathered batch, else row
-    const int64_t src = !valid ? 0 : gather_row(idx, lg, row);
+    const int64_t src = valid ? row : 0;
     float* part = partials + tile * (int64_t)P;
     const V* gf = reinterpret_cast<const V*>(ffr) + lane;
     const V* gb = reinterpret_cast<const V*>(bfr) + lane;
@@ -934,48 +926,14 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
 
     // ---- forward (each wave: its 16 records, activations in VGPRs) ----------
     V b[KC];
-    if constexpr (RAWL >= 0) {
-        static_assert(!UPSTREAM && !GENC && ACT == kActNone, "raw records feed the training step only");
-        constexpr int RW = RAWL == NRC_RAW14 ? 14 : 16;
-        if (chain) {
-            T* h0 = hT + sl * LD0;
-            // BF16: the first layer's weight fragments (hi and lo parts) start
-            // loading now, beside the encoding, so they are cached when the
-            // layer reads them (the LDS hand-over below orders every later
-            // memory access).  Measured: the BF16 step 17.8 -> 16.2 us; FP16,
-            // with half the fragments, no faster, so it does not prefetch.
-            constexpr int NPRE = SPLIT ? 4 * MB : 0;
-            V pre[NPRE > 0 ? NPRE : 1];
-            #pragma unroll
-            for (int i = 0; i < NPRE; ++i) pre[i] = gf[(i % (2 * MB)) * 64 + (i < 2 * MB ? 0 : lo_f)];
-            float x[RW];
-            if (valid) {
-                const float* rr = reinterpret_cast<const float*>(enc) + src * RW;
-                #pragma unroll
-                for (int k = 0; k < RW; ++k) x[k] = rr[k];
-            } else {
-                #pragma unroll
-                for (int k = 0; k < RW; ++k) x[k] = 0.0f;
-            }
-            encode_shared<T, PRESET, RAWL>(x, h0, g, valid);
-            wave_lds_sync();
-            #pragma unroll
-            for (int c = 0; c < 2; ++c) b[c] = *reinterpret_cast<const V*>(h0 + 32 * c + 8 * g);
-            #pragma unroll
-            for (int i = 0; i < NPRE; ++i) asm volatile("" :: "v"(pre[i]));
-        } else {
-            b[0] = b[1] = zero8<V>();
-        }
-    } else {
-        #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            b[c] = valid ? *reinterpret_cast<const V*>(enc + src * kEncWidth + 32 * c + 8 * g) : zero8<V>();
-            if (chain) *reinterpret_cast<V*>(hT + sl * LD0 + 32 * c + 8 * g) = b[c];
-        }
+    #pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        b[c] = valid ? *reinterpret_cast<const V*>(enc + src * kEncWidth + 32 * c + 8 * g) : zero8<V>();
+        if (chain) *reinterpret_cast<V*>(hT + sl * LD0 + 32 * c + 8 * g) = b[c];
     }
     float r[3];                      // reflectance factor of record sl (lanes 0..15)
     reflectance_operand(b[1], fcol, ln, r);
-    // this record's targets (or upstream gradient), loaded now and used after the forward pass
+    // this record's upstream gradient, loaded now and used after the forward pass
     float tg[3] = {0.f, 0.f, 0.f};
     if (ACT != kActStore && g == 0 && valid) {
         #pragma unroll
@@ -1086,27 +1044,14 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
         return;
     }
 
-    // ---- loss gradient (Eq. 5); lanes 0..15 of each wave hold y[0..2] -------
+    // ---- dL/dy; lanes 0..15 of each wave hold y[0..2] ------------------------
     // The prediction is the network output times r; the network's output
     // gradient is the prediction's gradient times r.
-    float d0 = 0.f, d1 = 0.f, d2 = 0.f, lterm = 0.f;
+    float d0 = 0.f, d1 = 0.f, d2 = 0.f;
     if (g == 0 && valid) {
-        if (UPSTREAM) {
-            d0 = tg[0] * grad_scale * r[0];
-            d1 = tg[1] * grad_scale * r[1];
-            d2 = tg[2] * grad_scale * r[2];
-        } else {
-            const float p0 = y[0] * r[0], p1 = y[1] * r[1], p2 = y[2] * r[2];
-            const float lum = (p0 + p1 + p2) * (1.0f / 3.0f);
-            const float inv_den = 1.0f / fmaf(lum, lum, loss_eps);
-            const float e0 = p0 - tg[0];
-            const float e1 = p1 - tg[1];
-            const float e2 = p2 - tg[2];
-            lterm = fmaf(e2, e2, fmaf(e1, e1, e0 * e0)) * inv_den;
-            d0 = 2.0f * e0 * inv_den * grad_scale * r[0];
-            d1 = 2.0f * e1 * inv_den * grad_scale * r[1];
-            d2 = 2.0f * e2 * inv_den * grad_scale * r[2];
-        }
+        d0 = tg[0] * grad_scale * r[0];
+        d1 = tg[1] * grad_scale * r[1];
+        d2 = tg[2] * grad_scale * r[2];
     }
     V bd = zero8<V>();
     if (g == 0 && chain) {
@@ -1115,8 +1060,6 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
         dO[1 * LDT + sl] = bd[1];
         dO[2 * LDT + sl] = bd[2];
     }
-    const float wl = wave_sum_compensated(lterm);
-    if (lane == 0 && chain) wsum[wave] = wl;
 
     // ---- weight gradients: dW_l = delta_{l+1} h_l^T over the tile's records --
     // Computed by the helper waves (hw = 0 .. NHW-1) while the chain waves run
@@ -1258,16 +1201,6 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
                 *reinterpret_cast<float4*>(genc + row * kEncWidth + 16 * mb + 4 * g) =
                     make_float4(acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]);
         }
-    }
-    if (tid == 0) {
-        // compensated combine of the waves' sums, in wave order
-        float t = 0.0f, c = 0.0f;
-        for (int w = 0; w < NW; ++w) {
-            const float x = wsum[w], u = t + x;
-            c += fabsf(t) >= fabsf(x) ? (t - u) + x : (x - u) + t;
-            t = u;
-        }
-        loss_part[tile] = t + c;
     }
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
     if (tid == 0) tile_bad[tile] = any_bad ? 1 : 0;
@@ -1466,66 +1399,20 @@ hipError_t fwd_raw_dispatch(const Geo& d, int preset, int layout, const void* ff
                                : fwd_raw_generic<T, W, NRC_PRESET_CONFIG, NRC_RAW16>(d, ffr, raw, n, rgb, s);
 }
 
-template <typename T, bool UP, bool GE, int ACT = kActNone, int RAWL = -1, int PRESET = NRC_PRESET_CONFIG>
-hipError_t train_launch(const Geo& d, const void* ffr, const void* bfr, const void* enc,
-                        const float* tgt, const int32_t* idx, int64_t n, float loss_eps, float grad_scale,
-                        float* partials, float* loss_part, int32_t* tile_bad, float* genc,
-                        hipStream_t s, void* act = nullptr, float* rgb = nullptr, LcgGather lg = LcgGather{}) {
+template <typename T, bool GE, int ACT>
+hipError_t train_launch(const Geo& d, const void* ffr, const void* bfr, const void* enc, const float* tgt, int64_t n,
+                        float grad_scale, float* partials, int32_t* tile_bad, float* genc, hipStream_t s,
+                        void* act, float* rgb = nullptr) {
     using S = TrainShape;
     const int64_t tiles = (n + S::TS - 1) / S::TS;
     if (tiles == 0) return hipSuccess;
     const size_t lds = (size_t)train_lds_bytes(d.H, ACT == kActStore);
-    auto k = k_train_mfma<T, UP, GE, ACT, RAWL, PRESET>;
+    auto k = k_train_mfma<T, GE, ACT>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(64 * (S::NW + train_helpers<ACT>())), lds, s, (const T*)ffr, (const T*)bfr,
-                       (const T*)enc, tgt, idx, n, d.H, loss_eps, grad_scale, partials, loss_part, tile_bad,
-                       genc, d.F, (T*)act, rgb, lg);
+    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(64 * (S::NW + train_helpers<ACT>())), lds, s, (const T*)ffr,
+                       (const T*)bfr, (const T*)enc, tgt, n, d.H, grad_scale, partials, tile_bad, genc, d.F, (T*)act,
+                       rgb);
     return hipGetLastError();
-}
-
-template <typename T>
-hipError_t train_dispatch(const Geo& d, const void* ffr, const void* bfr, const void* enc,
-                          const float* tgt, const int32_t* idx, int64_t n, bool upstream, float loss_eps,
-                          float grad_scale, float* partials, float* loss_part, int32_t* tile_bad,
-                          float* genc, hipStream_t s, const void* act, LcgGather lg) {
-    if (!upstream)
-        return train_launch<T, false, false>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
-                                                partials, loss_part, tile_bad, genc, s, nullptr, nullptr, lg);
-    if (act) {
-        if (genc)
-            return train_launch<T, true, true, kActLoad>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
-                                                            partials, loss_part, tile_bad, genc, s, (void*)act);
-        return train_launch<T, true, false, kActLoad>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
-                                                         partials, loss_part, tile_bad, genc, s, (void*)act);
-    }
-    if (genc)
-        return train_launch<T, true, true>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
-                                              partials, loss_part, tile_bad, genc, s);
-    return train_launch<T, true, false>(d, ffr, bfr, enc, tgt, idx, n, loss_eps, grad_scale,
-                                           partials, loss_part, tile_bad, genc, s);
-}
-
-// The training step on raw records (width 64, as the fused query path).
-template <typename T>
-hipError_t train_raw_dispatch(const Geo& d, int preset, int layout, const void* ffr, const void* bfr,
-                              const float* raw, const float* tgt, const int32_t* idx, int64_t n, float loss_eps,
-                              float grad_scale, float* partials, float* loss_part, int32_t* tile_bad,
-                              hipStream_t s, LcgGather lg) {
-#define NRC_TRAIN_RAW(PR, LA)                                                                                 \
-    return train_launch<T, false, false, kActNone, LA, PR>(d, ffr, bfr, raw, tgt, idx, n, loss_eps,      \
-                                                               grad_scale, partials, loss_part, tile_bad,     \
-                                                               nullptr, s, nullptr, nullptr, lg)
-    const bool r14 = layout == NRC_RAW14;
-    if (preset == NRC_PRESET_PAPER_GAUSS) {
-        if (r14) NRC_TRAIN_RAW(NRC_PRESET_PAPER_GAUSS, NRC_RAW14); else NRC_TRAIN_RAW(NRC_PRESET_PAPER_GAUSS, NRC_RAW16);
-    } else if (preset == NRC_PRESET_PAPER_TRI) {
-        if (r14) NRC_TRAIN_RAW(NRC_PRESET_PAPER_TRI, NRC_RAW14); else NRC_TRAIN_RAW(NRC_PRESET_PAPER_TRI, NRC_RAW16);
-    } else if (preset == NRC_PRESET_PAPER) {
-        if (r14) NRC_TRAIN_RAW(NRC_PRESET_PAPER, NRC_RAW14); else NRC_TRAIN_RAW(NRC_PRESET_PAPER, NRC_RAW16);
-    }
-    if (r14) NRC_TRAIN_RAW(NRC_PRESET_CONFIG, NRC_RAW14);
-    NRC_TRAIN_RAW(NRC_PRESET_CONFIG, NRC_RAW16);
-#undef NRC_TRAIN_RAW
 }
 
 }  // namespace
@@ -1583,29 +1470,16 @@ hipError_t launch_train_mfma(int precision, const Geo& d, const void* ffr, const
                              const void* enc, const float* tgt, const int32_t* idx, int64_t n, bool upstream,
                              float loss_eps, float grad_scale, float* partials, float* loss_part,
                              int32_t* tile_bad, float* genc, hipStream_t s, const void* act, LcgGather lg) {
-    if (train_in_tiles(d, n))
+    if (train_in_tiles(precision, d, n, upstream))
         return launch_train_tiles(precision, d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps, grad_scale, partials,
                                   loss_part, tile_bad, genc, s, act, act_outputs(d, act, n), lg);
-    if (precision == NRC_FP16)
-        return train_dispatch<_Float16>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps, grad_scale, partials,
-                                        loss_part, tile_bad, genc, s, act, lg);
-    return train_dispatch<__bf16>(d, ffr, bfr, enc, tgt, idx, n, upstream, loss_eps, grad_scale, partials,
-                                  loss_part, tile_bad, genc, s, act, lg);
-}
-
-hipError_t launch_train_mfma_raw(int precision, const Geo& d, int preset, int layout, const void* ffr,
-                                 const void* bfr, const float* raw, const float* tgt, const int32_t* idx,
-                                 int64_t n, float loss_eps, float grad_scale, float* partials, float* loss_part,
-                                 int32_t* tile_bad, hipStream_t s, LcgGather lg) {
-    if (d.W != 64) return hipErrorInvalidValue;
-    if (train_in_tiles(d, n))
-        return launch_train_tiles_raw(precision, d, preset, layout, ffr, bfr, raw, tgt, idx, n, loss_eps, grad_scale,
-                                      partials, loss_part, tile_bad, s, lg);
-    if (precision == NRC_FP16)
-        return train_raw_dispatch<_Float16>(d, preset, layout, ffr, bfr, raw, tgt, idx, n, loss_eps, grad_scale,
-                                            partials, loss_part, tile_bad, s, lg);
-    return train_raw_dispatch<__bf16>(d, preset, layout, ffr, bfr, raw, tgt, idx, n, loss_eps, grad_scale,
-                                      partials, loss_part, tile_bad, s, lg);
+    using T = _Float16;
+    void* a = const_cast<void*>(act);
+    if (act)
+        return genc ? train_launch<T, true, kActLoad>(d, ffr, bfr, enc, tgt, n, grad_scale, partials, tile_bad, genc, s, a)
+                    : train_launch<T, false, kActLoad>(d, ffr, bfr, enc, tgt, n, grad_scale, partials, tile_bad, genc, s, a);
+    return genc ? train_launch<T, true, kActNone>(d, ffr, bfr, enc, tgt, n, grad_scale, partials, tile_bad, genc, s, a)
+                : train_launch<T, false, kActNone>(d, ffr, bfr, enc, tgt, n, grad_scale, partials, tile_bad, genc, s, a);
 }
 
 template <typename T>
@@ -1617,8 +1491,8 @@ hipError_t fwd_train_dispatch(const Geo& d, const void* ffr, const void* enc, in
         else
             return fwd_wide<T, true>(d, ffr, EncBatch{enc, n, rgb}, (n + 63) / 64, s, act, act_outputs(d, act, n));
     }
-    return train_launch<T, true, false, kActStore>(d, ffr, nullptr, enc, nullptr, nullptr, n, 0.0f, 1.0f,
-                                                   nullptr, nullptr, nullptr, nullptr, s, act, rgb);
+    return train_launch<T, false, kActStore>(d, ffr, nullptr, enc, nullptr, n, 1.0f, nullptr, nullptr, nullptr, s, act,
+                                             rgb);
 }
 
 hipError_t launch_fwd_train_mfma(int precision, const Geo& d, const void* ffr, const void* enc, int64_t n,

@@ -139,8 +139,8 @@ Geo kernel_geo(const nrc_config& c) {
 
 // Weight-gradient partials a step over n records writes: one per tile, or one
 // per workgroup where workgroups take several tiles.
-static int64_t step_parts(const nrc_config& c, const Geo& d, int64_t n, const ScratchLayout& sl) {
-    return !fp32_form(c.precision) && train_in_tiles(d, n) ? train_parts(d, n) : sl.tiles;
+static int64_t step_parts(const nrc_config& c, const Geo& d, int64_t n, bool upstream, const ScratchLayout& sl) {
+    return !fp32_form(c.precision) && train_in_tiles(c.precision, d, n, upstream) ? train_parts(d, n) : sl.tiles;
 }
 
 // Enqueue one training step (forward, loss, backward, reduction, Adam) on s.
@@ -165,7 +165,7 @@ int enqueue_train_step(nrc_cache* c, const void* enc, const float* target, const
             e = launch_train_fp32_raw(d, cfg.enc_preset, raw_layout, c->w(), raw, target, idx, n, cfg.loss_eps,
                                       grad_scale, partials, loss_part, tile_bad, s, lg);
         else
-            e = launch_train_mfma_raw(cfg.precision, d, cfg.enc_preset, raw_layout, c->ffr(), c->bfr(), raw, target,
+            e = launch_train_tiles_raw(cfg.precision, d, cfg.enc_preset, raw_layout, c->ffr(), c->bfr(), raw, target,
                                       idx, n, cfg.loss_eps, grad_scale, partials, loss_part, tile_bad, s, lg);
     } else if (cfg.precision == NRC_FP32_VALU)
         e = launch_train_fp32_valu(d, c->w(), (const float*)enc, target, idx, n, false, cfg.loss_eps, grad_scale,
@@ -181,7 +181,7 @@ int enqueue_train_step(nrc_cache* c, const void* enc, const float* target, const
     int32_t* skipped_out = skipped_dev ? skipped_dev : (int32_t*)(scratch + sl.skipped);
     const AdamHyper hp{cfg.lr, cfg.beta1, cfg.beta2, cfg.adam_eps};
     const EmaArgs ema{c->ema() ? cfg.ema_alpha : 0.0f, c->e(), c->wbar(), c->effr()};
-    e = launch_reduce_adam(cfg.precision, d, !fp32_form(cfg.precision), partials, (int)step_parts(cfg, d, n, sl),
+    e = launch_reduce_adam(cfg.precision, d, !fp32_form(cfg.precision), partials, (int)step_parts(cfg, d, n, false, sl),
                            tile_bad, loss_part, (int)((n + 63) / 64), (float)(1.0 / (3.0 * (double)n)), loss_out,
                            1.0f / scale, c->w(), c->m(), c->v(), c->tslots(), c->parity, hp, ema,
                            skipped_out, c->ffr(), c->bfr(), s);
@@ -560,7 +560,8 @@ int nrc_backward(nrc_cache* cache, const void* enc, const void* act_ws, const fl
         e = launch_train_mfma(cfg.precision, d, cache->ffr(), cache->bfr(), enc, grad_rgb, nullptr, n, true,
                               cfg.loss_eps, scale, partials, loss_part, tile_bad, grad_enc, s, act_ws);
     if (e != hipSuccess) return device_fail(e, "backward kernel launch");
-    e = launch_reduce(d, !fp32_form(cfg.precision), partials, (int)step_parts(cfg, d, n, sl), 1.0f / scale, grad_w, s);
+    e = launch_reduce(d, !fp32_form(cfg.precision), partials, (int)step_parts(cfg, d, n, true, sl), 1.0f / scale, grad_w,
+                      s);
     if (e != hipSuccess) return device_fail(e, "gradient reduction launch");
     return ok();
 }

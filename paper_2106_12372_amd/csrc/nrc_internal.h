@@ -199,6 +199,22 @@ __device__ inline int64_t gather_row(const int32_t* idx, const LcgGather& lg, in
     return r;
 }
 
+// The same for slot base + rec, base the first slot of a 64-record tile (uniform
+// across the workgroup) and rec < 64: the orbit's jump to the tile runs on the
+// scalar unit and a lane makes six steps instead of one per bit of its slot.
+__device__ inline int64_t gather_row(const int32_t* idx, const LcgGather& lg, int64_t base, int rec) {
+    if (idx) return idx[base + rec];
+    if (!lg.mask) return base + rec;
+    uint32_t x = apply(power(lg.step, (uint64_t)base), lg.x0);
+    Affine f = lg.step;
+    #pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        if (rec >> b & 1) x = apply(f, x);
+        f = compose(f, f);
+    }
+    return (int64_t)(x & lg.mask);
+}
+
 struct AdamHyper {
     float lr, beta1, beta2, eps;
 };
@@ -244,10 +260,6 @@ hipError_t launch_train_fp32_valu_raw(const Geo& d, int preset, int layout, cons
                                       const float* tgt, const int32_t* idx, int64_t n, float loss_eps,
                                       float grad_scale, float* partials, float* loss_part, int32_t* tile_bad,
                                       hipStream_t s, LcgGather lg);
-hipError_t launch_train_mfma_raw(int precision, const Geo& d, int preset, int layout, const void* ffr,
-                                 const void* bfr, const float* raw, const float* tgt, const int32_t* idx,
-                                 int64_t n, float loss_eps, float grad_scale, float* partials, float* loss_part,
-                                 int32_t* tile_bad, hipStream_t s, LcgGather lg);
 hipError_t launch_fwd_raw_fp32(const Geo& d, int preset, int layout, const float* w, const float* raw,
                                int64_t n, float* rgb, hipStream_t s);
 // mlp_fp32_valu.hip (NRC_FP32_VALU: vector ALUs only)
@@ -277,11 +289,12 @@ hipError_t launch_train_mfma(int precision, const Geo& d, const void* ffr, const
 // (act_bytes_mfma / act_bytes_fp32 bytes) for a later backward.
 hipError_t launch_fwd_train_mfma(int precision, const Geo& d, const void* ffr, const void* enc, int64_t n,
                                  void* act, float* rgb, hipStream_t s);
-// train_tiles.hip: the FP16/BF16 trainer over more tiles than compute units
-// (and always at width 128).  It writes train_parts(d, n) partials and flags,
-// and a loss term for each 64 records.  Arguments as launch_train_mfma and
-// launch_train_mfma_raw; act_y: the network outputs of the activation buffer.
-bool train_in_tiles(const Geo& d, int64_t n);
+// train_tiles.hip: the FP16/BF16 trainer.  Where train_in_tiles holds, a call
+// writes train_parts(d, n) partials and flags, and a loss term for each 64
+// records; elsewhere (k_train_mfma) one partial and flag per tile.  Arguments as
+// launch_train_mfma, raw records as launch_train_fp32_raw; act_y: the network
+// outputs of the activation buffer.
+bool train_in_tiles(int precision, const Geo& d, int64_t n, bool upstream);
 int64_t train_parts(const Geo& d, int64_t n);
 hipError_t launch_train_tiles(int precision, const Geo& d, const void* ffr, const void* bfr, const void* enc,
                               const float* tgt, const int32_t* idx, int64_t n, bool upstream, float loss_eps,

@@ -1,21 +1,20 @@
-// Training over many records in the FP16/BF16 matrix-core forms: forward pass,
-// loss gradient of Eq. 5 (or an upstream gradient), data backward pass and
-// weight gradients, with the weight gradients of all a workgroup's tiles summed
-// in registers.
+// Training in the FP16/BF16 matrix-core forms: forward pass, loss gradient of Eq.
+// 5 (or an upstream gradient), data backward pass and weight gradients, with the
+// weight gradients of all a workgroup's tiles summed in registers.
 //
 // A workgroup of 8 waves takes 64-record tiles one after another.  In every
 // layer a wave owns one 16-row block of the output for NC of the tile's four
 // 16-record columns, so a weight fragment is read by one wave per tile (two at
 // width 64; every wave that holds records in k_train_mfma) and goes from L2 to
-// registers while the wave waits for the layer before.  Activations and deltas pass between the waves
-// through LDS, record-major, each 32-feature chunk of a row in the order of the
-// operand slots ("chained" order, nrc_internal.h): the B operand of the next
-// product is one 16-byte read.  Only two layers' deltas are held.  While the
-// waves form delta_l they also form dW_l = delta_{l+1} h_l^T over the tile's 64
-// records, the record index along K by LDS transpose reads, into accumulators
-// that stay in registers from tile to tile.  Each workgroup writes its sums
-// once, in the accumulator layout the reduction expects, so the partials no
-// longer grow with the batch.
+// registers while the wave waits for the layer before.  Activations and deltas
+// pass between the waves through LDS, record-major, each 32-feature chunk of a
+// row in the order of the operand slots ("chained" order, nrc_internal.h): the B
+// operand of the next product is one 16-byte read.  Only two layers' deltas are
+// held.  While the waves form delta_l they also form dW_l = delta_{l+1} h_l^T over
+// the tile's 64 records, the record index along K by LDS transpose reads, into
+// accumulators that stay in registers from tile to tile.  Each workgroup writes
+// its sums once, in the accumulator layout the reduction expects, so the partials
+// do not grow with the batch.
 //
 // Every record's forward pass, loss and deltas go through the same products in
 // the same order as in k_train_mfma; only the grouping of the records' weight
@@ -187,9 +186,10 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
     int src_e = -1, src_t = -1;              // n <= 2^31
     auto find = [&](int64_t t) {             // the records behind tile t's slots (-1: none)
         const int ft = anew(tid);
-        const int64_t re = t * kTS + (ft >> 3), rt = t * kTS + 16 * wave + (ft & 15);
-        src_e = re < n ? (int)gather_row(idx, lg, re) : -1;
-        src_t = wave < 4 && g == 0 && rt < n ? (int)gather_row(idx, lg, rt) : -1;
+        const int re = ft >> 3, rt = 16 * (wave & 3) + (ft & 15);
+        const int64_t base = t * kTS;
+        src_e = base + re < n ? (int)gather_row(idx, lg, base, re) : -1;
+        src_t = wave < 4 && g == 0 && base + rt < n ? (int)gather_row(idx, lg, base, rt) : -1;
     };
     auto fetch = [&] {
         in_v = zero8<V>();
@@ -213,18 +213,14 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
         const bool valid = row < n;
         if constexpr (RAWL >= 0) {
             constexpr int RW = RAWL == NRC_RAW14 ? 14 : 16;
-            if (out_wave) {
-                const int64_t src = valid ? gather_row(idx, lg, row) : 0;
-                float x[RW];
-                const float* rr = reinterpret_cast<const float*>(enc) + src * RW;
+            load_frags(gf, 2, rb, lo_f);                     // beside the encoding
+            const int64_t src = valid ? gather_row(idx, lg, tile * kTS, sl) : 0;
+            if (out_wave && g == 0 && valid) {
                 #pragma unroll
-                for (int k = 0; k < RW; ++k) x[k] = valid ? rr[k] : 0.0f;
-                if (g == 0 && valid) {
-                    #pragma unroll
-                    for (int c = 0; c < 3; ++c) tg[c] = tgt[src * 3 + c];
-                }
-                encode_shared<T, PRESET, RAWL>(x, h0 + sl * kLd0, g, valid);
+                for (int c = 0; c < 3; ++c) tg[c] = tgt[src * 3 + c];
             }
+            encode_half<T, PRESET, RAWL>(reinterpret_cast<const float*>(enc) + src * RW, h0 + sl * kLd0, wave >> 2, g,
+                                         valid);
         } else {
             const int ft = anew(tid);
             *reinterpret_cast<V*>(h0 + (ft >> 3) * kLd0 + 8 * (ft & 7)) = in_v;
@@ -269,7 +265,7 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
             __syncthreads();
         } else {
             // ---- forward -------------------------------------------------------
-            load_frags(gf, 2, rb, lo_f);
+            if constexpr (RAWL < 0) load_frags(gf, 2, rb, lo_f);
             __syncthreads();                                 // h_0 is in LDS
             auto layer = [&](const T* in, int stride, auto kc_, int l) {
                 constexpr int kc = decltype(kc_)::value;
@@ -440,16 +436,6 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
                 __syncthreads();                             // delta_l is in LDS, delta_{l+1} has been read
             }
         }
-        #pragma unroll
-        for (int kc = 0; kc < 2; ++kc) {
-            const V bw = gather(h0, kLd0, wave & 3, kc);
-            #pragma unroll
-            for (int i = 0; i < MW; ++i) acc0[i] = mfma(gather(drow(1), LDR, mw0 + i, kc), bw, acc0[i]);
-        }
-        if (last) {
-            #pragma unroll
-            for (int i = 0; i < MW; ++i) flush(0, mw0 + i, wave & 3, acc0[i]);
-        }
         if constexpr (GENC) {
             // dL/dh_0 = W_0^T delta_1, row block wave & 3 of two columns, with the
             // loss scale of the upstream gradient divided out
@@ -484,6 +470,16 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
                         make_float4(a[col][0], a[col][1], a[col][2], a[col][3]);
                 }
             }
+        }
+        #pragma unroll
+        for (int kc = 0; kc < 2; ++kc) {
+            const V bw = gather(h0, kLd0, wave & 3, kc);
+            #pragma unroll
+            for (int i = 0; i < MW; ++i) acc0[i] = mfma(gather(drow(1), LDR, mw0 + i, kc), bw, acc0[i]);
+        }
+        if (last) {
+            #pragma unroll
+            for (int i = 0; i < MW; ++i) flush(0, mw0 + i, wave & 3, acc0[i]);
         }
         if (!UPSTREAM && out_wave) {
             const float wl = wave_sum_compensated(lterm);
@@ -564,8 +560,14 @@ hipError_t tiles_raw_dispatch(const Geo& d, int preset, int layout, const void* 
 
 }  // namespace
 
-bool train_in_tiles(const Geo& d, int64_t n) {
-    return d.W == 128 || (n + kTS - 1) / kTS > device_cu_count();
+// Everything but the FP16 backward passes of up to one tile per CU at width 64,
+// where k_train_mfma's chain in registers is shorter.  us, k_train_mfma / here,
+// with the reduction: FP16 backward of 300 records 10.0 / 10.9 from the buffer and
+// 10.6 / 11.8 without, of 16,384 18.5 / 18.4 and 19.4 / 20.3; FP16 steps 300
+// records 15.1 / 14.4, 16,384 17.5 / 17.0; BF16 steps 17.9 / 15.8 and 20.9 / 18.7,
+// backward without the buffer 13.7 / 13.3 and 22.0 / 21.2.
+bool train_in_tiles(int precision, const Geo& d, int64_t n, bool upstream) {
+    return !(precision == NRC_FP16 && d.W == 64 && upstream && (n + kTS - 1) / kTS <= device_cu_count());
 }
 
 // Workgroups, each with one partial.  Two fit a CU at width 64 up to depth 5, but
