@@ -73,3 +73,29 @@ def test_weights_from_the_device_equal_weights_from_the_host(N, prec, width, n_h
     caches[1].set_weights_device(torch.from_numpy(w).cuda())
     torch.cuda.synchronize()
     assert torch.equal(caches[0].ws, caches[1].ws)
+
+
+def test_calls_go_to_the_current_stream(N):
+    """The handle the binding passes on is the current stream's, by whatever way it became
+    current, and an explicit stream's own."""
+    side = torch.cuda.Stream()
+    external = torch.cuda.ExternalStream(torch.cuda.Stream().cuda_stream)
+    for s in (torch.cuda.default_stream(), side, external):
+        with torch.cuda.stream(s):
+            assert N._stream(None) == torch.cuda.current_stream().cuda_stream == s.cuda_stream
+    assert N._stream(None) == torch.cuda.current_stream().cuda_stream
+    assert N._stream(side) == N._stream(side.cuda_stream) == side.cuda_stream
+
+
+def test_device_weights_of_any_stride(N):
+    """A strided vector is refused; a matrix of strided rows reaches the cache as its storage lies."""
+    c = N.Cache(N.make_config())
+    w = torch.rand(c.n_params, device="cuda")
+    with pytest.raises(ValueError, match="contiguous"):
+        c.set_weights_device(torch.rand(2 * c.n_params, device="cuda")[::2])
+    with pytest.raises(ValueError, match="float32"):
+        c.set_weights_device(w.double())
+    with pytest.raises(ValueError, match="device tensor"):
+        c.set_weights_device(w.cpu())
+    c.set_weights_device(w.view(-1, 64).t())
+    assert np.array_equal(c.get_weights(), w.cpu().numpy())
