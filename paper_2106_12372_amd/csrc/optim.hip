@@ -18,8 +18,6 @@
 namespace nrc {
 namespace {
 
-constexpr int kRedBlock = 256;
-
 __device__ inline void neumaier_add(float& s, float& c, float x) {
     const float t = s + x;
     if (fabsf(s) >= fabsf(x)) c += (s - t) + x; else c += (x - t) + s;
@@ -91,8 +89,16 @@ template <int N> struct Count { static constexpr int value = N; };
 constexpr int kRedParams = 32;   // weights per workgroup
 constexpr int kRedGroups = 8;    // tile groups per workgroup
 
+// Threads: the groups and, with ADAM, a fifth wave for what the update needs
+// beside the sums.  It ORs the flags and forms the bias corrections (a load and
+// three powf, one after the other) while the other four wait for their partials,
+// and workgroup 0's also adds up the loss.  In the first wave, ahead of its
+// partials' loads, these held every launch up.
+constexpr int kRedThreads = kRedParams * kRedGroups;
+constexpr int red_threads(bool adam) { return kRedThreads + (adam ? 64 : 0); }
+
 template <typename T, bool ADAM, bool NATIVE>
-__global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partials, int n_tiles,
+__global__ __launch_bounds__(red_threads(ADAM)) void k_reduce(const float* __restrict__ partials, int n_tiles,
                                                 const int32_t* __restrict__ tile_bad,
                                                 const float* __restrict__ loss_part, int n_loss,
                                                 float inv_count, float* __restrict__ loss_out, float inv_scale,
@@ -104,53 +110,46 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
                                                 int n_hidden) {
     __shared__ float s_sum[kRedGroups][kRedParams];
     __shared__ float s_cmp[kRedGroups][kRedParams];
+    __shared__ float s_bc[3];
     __shared__ int s_skip;
     const Geo d(width, n_hidden);
     const int P = d.n_params();
     const int tid = threadIdx.x, lane = tid & 63;
     const int pl = tid % kRedParams, grp = tid / kRedParams;
     const int sidx = blockIdx.x * kRedParams + pl;          // partial slot (coalesced across lanes)
+    const bool side = ADAM && __builtin_amdgcn_readfirstlane(tid >> 6) == kRedThreads / 64;
 
-    // Wave 0 ORs the per-tile non-finite flags; the first 256 are loaded now
-    // and combined after the sums, so no load waits on another.
-    int bad4[4] = {0, 0, 0, 0};
-    if (ADAM && tid < 64) {
+    int t_old = 0;
+    if (ADAM) t_old = tslots[parity];
+    if (side) {
+        constexpr int kBad = 8;                             // loads in flight
+        int any = 0;
+        for (int t = lane; t < n_tiles; t += 64 * kBad) {
+            int b[kBad];
+            #pragma unroll
+            for (int u = 0; u < kBad; ++u) b[u] = t + 64 * u < n_tiles ? tile_bad[t + 64 * u] : 0;
+            #pragma unroll
+            for (int u = 0; u < kBad; ++u) any |= b[u];
+        }
+        // bias corrections of the step this update would make (a skipped step
+        // updates nothing): lane 0's of m, lane 1's of v, lane 2's of the EMA
+        const float base = lane == 0 ? hp.beta1 : lane == 1 ? hp.beta2 : ema.alpha;
+        if (lane < (ema.alpha > 0.0f ? 3 : 2)) s_bc[lane] = 1.0f - powf(base, (float)(t_old + 1));
         #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (tid + 64 * u < n_tiles) bad4[u] = tile_bad[tid + 64 * u];
+        for (int off = 32; off >= 1; off >>= 1) any |= __shfl_xor(any, off, 64);
+        if (lane == 0) s_skip = any;
     }
     // The update's operands for this thread's weight are loaded before the
     // partials, so their latency overlaps the sums.
     const bool owner = grp == 0 && sidx < P;
     const int p = NATIVE ? param_of_slot(d, owner ? sidx : 0) : sidx;
     float w0 = 0.0f, m0 = 0.0f, v0 = 0.0f, e0 = 0.0f;
-    int t_old = 0;
+    int64_t fi = 0, bi = 0;
     if (ADAM && owner) {
         w0 = w[p];
         m0 = m[p];
         v0 = v[p];
         if (ema.alpha > 0.0f) e0 = ema.e[p];
-        t_old = tslots[parity];
-    }
-    // Workgroup 0's second wave loads the first 256 per-tile loss terms now,
-    // for the same reason.
-    const bool loss_wave = blockIdx.x == 0 && tid >= 64 && tid < 128 && loss_out != nullptr;
-    float lv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (loss_wave) {
-        #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (lane + 64 * u < n_loss) lv[u] = loss_part[lane + 64 * u];
-    }
-    // Bias corrections of the step this update would make (a skipped step
-    // updates nothing) and the weight's fragment slots, before the partials'
-    // loads (formed while those are in flight, the launch was 0.9 us slower).
-    const float t_next = (float)(t_old + 1);
-    float bc1 = 1.0f, bc2 = 1.0f, bce = 1.0f;
-    int64_t fi = 0, bi = 0;
-    if (ADAM && owner) {
-        bc1 = 1.0f - powf(hp.beta1, t_next);
-        bc2 = 1.0f - powf(hp.beta2, t_next);
-        if (ema.alpha > 0.0f) bce = 1.0f - powf(ema.alpha, t_next);
         if (ffr != nullptr || ema.effr != nullptr) frag_slots(d, p, fi, bi);
     }
     // The thread's partials, every kRedGroups-th, summed in order.  Rounds of 32
@@ -158,7 +157,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
     // last, which only some groups have (64 partials, 4,096 records: one round of 8
     // instead of 8 loads one after another, 2.4 us less per step).
     float s = 0.0f, c = 0.0f;
-    if (sidx < P) {
+    if (!side && sidx < P) {
         const float* src = partials + (int64_t)grp * P + sidx;
         const int64_t step = (int64_t)kRedGroups * P;
         auto round = [&](auto k_) {
@@ -179,25 +178,26 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
         if (k & 1) round(Count<1>{});
         if (grp < n_tiles % kRedGroups) round(Count<1>{});
     }
-    if (ADAM && tid < 64) {
-        int any = bad4[0] | bad4[1] | bad4[2] | bad4[3];
-        for (int t = tid + 256; t < n_tiles; t += 64) any |= tile_bad[t];
-        #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) any |= __shfl_xor(any, off, 64);
-        if (tid == 0) s_skip = any;
+    if (!side) {
+        s_sum[grp][pl] = s;
+        s_cmp[grp][pl] = c;
     }
-    s_sum[grp][pl] = s;
-    s_cmp[grp][pl] = c;
     __syncthreads();
 
-    if (loss_wave) {
+    if (side) {
+        if (blockIdx.x != 0 || loss_out == nullptr) return;
         // compensated sum of the per-tile loss terms, then a compensated
         // combine of the 64 lane sums in a fixed order
+        constexpr int kLoss = 32;                           // loads in flight
         float ls = 0.0f, lc = 0.0f;
-        #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (lane + 64 * u < n_loss) neumaier_add(ls, lc, lv[u]);
-        for (int t = lane + 256; t < n_loss; t += 64) neumaier_add(ls, lc, loss_part[t]);
+        for (int t = lane; t < n_loss; t += 64 * kLoss) {
+            float x[kLoss];
+            #pragma unroll
+            for (int u = 0; u < kLoss; ++u) x[u] = t + 64 * u < n_loss ? loss_part[t + 64 * u] : 0.0f;
+            #pragma unroll
+            for (int u = 0; u < kLoss; ++u)
+                if (t + 64 * u < n_loss) neumaier_add(ls, lc, x[u]);
+        }
         #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
             const float os = __shfl_xor(ls, off, 64), oc = __shfl_xor(lc, off, 64);
@@ -210,6 +210,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
             lc = ac;
         }
         if (lane == 0) *loss_out = (ls + lc) * inv_count;
+        return;
     }
     if (!owner) return;   // workgroup 0's thread 0 has slot 0 and stays
     float gv = 0.0f;
@@ -233,6 +234,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
         if (skipped_out) *skipped_out = skip;
     }
     if (skip) return;
+    const float bc1 = s_bc[0], bc2 = s_bc[1];
     // explicit fused multiply-adds: the rounding does not depend on which
     // product the compiler would contract
     const float m1 = fmaf(hp.beta1, m0, (1.0f - hp.beta1) * gv);
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
     if (ema.alpha > 0.0f) {
         // Eq. 2, bias-corrected: E_t = a E_{t-1} + (1 - a) W_t, W_bar_t = E_t / (1 - a^t).
         const float e1 = fmaf(ema.alpha, e0, (1.0f - ema.alpha) * w1);
-        const float wb = e1 / bce;
+        const float wb = e1 / s_bc[2];
         ema.e[p] = e1;
         ema.wbar[p] = wb;
         if (ema.effr != nullptr) put_frags<T>(d, fi, bi, wb, (T*)ema.effr, (T*)nullptr, false);
@@ -302,7 +304,7 @@ int reduce_blocks(int n_params) { return (n_params + kRedParams - 1) / kRedParam
 
 hipError_t launch_reduce(const Geo& d, bool native, const float* partials, int n_parts,
                          float inv_scale, float* grad, hipStream_t s) {
-    const dim3 grid(reduce_blocks(d.n_params())), block(256);
+    const dim3 grid(reduce_blocks(d.n_params())), block(red_threads(false));
     auto k = native ? k_reduce<_Float16, false, true> : k_reduce<_Float16, false, false>;
     hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_parts, (const int32_t*)nullptr,
                        (const float*)nullptr, 0, 1.0f, (float*)nullptr, inv_scale, grad, (float*)nullptr, (float*)nullptr,
@@ -316,7 +318,7 @@ hipError_t launch_reduce_adam(int precision, const Geo& d, bool native, const fl
                               float inv_count, float* loss_out, float inv_scale, float* w, float* m,
                               float* v, int32_t* tslots, int parity, AdamHyper hp, EmaArgs ema,
                               int32_t* skipped_out, void* ffr, void* bfr, hipStream_t s) {
-    const dim3 grid(reduce_blocks(d.n_params())), block(256);
+    const dim3 grid(reduce_blocks(d.n_params())), block(red_threads(true));
     if (precision == NRC_BF16) {
         auto k = native ? k_reduce<__bf16, true, true> : k_reduce<__bf16, true, false>;
         hipLaunchKernelGGL(k, grid, block, 0, s, partials, n_parts, tile_bad, loss_part, n_loss, inv_count,

@@ -104,3 +104,20 @@ def test_a_non_finite_gradient_in_any_tile_skips_the_step(N):
             _, skipped = N.nrc_train_step(c, enc, bad)
             assert int(skipped.item()) == 1
             assert np.array_equal(c.get_weights(), w)
+
+
+@pytest.mark.parametrize("n", [64 * 64, 64 * 65, 64 * 2048 - 1, 64 * 2049 + 3])
+def test_the_loss_of_any_number_of_tiles(N, n):
+    """The reduction adds the tiles' loss terms in rounds of 2,048: the loss of n records is
+    the mean over its parts (compensated FP32 sums of non-negative terms, one rounding each)."""
+    enc = torch.from_numpy(sd.uniform_features(n, 64, 3)).cuda().half()
+    y = torch.rand(n, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+
+    def loss(lo, hi):
+        c = N.Cache(N.make_config(precision="fp16", n_hidden=2))
+        c.set_weights(sd.glorot_weights(64, 2, seed=3))
+        return N.nrc_train_step(c, enc[lo:hi].clone(), y[lo:hi].clone())[0].item() * (hi - lo)
+
+    parts = sum(loss(lo, min(lo + 4096, n)) for lo in range(0, n, 4096))
+    # a tile's 64 terms are added in FP32 with compensation; scaling and its inverse round twice
+    assert abs(loss(0, n) - parts) <= 8 * 2.0 ** -24 * parts
