@@ -24,7 +24,18 @@ __device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-template <typename T> __device__ inline T to_t(float x) { return (T)x; }
+// x r rounded to the operand type.  FP16: once, by the mixed multiply-add; left
+// to the compiler the product is rounded to FP32 first in some kernels and not in
+// others, and a record's gradient would depend on the kernel its batch takes.
+template <typename T> __device__ inline T mul_to(float x, float r) {
+    if constexpr (__is_same(T, _Float16)) {
+        unsigned int d = 0;
+        asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "+v"(d) : "v"(x), "v"(r));
+        return __builtin_bit_cast(_Float16, (unsigned short)d);
+    } else {
+        return (T)(x * r);
+    }
+}
 
 // A compile-time integer as an argument.
 template <int N> struct IntC { static constexpr int value = N; };

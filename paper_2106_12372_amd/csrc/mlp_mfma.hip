@@ -591,7 +591,7 @@ __device__ inline void store_reflectance(T* dst, const float* f, int fcol) {
     constexpr int ac = PRESET == NRC_PRESET_CONFIG ? kAlbedoColConfig : kAlbedoColPaper;
     if (fcol) {
         #pragma unroll
-        for (int c = 0; c < 3; ++c) r[c] = (float)to_t<T>(f[ac + c]) + (float)to_t<T>(f[ac + 3 + c]);
+        for (int c = 0; c < 3; ++c) r[c] = (float)(T)f[ac + c] + (float)(T)f[ac + 3 + c];
     }
     *reinterpret_cast<f32x4*>(dst + 64) = r;
 }
@@ -1047,15 +1047,13 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
     // ---- dL/dy; lanes 0..15 of each wave hold y[0..2] ------------------------
     // The prediction is the network output times r; the network's output
     // gradient is the prediction's gradient times r.
-    float d0 = 0.f, d1 = 0.f, d2 = 0.f;
-    if (g == 0 && valid) {
-        d0 = tg[0] * grad_scale * r[0];
-        d1 = tg[1] * grad_scale * r[1];
-        d2 = tg[2] * grad_scale * r[2];
-    }
     V bd = zero8<V>();
+    if (g == 0 && valid) {
+        bd[0] = mul_to<T>(tg[0] * grad_scale, r[0]);
+        bd[1] = mul_to<T>(tg[1] * grad_scale, r[1]);
+        bd[2] = mul_to<T>(tg[2] * grad_scale, r[2]);
+    }
     if (g == 0 && chain) {
-        bd[0] = to_t<T>(d0); bd[1] = to_t<T>(d1); bd[2] = to_t<T>(d2);
         dO[0 * LDT + sl] = bd[0];
         dO[1 * LDT + sl] = bd[1];
         dO[2 * LDT + sl] = bd[2];

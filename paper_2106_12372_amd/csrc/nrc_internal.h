@@ -136,19 +136,57 @@ __device__ inline float relu(float x) { return __builtin_elementwise_maximum(x, 
 // in a fixed butterfly order; every lane ends with the same value.  Each pair
 // sum is formed with the lower lane's operand first and carries both lanes'
 // compensation terms, so the two partners of a pair compute identical bits.
+//
+// The partner's values come through VALU lane moves: by ds_bpermute, one LDS
+// latency per step, the sum was 0.8k cycles at the end of every training tile.
+template <int OFF>
+__device__ inline void lane_pair(float x, bool lo, float& a, float& b) {   // x of the pair's lower and upper lane
+    const int i = __builtin_bit_cast(int, x);
+    if constexpr (OFF >= 16) {
+        // the swaps leave the lower lanes' rows in one result, the upper lanes' in the other
+        const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap(i, i, false, false)
+                                 : __builtin_amdgcn_permlane16_swap(i, i, false, false);
+        const unsigned int lower = r[0], upper = r[1];
+        a = __builtin_bit_cast(float, lower);
+        b = __builtin_bit_cast(float, upper);
+    } else {
+        int o = 0;
+        if (OFF == 8) o = __builtin_amdgcn_mov_dpp(i, 0x128, 0xf, 0xf, true);         // rotation by 8 in rows of 16
+        if (OFF == 4) {
+            o = __builtin_amdgcn_mov_dpp(i, 0x141, 0xf, 0xf, true);                   // mirrored in rows of 8: lane ^ 7
+            o = __builtin_amdgcn_mov_dpp(o, 0x1b, 0xf, 0xf, true);                    // mirrored in rows of 4: lane ^ 3
+        }
+        if (OFF == 2) o = __builtin_amdgcn_mov_dpp(i, 0x4e, 0xf, 0xf, true);          // lanes 2 3 0 1 of each four
+        if (OFF == 1) o = __builtin_amdgcn_mov_dpp(i, 0xb1, 0xf, 0xf, true);          // lanes 1 0 3 2
+        const float y = __builtin_bit_cast(float, o);
+        a = lo ? x : y;
+        b = lo ? y : x;
+    }
+}
+
+template <int OFF>
+__device__ inline void pair_sum(float& s, float& c, int lane) {
+    float a, b, ca, cb;
+    const bool lo = (lane & OFF) == 0;
+    lane_pair<OFF>(s, lo, a, b);
+    lane_pair<OFF>(c, lo, ca, cb);
+    const float t = a + b;
+    const float e = fabsf(a) >= fabsf(b) ? (a - t) + b : (b - t) + a;
+    c = (ca + cb) + e;
+    s = t;
+}
+
+// LANES = 16: only the wave's first 16 lanes hold terms (lane 0 has the sum).
+template <int LANES = 64>
 __device__ inline float wave_sum_compensated(float v) {
     const int lane = __lane_id();
     float s = v, c = 0.0f;
-    #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const float os = __shfl_xor(s, off, 64), oc = __shfl_xor(c, off, 64);
-        const bool lo = (lane & off) == 0;
-        const float a = lo ? s : os, b = lo ? os : s;
-        const float t = a + b;
-        const float e = fabsf(a) >= fabsf(b) ? (a - t) + b : (b - t) + a;
-        c = ((lo ? c : oc) + (lo ? oc : c)) + e;
-        s = t;
-    }
+    if (LANES > 32) pair_sum<32>(s, c, lane);
+    if (LANES > 16) pair_sum<16>(s, c, lane);
+    pair_sum<8>(s, c, lane);
+    pair_sum<4>(s, c, lane);
+    pair_sum<2>(s, c, lane);
+    pair_sum<1>(s, c, lane);
     return s + c;
 }
 

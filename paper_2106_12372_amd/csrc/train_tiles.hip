@@ -22,12 +22,13 @@
 //
 // Bound by LDS traffic and the barrier between layers.  Cycle stamps of a tile:
 // width 128 (FP16) 28k cycles, 1.9k per forward layer, 3.2k per backward layer
-// with its weight gradient; width 64, two workgroups per CU, 15k, 0.9k and 1.4k.
+// with its weight gradient; width 64, two workgroups per CU, 15k, 0.9k and 1.4k
+// (a backward layer reads 88 KB from LDS, 0.7k cycles at 128 bytes each).
 // The partials' one write takes 27k cycles at width 128 (76 MB over the chip, at
 // the rate of a copy).  Whole training steps, us, k_train_mfma before and now:
-// width 64 FP16 65,536 records 48 / 34, 262,144 183 / 88, BF16 262,144 232 / 96;
-// width 128 FP16 1,000 records 53 / 28, 16,384 97 / 45, 65,536 306 / 78, BF16
-// 65,536 438 / 100.  At width 128 a wave with two row blocks and two columns
+// width 64 FP16 16,384 records 17.5 / 16.1, 65,536 48 / 29, 262,144 183 / 73, BF16
+// 1,000 records 18.6 / 14.1, 262,144 232 / 82; width 128 FP16 1,000 records 53 / 28,
+// 16,384 97 / 41, 65,536 306 / 73, BF16 65,536 438 / 100.  At width 128 a wave with two row blocks and two columns
 // instead of one and four was slower (83 and 134 us: its fragments spill).
 #include "mfma_ops.h"
 #include "nrc_internal.h"
@@ -51,11 +52,12 @@ __host__ __device__ constexpr int tiles_lds_bytes(int W, int H) {
 // forward pass from the activation buffer ([record][layer][feature], and the
 // network outputs [record][4]) instead of computing it; kActStore computes it,
 // writes the buffer and the predictions (to out) and stops there.  out: dL/d(input)
-// in the GENC forms.  MAXH: the most hidden layers the accumulators hold.
+// in the GENC forms.  MAXH: the most hidden layers the accumulators hold.  WGS:
+// workgroups per CU.
 constexpr int kActNone = 0, kActStore = 1, kActLoad = 2;
 
-template <typename T, int W, int MAXH, bool UPSTREAM, bool GENC, int ACT, int RAWL, int PRESET>
-__global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_train_tiles(const T* __restrict__ ffr, const T* __restrict__ bfr,
+template <typename T, int W, int MAXH, int WGS, bool UPSTREAM, bool GENC, int ACT, int RAWL, int PRESET>
+__global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* __restrict__ ffr, const T* __restrict__ bfr,
                                                              const T* __restrict__ enc,
                                                              const float* __restrict__ tgt,
                                                              const int32_t* __restrict__ idx, int64_t n, int n_hidden,
@@ -151,6 +153,21 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
             for (int j = 0; j < NW; ++j) accw[l][i][j] = zero;
     }
 
+    // With 256 registers per wave (one workgroup per CU) a layer's LDS reads at width
+    // 64 go out together, before its first product: left to the compiler, each
+    // product waits for operands read just before it, nine LDS latencies one after
+    // another in a backward layer (16,384 records, us per step: FP16 16.6 -> 16.2, BF16
+    // 17.7 -> 17.0).  128 registers hold neither these nor the weights below beside
+    // the sums (they spill).
+    constexpr bool ROOMY = W == 64 && WGS == 1;
+    // FP16: the weights of the whole backward chain are loaded ahead of it, too, as
+    // loads behind the stores of a layer's sums wait for those (1,000 records 13.6 ->
+    // 13.3 us per step; BF16, with its hi and lo parts, 17.1 -> 17.4 at 16,384).
+    constexpr bool EARLY = ROOMY && MAXH <= 5 && !SPLIT;
+    Frag fb[EARLY ? MAXH : 1][KC];
+    auto reads_first = [] {
+        if (ROOMY) __builtin_amdgcn_sched_barrier(0);
+    };
     // The weights are read anew for each tile, and what only a part of the tile
     // needs is computed there: held in registers across the tiles (their loads and
     // addresses are loop-invariant) they would spill the accumulators.
@@ -167,7 +184,7 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
     // sums leave as soon as the last tile has added to them, beside the layers
     // before it.
     float* part = partials + (int64_t)blockIdx.x * P;
-    bool bad = false;
+    float bad = 0.0f;                        // NaN once a sum is not finite
     auto flush = [&](int l, int mbp, int nbp, const f32x4& a) {
         const int fl = anew(lane), fg = fl >> 4, fn = fl & 15;
         const int NB = l == 0 ? 4 : MB;
@@ -176,7 +193,13 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
         const int lq = l == 0 ? fn : 4 * (2 * (nbp & 1) + (fn >> 3)) + (fn & 3);
         __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(part + geo.w_off(l) + ((mb * NB + nb) * 64 + 16 * gq + lq) * 4));
         #pragma unroll
-        for (int j = 0; j < 4; ++j) bad |= !isfinite(a[j]);
+        for (int j = 0; j < 4; ++j) bad = fmaf(a[j], 0.0f, bad);
+    };
+    auto flush_layer = [&](int l) {
+        #pragma unroll
+        for (int i = 0; i < MW; ++i)
+            #pragma unroll
+            for (int j = 0; j < NW; ++j) flush(l, mw0 + i, nw0 + j, accw[l - 1][i][j]);
     };
     // Encoded rows: a thread moves 16 bytes of record tid / 8, and the output lanes
     // their record's targets; both are loaded during the tile before.
@@ -270,11 +293,19 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
             auto layer = [&](const T* in, int stride, auto kc_, int l) {
                 constexpr int kc = decltype(kc_)::value;
                 f32x4 a[NC];
+                V b[KC][NC];
+                if (ROOMY) {
+                    #pragma unroll
+                    for (int c = 0; c < kc; ++c)
+                        #pragma unroll
+                        for (int col = 0; col < NC; ++col) b[c][col] = get(in, stride, col0 + col, c);
+                    reads_first();
+                }
                 #pragma unroll
                 for (int c = 0; c < kc; ++c)
                     #pragma unroll
                     for (int col = 0; col < NC; ++col)
-                        a[col] = mm(fr[c], get(in, stride, col0 + col, c), c == 0 ? zero : a[col]);
+                        a[col] = mm(fr[c], ROOMY ? b[c][col] : get(in, stride, col0 + col, c), c == 0 ? zero : a[col]);
                 // the next layer's weights are on their way before the barrier
                 if (l + 1 < n_hidden)
                     load_frags(gf + geo.fwd_base(l + 1) * 64, KC, rb, lo_f);
@@ -320,18 +351,27 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
         }
         // delta_H's weights: K = 32, one fragment per row block
         fr[0] = ld(gb + (geo.bwd_base(n_hidden) + rb) * 64, lo_b);
+        if (EARLY) {
+            #pragma unroll
+            for (int l = MAXH - 1; l >= (GENC ? 0 : 1); --l)
+                if (l < n_hidden) {
+                    #pragma unroll
+                    for (int c = 0; c < KC; ++c)
+                        fb[l][c] = ld(gb + (geo.bwd_base(l) + (l ? rb : wave & 3) * KC + c) * 64, lo_b);
+                }
+        }
 
         // ---- loss gradient (Eq. 5) in lanes 0 .. 15 of waves 0 .. 3 --------------
         float lterm = 0.0f;
         if (out_wave) {
             float r[3];
             reflectance_operand(*reinterpret_cast<const V*>(h0 + sl * kLd0 + 32 + 8 * g), fcol, ln, r);
-            float d0 = 0.f, d1 = 0.f, d2 = 0.f;
+            t4 d = t4{0, 0, 0, 0};
             if (g == 0 && valid) {
                 if (UPSTREAM) {
-                    d0 = tg[0] * grad_scale * r[0];
-                    d1 = tg[1] * grad_scale * r[1];
-                    d2 = tg[2] * grad_scale * r[2];
+                    d[0] = mul_to<T>(tg[0] * grad_scale, r[0]);
+                    d[1] = mul_to<T>(tg[1] * grad_scale, r[1]);
+                    d[2] = mul_to<T>(tg[2] * grad_scale, r[2]);
                 } else {
                     const float p0 = y[0] * r[0], p1 = y[1] * r[1], p2 = y[2] * r[2];
                     const float lum = (p0 + p1 + p2) * (1.0f / 3.0f);
@@ -340,13 +380,12 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
                     const float e1 = p1 - tg[1];
                     const float e2 = p2 - tg[2];
                     lterm = fmaf(e2, e2, fmaf(e1, e1, e0 * e0)) * inv_den;
-                    d0 = 2.0f * e0 * inv_den * grad_scale * r[0];
-                    d1 = 2.0f * e1 * inv_den * grad_scale * r[1];
-                    d2 = 2.0f * e2 * inv_den * grad_scale * r[2];
+                    d[0] = mul_to<T>(2.0f * e0 * inv_den * grad_scale, r[0]);
+                    d[1] = mul_to<T>(2.0f * e1 * inv_den * grad_scale, r[1]);
+                    d[2] = mul_to<T>(2.0f * e2 * inv_den * grad_scale, r[2]);
                 }
             }
             if (g == 0) {
-                const t4 d = t4{to_t<T>(d0), to_t<T>(d1), to_t<T>(d2), (T)0};
                 dO[0 * kLdT + sl] = d[0];
                 dO[1 * kLdT + sl] = d[1];
                 dO[2 * kLdT + sl] = d[2];
@@ -358,12 +397,16 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
         if constexpr (RAWL < 0) fetch();                     // the next tile's rows and targets
 
         // ---- data backward and weight gradients --------------------------------
-        // delta_l masked by ReLU'(z_l) into its row store
-        auto put_delta = [&](int l, const f32x4 (&a)[NC]) {
+        // h_l where this wave's delta_l goes, and delta_l masked by ReLU'(z_l) into its
+        // row store
+        auto h_at = [&](int l, int col) {
+            return *reinterpret_cast<const t4*>(hrow(l) + (16 * (col0 + col) + ln) * LDR + 32 * (rb >> 1) + 8 * g +
+                                                4 * (rb & 1));
+        };
+        auto put_delta = [&](int l, const f32x4 (&a)[NC], const t4 (&h)[NC]) {
             #pragma unroll
             for (int col = 0; col < NC; ++col) {
-                const t4 hv = *reinterpret_cast<const t4*>(hrow(l) + (16 * (col0 + col) + ln) * LDR + 32 * (rb >> 1) +
-                                                           8 * g + 4 * (rb & 1));
+                const t4 hv = ROOMY ? h[col] : h_at(l, col);
                 f32x4 v;
                 #pragma unroll
                 for (int j = 0; j < 4; ++j) v[j] = (float)hv[j] > 0.0f ? a[col][j] : 0.0f;
@@ -372,30 +415,43 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
         };
         {
             f32x4 a[NC];
+            t4 hv[NC];
+            V ho[2], dv[2];
+            auto out_operands = [&](int kc) {
+                dv[kc] = ln < kNOut ? *reinterpret_cast<const V*>(dO + ln * kLdT + 32 * kc + 8 * g) : zero8<V>();
+                ho[kc] = gather(hrow(n_hidden), LDR, wave, kc);
+            };
             #pragma unroll
             for (int col = 0; col < NC; ++col) {
                 V bd = zero8<V>();
                 const t4 d = *reinterpret_cast<const t4*>(dR + (16 * (col0 + col) + ln) * 4);
                 if (g == 0) { bd[0] = d[0]; bd[1] = d[1]; bd[2] = d[2]; }
                 a[col] = mm(fr[0], bd, zero);
+                if (ROOMY) hv[col] = h_at(n_hidden, col);
             }
-            if (n_hidden > 1)
-                load_frags(gb + geo.bwd_base(n_hidden - 1) * 64, KC, rb, lo_b);
-            else if (GENC)
-                load_frags(gb, KC, wave & 3, lo_b);
-            put_delta(n_hidden, a);
+            if (ROOMY && wave < MB) {
+                out_operands(0);
+                out_operands(1);
+            }
+            if (!EARLY) {
+                if (n_hidden > 1)
+                    load_frags(gb + geo.bwd_base(n_hidden - 1) * 64, KC, rb, lo_b);
+                else if (GENC)
+                    load_frags(gb, KC, wave & 3, lo_b);
+            }
+            put_delta(n_hidden, a, hv);
             if (wave < MB) {
                 #pragma unroll
                 for (int kc = 0; kc < 2; ++kc) {
-                    const V av = ln < kNOut ? *reinterpret_cast<const V*>(dO + ln * kLdT + 32 * kc + 8 * g) : zero8<V>();
-                    acco = mfma(av, gather(hrow(n_hidden), LDR, wave, kc), acco);
+                    if (!ROOMY) out_operands(kc);
+                    acco = mfma(dv[kc], ho[kc], acco);
                 }
                 if (last && g == 0) {
                     const int f = 32 * (wave >> 1) + 16 * ((ln >> 2) & 1) + 4 * (2 * (wave & 1) + (ln >> 3)) + (ln & 3);
                     #pragma unroll
                     for (int j = 0; j < kNOut; ++j) {
                         part[geo.w_off(n_hidden) + j * W + f] = acco[j];
-                        bad |= !isfinite(acco[j]);
+                        bad = fmaf(acco[j], 0.0f, bad);
                     }
                 }
             }
@@ -405,34 +461,47 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
         for (int l = MAXH - 1; l >= 1; --l) {
             if (l < n_hidden) {
                 f32x4 a[NC];
+                t4 hv[NC];
+                V dv[KC][NC], bw[2][NW], aw[2][MW];
+                auto operands = [&](int kc) {
+                    #pragma unroll
+                    for (int j = 0; j < NW; ++j) bw[kc][j] = gather(hrow(l), LDR, nw0 + j, kc);
+                    #pragma unroll
+                    for (int i = 0; i < MW; ++i) aw[kc][i] = gather(drow(l + 1), LDR, mw0 + i, kc);
+                };
+                if (ROOMY) {
+                    #pragma unroll
+                    for (int c = 0; c < KC; ++c)
+                        #pragma unroll
+                        for (int col = 0; col < NC; ++col) dv[c][col] = get(drow(l + 1), LDR, col0 + col, c);
+                    #pragma unroll
+                    for (int col = 0; col < NC; ++col) hv[col] = h_at(l, col);
+                    operands(0);
+                    operands(1);
+                    reads_first();
+                }
                 #pragma unroll
                 for (int c = 0; c < KC; ++c)
                     #pragma unroll
                     for (int col = 0; col < NC; ++col)
-                        a[col] = mm(fr[c], get(drow(l + 1), LDR, col0 + col, c), c == 0 ? zero : a[col]);
-                if (l > 1)
-                    load_frags(gb + geo.bwd_base(l - 1) * 64, KC, rb, lo_b);
-                else if (GENC)
-                    load_frags(gb, KC, wave & 3, lo_b);
-                put_delta(l, a);
+                        a[col] = mm(EARLY ? fb[l][c] : fr[c], ROOMY ? dv[c][col] : get(drow(l + 1), LDR, col0 + col, c),
+                                    c == 0 ? zero : a[col]);
+                if (!EARLY) {
+                    if (l > 1)
+                        load_frags(gb + geo.bwd_base(l - 1) * 64, KC, rb, lo_b);
+                    else if (GENC)
+                        load_frags(gb, KC, wave & 3, lo_b);
+                }
+                put_delta(l, a, hv);
                 #pragma unroll
                 for (int kc = 0; kc < 2; ++kc) {
-                    V bw[NW];
-                    #pragma unroll
-                    for (int j = 0; j < NW; ++j) bw[j] = gather(hrow(l), LDR, nw0 + j, kc);
-                    #pragma unroll
-                    for (int i = 0; i < MW; ++i) {
-                        const V aw = gather(drow(l + 1), LDR, mw0 + i, kc);
-                        #pragma unroll
-                        for (int j = 0; j < NW; ++j) accw[l - 1][i][j] = mfma(aw, bw[j], accw[l - 1][i][j]);
-                    }
-                }
-                if (last) {
+                    if (!ROOMY) operands(kc);
                     #pragma unroll
                     for (int i = 0; i < MW; ++i)
                         #pragma unroll
-                        for (int j = 0; j < NW; ++j) flush(l, mw0 + i, nw0 + j, accw[l - 1][i][j]);
+                        for (int j = 0; j < NW; ++j) accw[l - 1][i][j] = mfma(aw[kc][i], bw[kc][j], accw[l - 1][i][j]);
                 }
+                if (last) flush_layer(l);
                 __syncthreads();                             // delta_l is in LDS, delta_{l+1} has been read
             }
         }
@@ -447,7 +516,7 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
             for (int c = 0; c < KC; ++c)
                 #pragma unroll
                 for (int col = 0; col < 2; ++col)
-                    a[col] = mm(fr[c], get(drow(1), LDR, cg + col, c), c == 0 ? zero : a[col]);
+                    a[col] = mm(EARLY ? fb[0][c] : fr[c], get(drow(1), LDR, cg + col, c), c == 0 ? zero : a[col]);
             #pragma unroll
             for (int col = 0; col < 2; ++col) {
                 const int rec = 16 * (cg + col) + fn;
@@ -471,18 +540,31 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
                 }
             }
         }
-        #pragma unroll
-        for (int kc = 0; kc < 2; ++kc) {
-            const V bw = gather(h0, kLd0, wave & 3, kc);
+        {
+            V bw[2], aw[2][MW];
+            auto operands = [&](int kc) {
+                bw[kc] = gather(h0, kLd0, wave & 3, kc);
+                #pragma unroll
+                for (int i = 0; i < MW; ++i) aw[kc][i] = gather(drow(1), LDR, mw0 + i, kc);
+            };
+            if (ROOMY) {
+                operands(0);
+                operands(1);
+                reads_first();
+            }
             #pragma unroll
-            for (int i = 0; i < MW; ++i) acc0[i] = mfma(gather(drow(1), LDR, mw0 + i, kc), bw, acc0[i]);
+            for (int kc = 0; kc < 2; ++kc) {
+                if (!ROOMY) operands(kc);
+                #pragma unroll
+                for (int i = 0; i < MW; ++i) acc0[i] = mfma(aw[kc][i], bw[kc], acc0[i]);
+            }
         }
         if (last) {
             #pragma unroll
             for (int i = 0; i < MW; ++i) flush(0, mw0 + i, wave & 3, acc0[i]);
         }
         if (!UPSTREAM && out_wave) {
-            const float wl = wave_sum_compensated(lterm);
+            const float wl = wave_sum_compensated<16>(lterm);
             if (lane == 0) wsum[wave] = wl;
         }
         __syncthreads();                                     // h_0 and delta_1 have been read
@@ -499,8 +581,22 @@ __global__ __launch_bounds__(64 * kWaves, W == 64 && MAXH <= 5 ? 4 : 2) void k_t
     }
 
     if constexpr (ACT == kActStore) return;
-    const int any_bad = __syncthreads_or(bad ? 1 : 0);
+    const int any_bad = __syncthreads_or(bad != 0.0f ? 1 : 0);
     if (tid == 0 && part_bad) part_bad[blockIdx.x] = any_bad ? 1 : 0;
+}
+
+template <typename T, int W, int MAXH, int WGS, bool UP, bool GE, int ACT, int RAWL, int PRESET>
+hipError_t tiles_launch_as(const Geo& d, const void* ffr, const void* bfr, const void* enc, const float* tgt,
+                        const int32_t* idx, int64_t n, float loss_eps, float grad_scale, float* partials,
+                        float* loss_part, int32_t* part_bad, float* out, hipStream_t s, void* act, float* act_y,
+                        LcgGather lg) {
+    const size_t lds = (size_t)tiles_lds_bytes(W, d.H);
+    auto k = k_train_tiles<T, W, MAXH, WGS, UP, GE, ACT, RAWL, PRESET>;
+    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3((unsigned)train_parts(d, n)), dim3(64 * kWaves), lds, s, (const T*)ffr, (const T*)bfr,
+                       (const T*)enc, tgt, idx, n, d.H, loss_eps, grad_scale, partials, loss_part, part_bad, out,
+                       d.F, (T*)act, act_y, lg);
+    return hipGetLastError();
 }
 
 template <typename T, int W, int MAXH, bool UP, bool GE, int ACT, int RAWL, int PRESET>
@@ -508,13 +604,14 @@ hipError_t tiles_launch(const Geo& d, const void* ffr, const void* bfr, const vo
                         const int32_t* idx, int64_t n, float loss_eps, float grad_scale, float* partials,
                         float* loss_part, int32_t* part_bad, float* out, hipStream_t s, void* act, float* act_y,
                         LcgGather lg) {
-    const size_t lds = (size_t)tiles_lds_bytes(W, d.H);
-    auto k = k_train_tiles<T, W, MAXH, UP, GE, ACT, RAWL, PRESET>;
-    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3((unsigned)train_parts(d, n)), dim3(64 * kWaves), lds, s, (const T*)ffr, (const T*)bfr,
-                       (const T*)enc, tgt, idx, n, d.H, loss_eps, grad_scale, partials, loss_part, part_bad, out,
-                       d.F, (T*)act, act_y, lg);
-    return hipGetLastError();
+    if constexpr (W == 64 && MAXH <= 5)
+        if (train_parts(d, n) > device_cu_count())
+            return tiles_launch_as<T, W, MAXH, 2, UP, GE, ACT, RAWL, PRESET>(d, ffr, bfr, enc, tgt, idx, n, loss_eps,
+                                                                             grad_scale, partials, loss_part,
+                                                                             part_bad, out, s, act, act_y, lg);
+    return tiles_launch_as<T, W, MAXH, 1, UP, GE, ACT, RAWL, PRESET>(d, ffr, bfr, enc, tgt, idx, n, loss_eps,
+                                                                     grad_scale, partials, loss_part, part_bad, out,
+                                                                     s, act, act_y, lg);
 }
 
 template <typename T, int W, int MAXH>
