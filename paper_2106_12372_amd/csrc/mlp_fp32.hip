@@ -261,9 +261,9 @@ __device__ inline void wave_lds_sync() {
 // feeds 4 products instead of 16, a quarter of the LDS rate.  Encoded rows, us
 // before (64-query tiles) and now: 1,000 queries 43.6 / 10.2, 70,000 45.8 /
 // 30.0, 300,000 119 / 99, 2,073,600 638 / 628.
-template <bool RAW, int PRESET, int LAYOUT>
+template <bool RAW, int PRESET, int LAYOUT, bool STORE = false>
 __device__ inline void query_units(const float* __restrict__ w, const float* __restrict__ in, int64_t n,
-                                   float* __restrict__ rgb, int H, int fcol) {
+                                   float* __restrict__ rgb, int H, int fcol, float* __restrict__ act = nullptr) {
     extern __shared__ f4 sw[];
     constexpr int RW = LAYOUT == NRC_RAW14 ? 14 : 16, NT = 64 * kQWaves;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -273,7 +273,7 @@ __device__ inline void query_units(const float* __restrict__ w, const float* __r
     // one each, then claim the rest one at a time
     __shared__ int claimed;
     if (tid == 0) claimed = kQWaves;
-    const int64_t n_units = (n + 15) / 16;
+    const int64_t n_units = STORE ? (n + kTile - 1) / kTile * (kTile / 16) : (n + 15) / 16;
     const int64_t per = n_units / gridDim.x, extra = n_units % gridDim.x;
     const int64_t u_begin = (int64_t)blockIdx.x * per + ((int64_t)blockIdx.x < extra ? blockIdx.x : extra);
     const int64_t u_end = u_begin + per + ((int64_t)blockIdx.x < extra ? 1 : 0);
@@ -324,7 +324,7 @@ __device__ inline void query_units(const float* __restrict__ w, const float* __r
         int k = 0;
         if (lane == 0) k = atomicAdd(&claimed, 1);
         after = u_begin + __builtin_amdgcn_readfirstlane(k);
-        float act[16], r[kNOut] = {1.0f, 1.0f, 1.0f};
+        float h[16], r[kNOut] = {1.0f, 1.0f, 1.0f};
         if constexpr (RAW) {
             wave_lds_sync();
             #pragma unroll
@@ -343,7 +343,7 @@ __device__ inline void query_units(const float* __restrict__ w, const float* __r
         }
         #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            act[4 * b] = nxt[b].x; act[4 * b + 1] = nxt[b].y; act[4 * b + 2] = nxt[b].z; act[4 * b + 3] = nxt[b].w;
+            h[4 * b] = nxt[b].x; h[4 * b + 1] = nxt[b].y; h[4 * b + 2] = nxt[b].z; h[4 * b + 3] = nxt[b].w;
         }
         const bool more = after < u_end;
         if (more) load_in(after);
@@ -361,18 +361,28 @@ __device__ inline void query_units(const float* __restrict__ w, const float* __r
                 for (int q = 0; q < 4; ++q)
                     #pragma unroll
                     for (int ob = 0; ob < 4; ++ob)
-                        acc[ob] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ob][q], act[4 * obp + q], acc[ob], 0, 0, 0);
+                        acc[ob] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ob][q], h[4 * obp + q], acc[ob], 0, 0, 0);
             }
             #pragma unroll
             for (int ob = 0; ob < 4; ++ob)
                 #pragma unroll
-                for (int q = 0; q < 4; ++q) act[4 * ob + q] = relu(acc[ob][q]);
+                for (int q = 0; q < 4; ++q) h[4 * ob + q] = relu(acc[ob][q]);
+            if constexpr (STORE) {
+                // rows past the end: zeros, as their deltas multiply them
+                const int64_t s = row_of(unit);
+                float* dst = act + ((s / kTile * H + l) * kTile + s % kTile) * kW + 4 * g;
+                #pragma unroll
+                for (int ob = 0; ob < 4; ++ob) {
+                    const f4 v = f4{h[4 * ob], h[4 * ob + 1], h[4 * ob + 2], h[4 * ob + 3]};
+                    *reinterpret_cast<f4*>(dst + 16 * ob) = s < n ? v : f4{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+            }
         }
         f4 po = f4{0.0f, 0.0f, 0.0f, 0.0f};
         #pragma unroll
         for (int b = 0; b < 4; ++b)
             #pragma unroll
-            for (int q = 0; q < 4; ++q) po = __builtin_amdgcn_mfma_f32_4x4x1f32(wo[b][q], act[4 * b + q], po, 0, 0, 0);
+            for (int q = 0; q < 4; ++q) po = __builtin_amdgcn_mfma_f32_4x4x1f32(wo[b][q], h[4 * b + q], po, 0, 0, 0);
         float y[kNOut];
         #pragma unroll
         for (int o = 0; o < kNOut; ++o) {
@@ -382,6 +392,10 @@ __device__ inline void query_units(const float* __restrict__ w, const float* __r
         }
         const int64_t s = row_of(unit);
         if (g == 0 && s < n) store_query(rgb, s, y, r);
+        if constexpr (STORE) {
+            if (g == 0 && s < n)
+                *reinterpret_cast<f4*>(act + (n_units * 16 * H) * kW + s * 4) = f4{y[0], y[1], y[2], 0.0f};
+        }
         if constexpr (RAW) {
             if (more) encode_shared<PRESET, LAYOUT>(x, h0, g, true);
         }
@@ -392,6 +406,15 @@ __global__ __launch_bounds__(64 * kQWaves) void k_fwd_fp32(const float* __restri
                                                           const float* __restrict__ enc, int64_t n,
                                                           float* __restrict__ rgb, int n_hidden, int fcol) {
     query_units<false, NRC_PRESET_CONFIG, NRC_RAW14>(w, enc, n, rgb, n_hidden, fcol);
+}
+
+// The autograd form's forward pass: the activations go to its buffer (see
+// k_train_fp32) as the layers end.
+__global__ __launch_bounds__(64 * kQWaves) void k_fwd_store_fp32(const float* __restrict__ w,
+                                                                const float* __restrict__ enc, int64_t n,
+                                                                float* __restrict__ rgb, int n_hidden, int fcol,
+                                                                float* __restrict__ act) {
+    query_units<false, NRC_PRESET_CONFIG, NRC_RAW14, true>(w, enc, n, rgb, n_hidden, fcol, act);
 }
 
 template <int PRESET, int LAYOUT>
@@ -912,16 +935,16 @@ __global__ __launch_bounds__(64 * (kChainWaves + kGradWaves)) void k_train_fp32(
 // hidden layer, 16 H KB, fill most of the CU's LDS), its waves claiming the
 // tiles or units of the workgroup's share.
 inline size_t query_lds_bytes(const Geo& d) { return (size_t)(16 * d.H) * 64 * sizeof(f4); }
-template <typename K>
+template <typename K, typename... More>
 hipError_t query_launch(K kernel, const Geo& d, size_t lds, const float* w, const float* in, int64_t n, float* rgb,
-                        hipStream_t s) {
+                        hipStream_t s, More... more) {
     const int64_t tiles = (n + 63) / 64, cus = device_cu_count();
     if (tiles == 0) return hipSuccess;
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     // one workgroup per CU, or one per tile where there are fewer tiles
     hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles < cus ? tiles : cus)), dim3(64 * kQWaves), lds, s, w, in, n, rgb,
-                       d.H, d.F);
+                       d.H, d.F, more...);
     return hipGetLastError();
 }
 
@@ -1035,6 +1058,11 @@ hipError_t launch_train_fp32_raw(const Geo& d, int preset, int layout, const flo
 
 hipError_t launch_fwd_train_fp32(const Geo& d, const float* w, const float* enc, int64_t n, float* act,
                                  float* rgb, hipStream_t s) {
+    // More tiles than CUs: k_train_fp32 takes them in whole rounds, a tile's
+    // activations leaving LDS only after its last layer (us, k_train_fp32 / units:
+    // 16,384 records 12.9 / 13.4, 20,000 22 / 18.5, 40,001 32.3 / 25.6).
+    if ((n + kTile - 1) / kTile > device_cu_count())
+        return query_launch(k_fwd_store_fp32, d, query_lds_bytes(d), w, enc, n, rgb, s, act);
     return train_fp32_launch<true, false, kActStore>(d, w, enc, nullptr, nullptr, n, 0.0f, 1.0f, nullptr, nullptr,
                                                      nullptr, nullptr, s, act, rgb);
 }

@@ -669,9 +669,9 @@ bool train_in_tiles(int precision, const Geo& d, int64_t n, bool upstream) {
 
 // Workgroups, each with one partial.  Two fit a CU at width 64 up to depth 5, but
 // up to three tiles per CU one is better: the second partial per CU costs the
-// reduction more than the overlap saves (us per FP16 step, one / two per CU:
-// 20,000 records 23.0 / 25.3, 32,768 23.6 / 25.7, 49,152 28.6 / 29.0, 65,536 35.6
-// / 35.2, 262,144 108.8 / 88.8).
+// reduction more than the overlap saves (us per step, one / two per CU: FP16 32,768
+// records 21.1 / 23.3, 49,152 25.8 / 25.2, 65,536 30.9 / 28.8, 98,304 40.9 / 35.6; BF16
+// 32,768 21.9 / 25.1, 49,152 27.1 / 28.1, 65,536 32.4 / 31.7).
 int64_t train_parts(const Geo& d, int64_t n) {
     const int64_t tiles = (n + kTS - 1) / kTS, cus = device_cu_count();
     const bool two = 2 * tiles_lds_bytes(d.W, d.H) <= 160 * 1024 && tiles > 3 * cus;

@@ -99,3 +99,22 @@ def test_device_weights_of_any_stride(N):
         c.set_weights_device(w.cpu())
     c.set_weights_device(w.view(-1, 64).t())
     assert np.array_equal(c.get_weights(), w.cpu().numpy())
+
+
+@pytest.mark.parametrize("n_hidden,past", [(5, 1), (5, 64 * 40 + 17), (6, 33), (1, 64), (2, 64 * 300 - 1)])
+def test_fp32_forward_with_activations_over_many_tiles(N, n_hidden, past):
+    """More tiles than compute units take another kernel: same predictions as in slices, and a
+    buffer that gives the gradients of a recomputed forward pass, equal bit for bit."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 64 * cus + past
+    c = N.Cache(N.make_config(n_hidden=n_hidden, precision="fp32", factorize=n_hidden == 5))
+    c.set_weights(sd.glorot_weights(64, n_hidden, seed=4))
+    enc = torch.from_numpy(sd.uniform_features(n, 64, 21)).cuda()
+    up = torch.rand(n, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(2)) - 0.5
+    act = torch.full((N.nrc_act_ws_bytes(c.cfg, n),), 0xff, dtype=torch.uint8, device="cuda")   # NaN where nothing is written
+    rgb, act = N.nrc_forward_train(c, enc, act=act)
+    assert torch.equal(rgb, N.nrc_forward(c, enc))
+    for lo in range(0, n, 64 * cus):
+        assert torch.equal(N.nrc_forward_train(c, enc[lo:lo + 64 * cus].clone())[0], rgb[lo:lo + 64 * cus])
+    for got, ref in zip(N.nrc_backward(c, enc, up, act=act), N.nrc_backward(c, enc, up)):
+        assert torch.equal(got, ref)
