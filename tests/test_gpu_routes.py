@@ -118,3 +118,17 @@ def test_fp32_forward_with_activations_over_many_tiles(N, n_hidden, past):
         assert torch.equal(N.nrc_forward_train(c, enc[lo:lo + 64 * cus].clone())[0], rgb[lo:lo + 64 * cus])
     for got, ref in zip(N.nrc_backward(c, enc, up, act=act), N.nrc_backward(c, enc, up)):
         assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16", "fp32"])
+@pytest.mark.parametrize("preset,layout", [(0, 0), (1, 1), (2, 0), (3, 1), (0, 1), (3, 0)])
+def test_a_row_is_encoded_alike_in_any_batch(N, prec, preset, layout):
+    """Rows of ragged batches equal the same vertices' rows in one large batch bit for bit, and
+    nothing is written past a batch's last row."""
+    c = N.Cache(N.make_config(precision=prec, enc_preset=preset))
+    raw = torch.from_numpy(sd.raw_records(64 * 700 + 5, 31, layout)).cuda()
+    whole = N.nrc_encode(c, raw, layout)
+    for lo, n in ((0, 1), (64, 63), (128, 64), (1000, 65), (63, 321), (64 * 650, 64 * 50 + 5)):
+        out = torch.full((n + 2, 64), 7.0, dtype=c.enc_dtype, device="cuda")
+        N.nrc_encode(c, raw[lo:lo + n].clone(), layout, enc=out[:n])
+        assert torch.equal(out[:n], whole[lo:lo + n]) and bool((out[n:] == 7.0).all())
