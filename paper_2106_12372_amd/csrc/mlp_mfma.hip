@@ -467,18 +467,20 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restric
                 #pragma unroll
                 for (int p = 0; p < KC; ++p) b[col][p] = nb[col][p];
             if constexpr (ACT) {
-                typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+                // A lane holds features 4g .. +3 and 16 + 4g .. +3 of a chunk; lane groups
+                // 2k and 2k + 1 trade halves, so that each writes 8 in a row, 8k .. +7 and
+                // 16 + 8k .. +7: one 16-byte store instead of two of 8 (65,536 FP16 records
+                // 27.4 -> 21.2 us, 92 MB written or read).
                 #pragma unroll
                 for (int col = 0; col < COLS; ++col) {
                     const int64_t row = base + 16 * col + ln;
-                    if (row < cnt) {
-                        T* dst = act + (row * n_hidden + l) * W + 4 * g;
-                        #pragma unroll
-                        for (int p = 0; p < KC; ++p) {
-                            const u32x4 u = __builtin_bit_cast(u32x4, b[col][p]);
-                            *reinterpret_cast<u32x2*>(dst + 32 * p) = u32x2{u[0], u[1]};
-                            *reinterpret_cast<u32x2*>(dst + 32 * p + 16) = u32x2{u[2], u[3]};
-                        }
+                    T* dst = act + (row * n_hidden + l) * W + 8 * (g >> 1) + 16 * (g & 1);
+                    #pragma unroll
+                    for (int p = 0; p < KC; ++p) {
+                        const u32x4 u = __builtin_bit_cast(u32x4, b[col][p]);
+                        const auto x = __builtin_amdgcn_permlane16_swap(u[0], u[2], false, false);
+                        const auto y = __builtin_amdgcn_permlane16_swap(u[1], u[3], false, false);
+                        if (row < cnt) *reinterpret_cast<u32x4*>(dst + 32 * p) = u32x4{x[0], y[0], x[1], y[1]};
                     }
                 }
             }
