@@ -173,9 +173,10 @@ __device__ inline void encode_shared(const float (&x)[RW], T* h0, int g, bool va
 // of each of four lane groups: first (half 0) the frequency encodings, position
 // coordinate g per group, then (half 1) the one-blob of angle g and a quarter of
 // the rest.  Both halves of a record run at once, in different waves, and neither
-// diverges far.  valid = false: zeros.  The same arithmetic as encode_part.
+// diverges far.  valid = false: zeros.  The same arithmetic as encode_part.  Feature
+// k goes to k ^ key (a multiple of 4).
 template <typename T, int PRESET, int LAYOUT>
-__device__ inline void encode_half(const float* __restrict__ rr, T* h0, int half, int g, bool valid) {
+__device__ inline void encode_half(const float* __restrict__ rr, T* h0, int key, int half, int g, bool valid) {
     constexpr bool paper = PRESET != NRC_PRESET_CONFIG, gauss = PRESET == NRC_PRESET_PAPER_GAUSS;
     if (half == 0) {
         if (g < 3) {
@@ -184,7 +185,7 @@ __device__ inline void encode_half(const float* __restrict__ rr, T* h0, int half
             #pragma unroll
             for (int k = 0; k < 12; ++k) f[k] = valid ? f[k] : 0.0f;
             #pragma unroll
-            for (int q = 0; q < 3; ++q) store4<T>(h0 + 12 * g + 4 * q, f + 4 * q);
+            for (int q = 0; q < 3; ++q) store4<T>(h0 + ((12 * g + 4 * q) ^ key), f + 4 * q);
         }
         return;
     }
@@ -204,7 +205,7 @@ __device__ inline void encode_half(const float* __restrict__ rr, T* h0, int half
     if (gauss) one_blob4_gauss(s, e); else one_blob4(s, e);
     #pragma unroll
     for (int k = 0; k < 4; ++k) e[k] = valid ? e[k] : 0.0f;
-    store4<T>(h0 + 36 + 4 * g, e);
+    store4<T>(h0 + ((36 + 4 * g) ^ key), e);
     if (g == 3) return;
     if (paper) {
         const float one = valid ? 1.0f : 0.0f;
@@ -224,7 +225,7 @@ __device__ inline void encode_half(const float* __restrict__ rr, T* h0, int half
         e[2] = g == 0 ? v[2] : g == 1 ? v[6] : 0.0f;
         e[3] = g == 0 ? v[3] : 0.0f;
     }
-    store4<T>(h0 + 52 + 4 * g, e);
+    store4<T>(h0 + ((52 + 4 * g) ^ key), e);
 }
 
 }  // namespace

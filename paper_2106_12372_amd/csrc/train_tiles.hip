@@ -26,8 +26,8 @@
 // (a backward layer reads 88 KB from LDS, 0.7k cycles at 128 bytes each).
 // The partials' one write takes 27k cycles at width 128 (76 MB over the chip, at
 // the rate of a copy).  Whole training steps, us, k_train_mfma before and now:
-// width 64 FP16 16,384 records 17.5 / 16.1, 65,536 48 / 29, 262,144 183 / 73, BF16
-// 1,000 records 18.6 / 14.1, 262,144 232 / 82; width 128 FP16 1,000 records 53 / 28,
+// width 64 FP16 16,384 records 17.5 / 16.0, 65,536 48 / 29, 262,144 183 / 72, BF16
+// 1,000 records 18.6 / 13.9, 262,144 232 / 82; width 128 FP16 1,000 records 53 / 28,
 // 16,384 97 / 41, 65,536 306 / 73, BF16 65,536 438 / 100.  At width 128 a wave with two row blocks and two columns
 // instead of one and four was slower (83 and 134 us: its fragments spill).
 #include "mfma_ops.h"
@@ -38,14 +38,28 @@ namespace {
 
 constexpr int kTS = 64;           // records per tile
 constexpr int kWaves = 8;
-constexpr int kLd0 = 72;          // LDS row strides, elements: h_0
 constexpr int kLdT = 72;          // dL/dy, feature-major
 
-__host__ __device__ constexpr int row_stride(int W) { return W + 8; }
-// LDS bytes: h_0 [64][72], h_1 .. h_H and two deltas [64][W + 8], dL/dy
+// Where a wave has 256 registers at width 64 (ROOMY), the LDS rows of h_0 .. h_H and
+// the deltas are unpadded and element e of row r lies at e ^ row_key: the row's
+// 16-byte chunks change places by bits of r, so that no access below puts two lanes
+// of a pass on one bank.  Those are the 16-byte reads of one chunk of 16 rows (a pass
+// takes 8 lanes of one lane group and the other 8 rows' of the next) and the
+// transpose reads of two chunks of rows 8g .. +3 by two lane groups.  Elsewhere the
+// rows have 8 elements of padding and every access twice its passes: the addresses
+// need more registers and vector instructions than there are to spare.  Steps, us,
+// padded / swapped: FP16 1,000 records 13.2 / 12.8, 16,384 16.0 / 15.9, depth 8 16.8 /
+// 16.2; two workgroups per CU, 262,144 records, 72.5 / 75.5; width 128, 65,536, 73 / 78.
+__host__ __device__ constexpr bool roomy(int W, int wgs) { return W == 64 && wgs == 1; }
+__host__ __device__ constexpr int row_stride(int W, bool swap) { return swap ? W : W + 8; }
+template <bool SWAP>
+__device__ inline int row_key(int r) {
+    return SWAP ? (r & 2) << 4 | (r & 8) << 1 : 0;
+}
+// LDS bytes: h_0 [64][72 or 64], h_1 .. h_H and two deltas [64][W + 8 or W], dL/dy
 // feature-major [3][72] and record-major [64][4], network outputs [64][4] (FP32).
-__host__ __device__ constexpr int tiles_lds_bytes(int W, int H) {
-    return (kTS * (kLd0 + (H + 2) * row_stride(W)) + 3 * kLdT + kTS * 4) * 2 + kTS * 16;
+__host__ __device__ constexpr int tiles_lds_bytes(int W, int H, bool swap) {
+    return (kTS * (row_stride(64, swap) + (H + 2) * row_stride(W, swap)) + 3 * kLdT + kTS * 4) * 2 + kTS * 16;
 }
 
 // UPSTREAM, GENC, RAWL, PRESET as in k_train_mfma.  ACT: kActLoad reads the
@@ -71,14 +85,15 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
     using V = typename Vec8<T>::type;
     typedef T t4 __attribute__((ext_vector_type(4)));
     constexpr bool SPLIT = __is_same(T, __bf16);
-    constexpr int MB = W / 16, KC = W / 32, LDR = row_stride(W);
+    constexpr bool ROOMY = roomy(W, WGS);
+    constexpr int MB = W / 16, KC = W / 32, LD0 = row_stride(64, ROOMY), LDR = row_stride(W, ROOMY);
     constexpr int RG = W / 16, NC = W / 32;                  // waves: RG row blocks x (8 / RG) groups of NC columns
     constexpr int NTH = 64 * kWaves;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     __shared__ float wsum[4];
     // every region at a fixed offset, the activations last
     T* h0 = reinterpret_cast<T*>(smem_raw);
-    T* dO = h0 + kTS * kLd0;                                 // dL/dy [3][kLdT]
+    T* dO = h0 + kTS * LD0;                                 // dL/dy [3][kLdT]
     T* dR = dO + 3 * kLdT;                                   // dL/dy [64][4]
     float* fy = reinterpret_cast<float*>(dR + kTS * 4);      // network outputs [64][4]
     T* ds = reinterpret_cast<T*>(fy + kTS * 4);              // delta_l in block l & 1
@@ -118,21 +133,22 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
     // The four values of this wave's row block a lane holds of column col, into a
     // row store.
     auto put = [&](T* rows, int col, f32x4 v, bool relu_it) {
-        T* dst = rows + (16 * col + ln) * LDR + 32 * (rb >> 1) + 8 * g + 4 * (rb & 1);
+        T* dst = rows + (16 * col + ln) * LDR + ((32 * (rb >> 1) + 8 * g + 4 * (rb & 1)) ^ row_key<ROOMY>(ln));
         const V p = pack8<T, V>(v, v);
         const V q = relu_it ? relu_packed(p) : p;
         *reinterpret_cast<t4*>(dst) = __builtin_shufflevector(q, q, 0, 1, 2, 3);
     };
     // B operand chunk c of column col from a row store in slot order.
     auto get = [&](const T* rows, int stride, int col, int c) {
-        return *reinterpret_cast<const V*>(rows + (16 * col + ln) * stride + 32 * c + 8 * g);
+        return *reinterpret_cast<const V*>(rows + (16 * col + ln) * stride + ((32 * c + 8 * g) ^ row_key<ROOMY>(ln)));
     };
     // Operand of records 32 kc + 8 g .. +7 for row positions 16 blk + ln of a
     // record-major store (the transpose read of k_train_mfma).
     auto gather = [&](const T* base, int stride, int blk, int kc) {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-        const T* p = base + (32 * kc + 8 * g + (ln >> 2)) * stride + 16 * blk + 4 * (ln & 3);
+        const int r = 8 * g + (ln >> 2);                     // rows r and r + 4 have one key
+        const T* p = base + (32 * kc + r) * stride + ((16 * blk + 4 * (ln & 3)) ^ row_key<ROOMY>(r));
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * stride));
         return __builtin_bit_cast(V, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -153,13 +169,12 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
             for (int j = 0; j < NW; ++j) accw[l][i][j] = zero;
     }
 
-    // With 256 registers per wave (one workgroup per CU) a layer's LDS reads at width
+    // ROOMY (one workgroup per CU, 256 registers per wave): a layer's LDS reads at width
     // 64 go out together, before its first product: left to the compiler, each
     // product waits for operands read just before it, nine LDS latencies one after
     // another in a backward layer (16,384 records, us per step: FP16 16.6 -> 16.2, BF16
     // 17.7 -> 17.0).  128 registers hold neither these nor the weights below beside
     // the sums (they spill).
-    constexpr bool ROOMY = W == 64 && WGS == 1;
     // FP16: the weights of the whole backward chain are loaded ahead of it, too, as
     // loads behind the stores of a layer's sums wait for those (1,000 records 13.6 ->
     // 13.3 us per step; BF16, with its hi and lo parts, 17.1 -> 17.4 at 16,384).
@@ -242,11 +257,11 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
                 #pragma unroll
                 for (int c = 0; c < 3; ++c) tg[c] = tgt[src * 3 + c];
             }
-            encode_half<T, PRESET, RAWL>(reinterpret_cast<const float*>(enc) + src * RW, h0 + sl * kLd0, wave >> 2, g,
-                                         valid);
+            encode_half<T, PRESET, RAWL>(reinterpret_cast<const float*>(enc) + src * RW, h0 + sl * LD0, row_key<ROOMY>(ln),
+                                    wave >> 2, g, valid);
         } else {
             const int ft = anew(tid);
-            *reinterpret_cast<V*>(h0 + (ft >> 3) * kLd0 + 8 * (ft & 7)) = in_v;
+            *reinterpret_cast<V*>(h0 + (ft >> 3) * LD0 + ((8 * (ft & 7)) ^ row_key<ROOMY>(ft >> 3))) = in_v;
             find(tile + gridDim.x);
         }
         f32x4 y = zero;
@@ -276,9 +291,11 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
                     for (int k = 0; k < NR; ++k)
                         if (lb + u < n_hidden) {
                             const V x = v[u][k];
-                            T* dst = hrow(lb + u + 1) + (rec0 + k * (NTH / CPR)) * LDR + 32 * (q >> 2) + 8 * gq + iq;
-                            *reinterpret_cast<t4*>(dst) = __builtin_shufflevector(x, x, 0, 1, 2, 3);
-                            *reinterpret_cast<t4*>(dst + 8) = __builtin_shufflevector(x, x, 4, 5, 6, 7);
+                            const int r = rec0 + k * (NTH / CPR), at = 32 * (q >> 2) + 8 * gq + iq;
+                            T* dst = hrow(lb + u + 1) + r * LDR;
+                            *reinterpret_cast<t4*>(dst + (at ^ row_key<ROOMY>(r))) = __builtin_shufflevector(x, x, 0, 1, 2, 3);
+                            *reinterpret_cast<t4*>(dst + ((at + 8) ^ row_key<ROOMY>(r))) =
+                                __builtin_shufflevector(x, x, 4, 5, 6, 7);
                         }
             }
             if (out_wave && g == 0 && valid) {
@@ -315,7 +332,7 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
                 for (int col = 0; col < NC; ++col) put(hrow(l + 1), col0 + col, a[col], true);
                 __syncthreads();                             // h_{l+1} is in LDS
             };
-            layer(h0, kLd0, IntC<2>{}, 0);
+            layer(h0, LD0, IntC<2>{}, 0);
             for (int l = 1; l < n_hidden; ++l) layer(hrow(l), LDR, IntC<KC>{}, l);
             if (out_wave) {
                 #pragma unroll
@@ -326,7 +343,7 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
             fetch();                                         // the next tile's rows
             if (out_wave) {
                 float r[3];
-                reflectance_operand(*reinterpret_cast<const V*>(h0 + sl * kLd0 + 32 + 8 * g), fcol, ln, r);
+                reflectance_operand(get(h0, LD0, wave & 3, 1), fcol, ln, r);
                 if (g == 0 && valid) {
                     #pragma unroll
                     for (int c = 0; c < 3; ++c) out[row * 3 + c] = y[c] * r[c];
@@ -340,8 +357,10 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
                 #pragma unroll
                 for (int rec = tid / CPR; rec < kTS; rec += NTH / CPR) {
                     const int64_t ar = tile * kTS + rec;
-                    const T* p = hrow(l + 1) + rec * LDR + 32 * (q >> 2) + 8 * gq + iq;
-                    const t4 a = *reinterpret_cast<const t4*>(p), b = *reinterpret_cast<const t4*>(p + 8);
+                    const T* p = hrow(l + 1) + rec * LDR;
+                    const int at = 32 * (q >> 2) + 8 * gq + iq;
+                    const t4 a = *reinterpret_cast<const t4*>(p + (at ^ row_key<ROOMY>(rec)));
+                    const t4 b = *reinterpret_cast<const t4*>(p + ((at + 8) ^ row_key<ROOMY>(rec)));
                     if (ar < n)
                         *reinterpret_cast<V*>(act + (ar * n_hidden + l) * W + 8 * q) =
                             __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -365,7 +384,7 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
         float lterm = 0.0f;
         if (out_wave) {
             float r[3];
-            reflectance_operand(*reinterpret_cast<const V*>(h0 + sl * kLd0 + 32 + 8 * g), fcol, ln, r);
+            reflectance_operand(get(h0, LD0, wave & 3, 1), fcol, ln, r);
             t4 d = t4{0, 0, 0, 0};
             if (g == 0 && valid) {
                 if (UPSTREAM) {
@@ -400,8 +419,8 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
         // h_l where this wave's delta_l goes, and delta_l masked by ReLU'(z_l) into its
         // row store
         auto h_at = [&](int l, int col) {
-            return *reinterpret_cast<const t4*>(hrow(l) + (16 * (col0 + col) + ln) * LDR + 32 * (rb >> 1) + 8 * g +
-                                                4 * (rb & 1));
+            return *reinterpret_cast<const t4*>(hrow(l) + (16 * (col0 + col) + ln) * LDR +
+                                                ((32 * (rb >> 1) + 8 * g + 4 * (rb & 1)) ^ row_key<ROOMY>(ln)));
         };
         auto put_delta = [&](int l, const f32x4 (&a)[NC], const t4 (&h)[NC]) {
             #pragma unroll
@@ -543,7 +562,7 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
         {
             V bw[2], aw[2][MW];
             auto operands = [&](int kc) {
-                bw[kc] = gather(h0, kLd0, wave & 3, kc);
+                bw[kc] = gather(h0, LD0, wave & 3, kc);
                 #pragma unroll
                 for (int i = 0; i < MW; ++i) aw[kc][i] = gather(drow(1), LDR, mw0 + i, kc);
             };
@@ -590,7 +609,7 @@ hipError_t tiles_launch_as(const Geo& d, const void* ffr, const void* bfr, const
                         const int32_t* idx, int64_t n, float loss_eps, float grad_scale, float* partials,
                         float* loss_part, int32_t* part_bad, float* out, hipStream_t s, void* act, float* act_y,
                         LcgGather lg) {
-    const size_t lds = (size_t)tiles_lds_bytes(W, d.H);
+    const size_t lds = (size_t)tiles_lds_bytes(W, d.H, roomy(W, WGS));
     auto k = k_train_tiles<T, W, MAXH, WGS, UP, GE, ACT, RAWL, PRESET>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3((unsigned)train_parts(d, n)), dim3(64 * kWaves), lds, s, (const T*)ffr, (const T*)bfr,
@@ -659,10 +678,10 @@ hipError_t tiles_raw_dispatch(const Geo& d, int preset, int layout, const void* 
 
 // Everything but the FP16 backward passes of up to one tile per CU at width 64,
 // where k_train_mfma's chain in registers is shorter.  us, k_train_mfma / here,
-// with the reduction: FP16 backward of 300 records 10.0 / 10.9 from the buffer and
-// 10.6 / 11.8 without, of 16,384 18.5 / 18.4 and 19.4 / 20.3; FP16 steps 300
-// records 15.1 / 14.4, 16,384 17.5 / 17.0; BF16 steps 17.9 / 15.8 and 20.9 / 18.7,
-// backward without the buffer 13.7 / 13.3 and 22.0 / 21.2.
+// with the reduction: FP16 backward of 300 records 9.7 / 10.4 from the buffer and
+// 10.3 / 11.1 without, of 16,384 17.8 / 18.5 and 19.1 / 19.9; FP16 steps 300 records
+// 15.1 / 12.6, 16,384 17.5 / 16.0; BF16 steps 17.9 / 13.4 and 20.9 / 17.0, backward
+// without the buffer 13.7 / 12.2 and 22.0 / 20.5.
 bool train_in_tiles(int precision, const Geo& d, int64_t n, bool upstream) {
     return !(precision == NRC_FP16 && d.W == 64 && upstream && (n + kTS - 1) / kTS <= device_cu_count());
 }
@@ -674,7 +693,7 @@ bool train_in_tiles(int precision, const Geo& d, int64_t n, bool upstream) {
 // 32,768 21.9 / 25.1, 49,152 27.1 / 28.1, 65,536 32.4 / 31.7).
 int64_t train_parts(const Geo& d, int64_t n) {
     const int64_t tiles = (n + kTS - 1) / kTS, cus = device_cu_count();
-    const bool two = 2 * tiles_lds_bytes(d.W, d.H) <= 160 * 1024 && tiles > 3 * cus;
+    const bool two = 2 * tiles_lds_bytes(d.W, d.H, false) <= 160 * 1024 && tiles > 3 * cus;
     const int64_t wgs = two ? 2 * cus : cus;
     return tiles < wgs ? tiles : wgs;
 }
