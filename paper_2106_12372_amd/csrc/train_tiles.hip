@@ -42,14 +42,18 @@ constexpr int kLdT = 72;          // dL/dy, feature-major
 
 // Where a wave has 256 registers at width 64 (ROOMY), the LDS rows of h_0 .. h_H and
 // the deltas are unpadded and element e of row r lies at e ^ row_key: the row's
-// 16-byte chunks change places by bits of r, so that no access below puts two lanes
-// of a pass on one bank.  Those are the 16-byte reads of one chunk of 16 rows (a pass
-// takes 8 lanes of one lane group and the other 8 rows' of the next) and the
-// transpose reads of two chunks of rows 8g .. +3 by two lane groups.  Elsewhere the
-// rows have 8 elements of padding and every access twice its passes: the addresses
-// need more registers and vector instructions than there are to spare.  Steps, us,
-// padded / swapped: FP16 1,000 records 13.2 / 12.8, 16,384 16.0 / 15.9, depth 8 16.8 /
-// 16.2; two workgroups per CU, 262,144 records, 72.5 / 75.5; width 128, 65,536, 73 / 78.
+// 16-byte chunks change places by bits of r, so that no 16-byte read of a chunk of 16
+// rows (a pass takes 8 lanes of one lane group and the other 8 rows' of the next) and
+// no transpose read of two chunks of rows 8g .. +3 by two lane groups puts two lanes
+// of a pass on one bank.  With 8 elements of padding, as elsewhere, these take twice
+// their passes (by the conflict counters, 8 and 4 instead of 4 and 2); the fewer
+// 8-byte stores take 16 instead of 8, the 8-byte reads 4 either way.  Swapped rows'
+// addresses need registers and vector instructions that the other instances lack.
+// Steps, us, padded / swapped: FP16 1,000 records 13.2 / 12.8, 16,384 16.0 / 15.9, a raw
+// frame's four 70.5 / 67.8, depth 8 16.8 / 16.3; two workgroups per CU, 262,144 records,
+// 72.5 / 75.5; width 128, 65,536, 73 / 78.  A key that spreads the stores as well (bits
+// 3 ^ 2 and 2 below bit 1) gives rows r and r + 4 of a transpose read addresses of
+// their own: 1,000 records 13.1, 40,001 24.0 instead of 24.7, not kept.
 __host__ __device__ constexpr bool roomy(int W, int wgs) { return W == 64 && wgs == 1; }
 __host__ __device__ constexpr int row_stride(int W, bool swap) { return swap ? W : W + 8; }
 template <bool SWAP>
