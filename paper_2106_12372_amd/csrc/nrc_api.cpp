@@ -120,9 +120,9 @@ ScratchLayout scratch_layout(const nrc_config& c, int64_t n) {
     return L;
 }
 
-// Bytes of the autograd form's activation buffer: per training tile, h_1 .. h_H
-// at the operand precision, then the network output of every record as four
-// floats (see k_train_mfma / k_train_fp32).
+// Bytes of the autograd form's activation buffer: h_1 .. h_H of every record of
+// every training tile at the operand precision, then the network output of each as
+// four floats (layouts: k_train_tiles for FP16/BF16, k_train_fp32).
 size_t act_layout(const nrc_config& c, int64_t n) {
     const int ts = train_tile(c.precision, c.width);
     const size_t tiles = (size_t)((n + ts - 1) / ts);

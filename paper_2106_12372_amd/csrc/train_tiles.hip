@@ -66,7 +66,9 @@ __host__ __device__ constexpr int tiles_lds_bytes(int W, int H, bool swap) {
     return (kTS * (row_stride(64, swap) + (H + 2) * row_stride(W, swap)) + 3 * kLdT + kTS * 4) * 2 + kTS * 16;
 }
 
-// UPSTREAM, GENC, RAWL, PRESET as in k_train_mfma.  ACT: kActLoad reads the
+// UPSTREAM: tgt holds dL/d(prediction) instead of targets.  GENC: dL/d(input) is
+// formed too.  RAWL >= 0: enc points at raw records of that layout, encoded here
+// with PRESET; -1: encoded rows.  ACT: kActLoad reads the
 // forward pass from the activation buffer ([record][layer][feature], and the
 // network outputs [record][4]) instead of computing it; kActStore computes it,
 // writes the buffer and the predictions (to out) and stops there.  out: dL/d(input)
