@@ -203,6 +203,16 @@ def _ptr(t) -> int:
     return 0 if t is None else t.data_ptr()
 
 
+def _dense(t) -> bool:
+    """Whether t's elements fill t.numel() elements of memory from t.data_ptr() on, in any order."""
+    at = 1
+    for stride, size in sorted((st, n) for st, n in zip(t.stride(), t.shape) if n != 1):
+        if stride != at:
+            return False
+        at *= size
+    return True
+
+
 def _need(t, dtype, shape_tail, name):
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
@@ -284,8 +294,14 @@ class Cache:
         check(lib.nrc_set_weights(self.handle, w.ctypes.data_as(POINTER(c_float)), w.size, _stream(stream)))
 
     def set_weights_device(self, w, stream=None):
+        """The cache's weights from an FP32 device tensor of n_params elements, in
+        the order in which they lie in memory (a transposed matrix's storage order,
+        where set_weights takes its rows)."""
         if not (w.is_contiguous() and w.is_cuda and w.dtype == _torch().float32):
             _need(w.reshape(-1, 1), _torch().float32, (1,), "weights")
+            # the reshape copies what has gaps or repeats, the call reads w itself
+            if not _dense(w):
+                raise ValueError("weights must be contiguous")
         check(lib.nrc_set_weights_device(self.handle, _ptr(w), w.numel(), _stream(stream)))
 
     def get_weights(self, stream=None) -> np.ndarray:
