@@ -348,14 +348,28 @@ int nrc_set_weights(nrc_cache* cache, const float* host_w, int64_t n, void* stre
     return upload_state(cache, host_w, nullptr, nullptr, 0, (hipStream_t)stream);
 }
 
+// Whether p is memory of the given device (0.1 us of host time).
+static bool on_device(const void* p, int device) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeDevice && a.device == device;
+    (void)hipGetLastError();
+    return false;
+}
+
 int nrc_set_weights_device(nrc_cache* cache, const float* dev_w, int64_t n, void* stream) {
     if (!cache || !dev_w) return fail(NRC_EINVAL, "NULL argument");
     if (((uintptr_t)dev_w & 3) != 0) return fail(NRC_EINVAL, "misaligned weights");
     const Geo d(cache->cfg.width, cache->cfg.n_hidden);
     if (n != d.n_params()) return fail(NRC_EINVAL, "expected %d weights, got %lld", d.n_params(), (long long)n);
-    const hipError_t e = launch_install(cache->cfg.precision, d, dev_w, cache->w(), cache->m(), cache->v(),
-                                        cache->tslots(), cache->e(), cache->wbar(), cache->ffr(), cache->bfr(),
-                                        cache->effr(), (hipStream_t)stream);
+    hipError_t e = hipSuccess;
+    if (!on_device(dev_w, cache->device)) {
+        // a kernel may not reach another device's memory, a copy does
+        e = hipMemcpyAsync(cache->w(), dev_w, (size_t)n * 4, hipMemcpyDefault, (hipStream_t)stream);
+        dev_w = cache->w();
+    }
+    if (e == hipSuccess)
+        e = launch_install(cache->cfg.precision, d, dev_w, cache->w(), cache->m(), cache->v(), cache->tslots(),
+                           cache->e(), cache->wbar(), cache->ffr(), cache->bfr(), cache->effr(), (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "device weight upload");
     cache->parity = 0;
     return ok();

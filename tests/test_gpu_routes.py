@@ -132,3 +132,45 @@ def test_a_row_is_encoded_alike_in_any_batch(N, prec, preset, layout):
         out = torch.full((n + 2, 64), 7.0, dtype=c.enc_dtype, device="cuda")
         N.nrc_encode(c, raw[lo:lo + n].clone(), layout, enc=out[:n])
         assert torch.equal(out[:n], whole[lo:lo + n]) and bool((out[n:] == 7.0).all())
+
+
+def _installed(N, cfg, src, upload):
+    c = N.Cache(cfg)
+    upload(c, src)
+    torch.cuda.synchronize()
+    return c.ws.clone()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
+def test_device_weights_that_a_kernel_may_not_reach(N, prec):
+    """Weights in pinned host memory, or on another device, are copied to the cache first:
+    every byte of its workspace is what the cache's own device's weights give."""
+    cfg = N.make_config(n_hidden=3, precision=prec, ema_alpha=0.9)
+    w = torch.from_numpy(sd.glorot_weights(64, 3, seed=5))
+    want = _installed(N, cfg, w.cuda(), lambda c, t: c.set_weights_device(t))
+    call = lambda c, t: N.check(N.lib.nrc_set_weights_device(c.handle, t.data_ptr(), t.numel(), N._stream(None)))
+    assert torch.equal(_installed(N, cfg, w.pin_memory(), call), want)
+    if torch.cuda.device_count() > 1:
+        other = w.to("cuda:1")
+        torch.cuda.synchronize(1)
+        assert torch.equal(_installed(N, cfg, other, lambda c, t: c.set_weights_device(t)), want)
+
+
+def test_device_weights_set_inside_a_graph(N):
+    """The upload can be captured; every replay installs what the tensor holds then."""
+    c, ref = (N.Cache(N.make_config(precision="fp16", ema_alpha=0.9)) for _ in range(2))
+    w = torch.zeros(c.n_params, device="cuda")
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        c.set_weights_device(w)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=side):
+            c.set_weights_device(w)
+    for seed in range(3):
+        host = sd.glorot_weights(64, 5, seed=seed)
+        w.copy_(torch.from_numpy(host))
+        ref.set_weights(host)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(c.ws, ref.ws)
