@@ -13,8 +13,8 @@
 // held.  While the waves form delta_l they also form dW_l = delta_{l+1} h_l^T over
 // the tile's 64 records, the record index along K by LDS transpose reads, into
 // accumulators that stay in registers from tile to tile.  Each workgroup writes
-// its sums once, in the accumulator layout the reduction expects, so the partials
-// do not grow with the batch.
+// its sums once, in the accumulator layout the reduction expects: one partial per
+// up to kHeld tiles.
 //
 // Every record's forward pass, loss and deltas go through the same products in
 // the same order as in k_train_mfma; only the grouping of the records' weight
@@ -39,6 +39,19 @@ namespace {
 constexpr int kTS = 64;           // records per tile
 constexpr int kWaves = 8;
 constexpr int kLdT = 72;          // dL/dy, feature-major
+
+// The most tiles of a workgroup; larger batches take several launches, one after the
+// other, each with partials of its own.  A tile adds to its workgroup's sums in plain
+// FP32, the reduction adds the partials with compensation.  Held without end the sums'
+// error grows with the batch: small terms after large ones vanish, and in a model of
+// the additions (non-negative terms, 256 workgroups, mean relative error) 512 tiles
+// each give 2.8e-8 and 4,096 6.5e-8.  With 8 it is 2.0e-8 for any number, as with one
+// partial per tile: that of rounding the result.  Steps at depth 5, us, one launch /
+// as here (more partials, 4 us from launch to launch): FP16 width 64 262,208 records
+// 73.9 / 81.6, 524,288 132 / 141, 1,048,576 252 / 279; width 128 262,144 208 / 232.
+// Starting the sums anew inside the kernel took 75.2, 139, 272 and 223, but spills more
+// registers at width 128 (BF16 65,536 records 93.9 / 96.4).
+constexpr int kHeld = 8;
 
 // Where a wave has 256 registers at width 64 (ROOMY), the LDS rows of h_0 .. h_H and
 // the deltas are unpadded and element e of row r lies at e ^ row_key: the row's
@@ -610,18 +623,45 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
     if (tid == 0 && part_bad) part_bad[blockIdx.x] = any_bad ? 1 : 0;
 }
 
+// Workgroups of a launch.  Two fit a CU at width 64 up to depth 5, but up to three
+// tiles per CU one is better: the second partial per CU costs the reduction more than
+// the overlap saves (us per step, one / two per CU: FP16 32,768 records 21.1 / 23.3,
+// 49,152 25.8 / 25.2, 65,536 30.9 / 28.8, 98,304 40.9 / 35.6; BF16 32,768 21.9 / 25.1,
+// 49,152 27.1 / 28.1, 65,536 32.4 / 31.7).
+int64_t train_wgs(const Geo& d, int64_t n) {
+    const int64_t tiles = (n + kTS - 1) / kTS, cus = device_cu_count();
+    const bool two = 2 * tiles_lds_bytes(d.W, d.H, false) <= 160 * 1024 && tiles > 3 * cus;
+    const int64_t wgs = two ? 2 * cus : cus;
+    return tiles < wgs ? tiles : wgs;
+}
+
 template <typename T, int W, int MAXH, int WGS, bool UP, bool GE, int ACT, int RAWL, int PRESET>
-hipError_t tiles_launch_as(const Geo& d, const void* ffr, const void* bfr, const void* enc, const float* tgt,
-                        const int32_t* idx, int64_t n, float loss_eps, float grad_scale, float* partials,
-                        float* loss_part, int32_t* part_bad, float* out, hipStream_t s, void* act, float* act_y,
-                        LcgGather lg) {
+hipError_t tiles_launch_as(const Geo& d, int64_t wgs, const void* ffr, const void* bfr, const void* enc,
+                           const float* tgt, const int32_t* idx, int64_t n, float loss_eps, float grad_scale,
+                           float* partials, float* loss_part, int32_t* part_bad, float* out, hipStream_t s, void* act,
+                           float* act_y, LcgGather lg) {
     const size_t lds = (size_t)tiles_lds_bytes(W, d.H, roomy(W, WGS));
     auto k = k_train_tiles<T, W, MAXH, WGS, UP, GE, ACT, RAWL, PRESET>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3((unsigned)train_parts(d, n)), dim3(64 * kWaves), lds, s, (const T*)ffr, (const T*)bfr,
-                       (const T*)enc, tgt, idx, n, d.H, loss_eps, grad_scale, partials, loss_part, part_bad, out,
-                       d.F, (T*)act, act_y, lg);
-    return hipGetLastError();
+    // the forward-only form keeps no sums: one launch
+    const int64_t span = ACT == kActStore ? n : wgs * kHeld * kTS;
+    const bool gathered = idx || lg.mask;
+    for (int64_t at = 0, part = 0; at < n; at += span, part += wgs) {
+        const int64_t cnt = n - at < span ? n - at : span, tiles = (cnt + kTS - 1) / kTS;
+        const int64_t row = gathered ? 0 : at;               // the launch's first record
+        const LcgGather l{lg.step, apply(power(lg.step, (uint64_t)at), lg.x0) & lg.mask, lg.mask};
+        const void* e = RAWL >= 0 ? (const void*)((const float*)enc + row * (RAWL == NRC_RAW14 ? 14 : 16))
+                                  : (const void*)((const T*)enc + row * kEncWidth);
+        hipLaunchKernelGGL(k, dim3((unsigned)(tiles < wgs ? tiles : wgs)), dim3(64 * kWaves), lds, s, (const T*)ffr,
+                           (const T*)bfr, (const T*)e, tgt ? tgt + row * 3 : nullptr, idx ? idx + at : nullptr, cnt, d.H,
+                           loss_eps, grad_scale, partials ? partials + part * d.n_params() : nullptr,
+                           loss_part ? loss_part + at / kTS : nullptr, part_bad ? part_bad + part : nullptr,
+                           out ? out + at * (GE ? kEncWidth : kNOut) : nullptr, d.F,
+                           act ? (T*)act + at * d.H * d.W : nullptr, act_y ? act_y + at * 4 : nullptr, l);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
 }
 
 template <typename T, int W, int MAXH, bool UP, bool GE, int ACT, int RAWL, int PRESET>
@@ -629,12 +669,13 @@ hipError_t tiles_launch(const Geo& d, const void* ffr, const void* bfr, const vo
                         const int32_t* idx, int64_t n, float loss_eps, float grad_scale, float* partials,
                         float* loss_part, int32_t* part_bad, float* out, hipStream_t s, void* act, float* act_y,
                         LcgGather lg) {
+    const int64_t wgs = train_wgs(d, n);
     if constexpr (W == 64 && MAXH <= 5)
-        if (train_parts(d, n) > device_cu_count())
-            return tiles_launch_as<T, W, MAXH, 2, UP, GE, ACT, RAWL, PRESET>(d, ffr, bfr, enc, tgt, idx, n, loss_eps,
+        if (wgs > device_cu_count())
+            return tiles_launch_as<T, W, MAXH, 2, UP, GE, ACT, RAWL, PRESET>(d, wgs, ffr, bfr, enc, tgt, idx, n, loss_eps,
                                                                              grad_scale, partials, loss_part,
                                                                              part_bad, out, s, act, act_y, lg);
-    return tiles_launch_as<T, W, MAXH, 1, UP, GE, ACT, RAWL, PRESET>(d, ffr, bfr, enc, tgt, idx, n, loss_eps,
+    return tiles_launch_as<T, W, MAXH, 1, UP, GE, ACT, RAWL, PRESET>(d, wgs, ffr, bfr, enc, tgt, idx, n, loss_eps,
                                                                      grad_scale, partials, loss_part, part_bad, out,
                                                                      s, act, act_y, lg);
 }
@@ -692,16 +733,11 @@ bool train_in_tiles(int precision, const Geo& d, int64_t n, bool upstream) {
     return !(precision == NRC_FP16 && d.W == 64 && upstream && (n + kTS - 1) / kTS <= device_cu_count());
 }
 
-// Workgroups, each with one partial.  Two fit a CU at width 64 up to depth 5, but
-// up to three tiles per CU one is better: the second partial per CU costs the
-// reduction more than the overlap saves (us per step, one / two per CU: FP16 32,768
-// records 21.1 / 23.3, 49,152 25.8 / 25.2, 65,536 30.9 / 28.8, 98,304 40.9 / 35.6; BF16
-// 32,768 21.9 / 25.1, 49,152 27.1 / 28.1, 65,536 32.4 / 31.7).
+// Partials of a step or backward pass: one for each workgroup of its launches.
 int64_t train_parts(const Geo& d, int64_t n) {
-    const int64_t tiles = (n + kTS - 1) / kTS, cus = device_cu_count();
-    const bool two = 2 * tiles_lds_bytes(d.W, d.H, false) <= 160 * 1024 && tiles > 3 * cus;
-    const int64_t wgs = two ? 2 * cus : cus;
-    return tiles < wgs ? tiles : wgs;
+    const int64_t tiles = (n + kTS - 1) / kTS, wgs = train_wgs(d, n);
+    const int64_t full = (tiles - 1) / (wgs * kHeld), left = tiles - full * wgs * kHeld;
+    return full * wgs + (left < wgs ? left : wgs);
 }
 
 hipError_t launch_train_tiles(int precision, const Geo& d, const void* ffr, const void* bfr, const void* enc,

@@ -121,3 +121,77 @@ def test_the_loss_of_any_number_of_tiles(N, n):
     parts = sum(loss(lo, min(lo + 4096, n)) for lo in range(0, n, 4096))
     # a tile's 64 terms are added in FP32 with compensation; scaling and its inverse round twice
     assert abs(loss(0, n) - parts) <= 8 * 2.0 ** -24 * parts
+
+
+# ---------------------------------------------------------------------------
+# Many tiles per workgroup
+# ---------------------------------------------------------------------------
+TILES = 129                                     # per workgroup, more than its sums are held for
+
+
+@pytest.mark.parametrize("prec,width,wgs_per_cu", [("fp16", 64, 2), ("bf16", 64, 2), ("fp16", 128, 1), ("bf16", 128, 1)])
+@pytest.mark.parametrize("n_hidden", [1, 3])
+def test_small_gradients_after_large_ones_are_not_lost(N, prec, width, wgs_per_cu, n_hidden):
+    """A weight gradient's terms, positive and equal but for a factor: the records of every
+    workgroup's first tile weigh 2^24 times the others'.  A tile's term of 1 is half a unit in
+    the last place of the 2^24 before it and vanishes in an FP32 sum that holds both.  A sum
+    over at most 8 tiles loses at most 7 * 2^-24 of the gradient, one over all of them
+    128 * 2^-24.  Every operand is a power of two, so products and exact sums are known;
+    16 * 2^-24 leaves room for the sums' own roundings (two per tile)."""
+    cus = _cus()
+    wgs = cus * wgs_per_cu
+    n = 64 * wgs * TILES
+    c = N.Cache(N.make_config(width=width, n_hidden=n_hidden, precision=prec, loss_scale=1.0))
+    w = np.concatenate([np.full(64 * width, 2.0 ** -6)] + [np.full(width * width, 1.0 / width)] * (n_hidden - 1) +
+                       [np.full(3 * width, 0.25)]).astype(np.float32)
+    c.set_weights(w)                            # every activation and prediction weight as below
+    enc = torch.ones((n, 64), dtype=c.enc_dtype, device="cuda")
+    up = torch.zeros((n, 3), device="cuda")
+    up[:, 0] = 2.0 ** -12
+    up[: 64 * wgs, 0] = 2.0 ** 12               # tile b is workgroup b's first
+    grad, _ = N.nrc_backward(c, enc, up, want_grad_enc=False)
+    total = 64 * wgs * (2.0 ** 12 + (TILES - 1) * 2.0 ** -12)
+    want = np.full(w.shape, 0.25 * total)       # h_l = 1 and delta_l = dL/dy / 4 in every layer
+    want[-3 * width:] = 0.0
+    want[-3 * width:-2 * width] = total         # dL/dy is zero in two channels
+    got = grad.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - want) <= 16 * 2.0 ** -24 * want)
+
+
+# tiles per compute unit, records past the last whole tile: two launches, the second
+# with one whole tile and a ragged one, or as many as the first less a record
+@pytest.mark.parametrize("prec,width,n_hidden,per_cu,rest", [("fp16", 64, 2, 16, 69), ("bf16", 64, 5, 16, 69),
+                                                             ("fp16", 64, 6, 8, 69), ("bf16", 64, 8, 8, 69),
+                                                             ("fp16", 128, 5, 8, 69), ("bf16", 128, 3, 16, -1)])
+def test_gradients_over_several_launches(N, prec, width, n_hidden, per_cu, rest):
+    test_gradients_of_a_large_batch_and_of_its_slices(N, prec, width, n_hidden, per_cu, rest)
+
+
+@pytest.mark.parametrize("prec,n_hidden,layout", [("fp16", 2, 0), ("bf16", 5, 1), ("fp16", 8, 1)])
+@pytest.mark.parametrize("n", [64 * 8 * 512 + 64 + 5, 1 << 20])   # an index list; the orbit in the kernel
+def test_steps_over_several_launches(N, prec, n_hidden, layout, n):
+    """Raw, encoded and indexed steps as above, and a step on the rows as they lie equal to
+    one through the list 0, 1, 2, ...; the loss is that of the same records in slices."""
+    test_raw_encoded_and_indexed_steps_agree(N, prec, n_hidden, 1, layout, n - 64 * _cus())
+    cfg = N.make_config(n_hidden=n_hidden, precision=prec, enc_preset=1)
+    w = sd.glorot_weights(64, n_hidden, seed=6)
+    raw = sd.raw_records(n, 78, layout)
+    res = []
+    for form in ("rows", "list"):
+        c = N.Cache(cfg)
+        c.set_weights(w)
+        enc, y = N.nrc_encode(c, torch.from_numpy(raw).cuda(), layout), torch.from_numpy(sd.targets(raw)).cuda()
+        if form == "rows":
+            loss, skipped = N.nrc_train_step(c, enc, y)
+        else:
+            loss, skipped = N.nrc_train_step_indexed(c, enc, y, torch.arange(n, dtype=torch.int32, device="cuda"))
+        assert int(skipped.item()) == 0
+        res.append((loss.clone(), c.ws.clone()))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    bad = y.clone()
+    bad[n - 1, 2] = float("inf")                # in the last launch
+    assert int(N.nrc_train_step(c, enc, bad)[1].item()) == 1
+
+
+def test_the_loss_over_several_launches(N):
+    test_the_loss_of_any_number_of_tiles(N, 64 * 8 * 512 + 64 * 70 + 1)
