@@ -195,3 +195,45 @@ def test_steps_over_several_launches(N, prec, n_hidden, layout, n):
 
 def test_the_loss_over_several_launches(N):
     test_the_loss_of_any_number_of_tiles(N, 64 * 8 * 512 + 64 * 70 + 1)
+
+
+# ---------------------------------------------------------------------------
+# Two workgroups per compute unit (width 64, up to depth 5, more than three tiles each)
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("prec,n_hidden", [("fp16", 5), ("bf16", 5), ("bf16", 2), ("fp16", 1)])
+@pytest.mark.parametrize("preset,layout", [(p, la) for p in range(4) for la in range(2)])
+def test_steps_of_two_workgroups_per_cu_agree(N, prec, n_hidden, preset, layout):
+    test_raw_encoded_and_indexed_steps_agree(N, prec, n_hidden, preset, layout, 64 * (2 * _cus() + 5) + 9)
+
+
+@pytest.mark.parametrize("prec,n_hidden", [("fp16", 5), ("bf16", 5), ("fp16", 1), ("bf16", 3)])
+def test_the_weights_of_a_step_with_two_workgroups_per_cu(N, prec, n_hidden):
+    """The first moment after one step is 0.1 times the gradient.  The gradient of four tiles
+    per compute unit is the mean over its quarters, one tile and one workgroup per compute
+    unit each: with the loss scale in proportion to the records their deltas are the same
+    numbers.  Weights and inputs are non-negative and the targets zero, so every product is
+    non-negative and the bound is that of the gradients above."""
+    q = 64 * _cus()
+    enc_np = sd.uniform_features(4 * q, 64, 17)
+    w = np.abs(sd.glorot_weights(64, n_hidden, seed=2)) / np.float32(8.0)
+
+    def step(lo, hi):
+        c = N.Cache(N.make_config(n_hidden=n_hidden, precision=prec, loss_scale=2.0 ** 16 * (hi - lo) / q))
+        c.set_weights(w)
+        enc = torch.from_numpy(enc_np[lo:hi]).cuda().to(c.enc_dtype)
+        loss, skipped = N.nrc_train_step(c, enc, torch.zeros((hi - lo, 3), device="cuda"))
+        assert int(skipped.item()) == 0
+        _, m, v, t = c.get_state()
+        assert t == 1
+        return loss.item(), m.astype(np.float64), c
+
+    loss, m, c = step(0, 4 * q)
+    parts = [step(i * q, (i + 1) * q) for i in range(4)]
+    want = sum(p[1] for p in parts) / 4
+    bound = 2 * (64 * (4 + 1) + 2 * _cus()) * 2.0 ** -24
+    assert np.all(want >= 0) and np.count_nonzero(want) > want.size // 2
+    assert np.all(np.abs(m - want) <= bound * want)
+    assert abs(loss - sum(p[0] for p in parts) / 4) <= 8 * 2.0 ** -24 * loss
+    # Adam's first step from there: w - lr * sign(g) but for eps, in every weight
+    moved = w.astype(np.float64) - c.get_weights()
+    assert np.any(want > 1e-6) and np.allclose(moved[want > 1e-6], 1e-2, rtol=1e-2)
