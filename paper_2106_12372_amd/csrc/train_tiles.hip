@@ -623,14 +623,16 @@ __global__ __launch_bounds__(64 * kWaves, 2 * WGS) void k_train_tiles(const T* _
     if (tid == 0 && part_bad) part_bad[blockIdx.x] = any_bad ? 1 : 0;
 }
 
-// Workgroups of a launch.  Two fit a CU at width 64 up to depth 5, but up to three
+// Workgroups of a launch.  Two fit a CU at width 64 up to depth 5 (at width 128 a wave
+// takes 256 registers and one fills the CU; with two, a step of 65,536 FP16 records took
+// 25.4 instead of 21.9 us at depth 1, 41.4 instead of 33.0 at depth 2), but up to three
 // tiles per CU one is better: the second partial per CU costs the reduction more than
 // the overlap saves (us per step, one / two per CU: FP16 32,768 records 21.1 / 23.3,
 // 49,152 25.8 / 25.2, 65,536 30.9 / 28.8, 98,304 40.9 / 35.6; BF16 32,768 21.9 / 25.1,
 // 49,152 27.1 / 28.1, 65,536 32.4 / 31.7).
 int64_t train_wgs(const Geo& d, int64_t n) {
     const int64_t tiles = (n + kTS - 1) / kTS, cus = device_cu_count();
-    const bool two = 2 * tiles_lds_bytes(d.W, d.H, false) <= 160 * 1024 && tiles > 3 * cus;
+    const bool two = d.W == 64 && d.H <= 5 && tiles > 3 * cus;
     const int64_t wgs = two ? 2 * cus : cus;
     return tiles < wgs ? tiles : wgs;
 }

@@ -237,3 +237,21 @@ def test_the_weights_of_a_step_with_two_workgroups_per_cu(N, prec, n_hidden):
     # Adam's first step from there: w - lr * sign(g) but for eps, in every weight
     moved = w.astype(np.float64) - c.get_weights()
     assert np.any(want > 1e-6) and np.allclose(moved[want > 1e-6], 1e-2, rtol=1e-2)
+
+
+@pytest.mark.parametrize("prec,width,n_hidden,per_cu", [("fp16", 128, 1, 1), ("bf16", 128, 2, 1), ("fp16", 128, 5, 1),
+                                                        ("bf16", 64, 6, 1), ("fp16", 64, 5, 2), ("bf16", 64, 1, 2)])
+def test_workgroups_beyond_those_a_cu_holds_are_not_launched(N, prec, width, n_hidden, per_cu):
+    """A wave of the width-128 trainer takes 256 registers: one workgroup fills a compute
+    unit whatever its LDS.  Each workgroup writes one partial of n_params floats, from the
+    start of the scratch on."""
+    cus = _cus()
+    n = 64 * 4 * cus
+    c = N.Cache(N.make_config(width=width, n_hidden=n_hidden, precision=prec))
+    c.set_weights(sd.glorot_weights(width, n_hidden, seed=2))
+    enc = torch.from_numpy(sd.uniform_features(n, 64, 11)).cuda().to(c.enc_dtype)
+    sc = N._aligned_bytes(N.nrc_train_scratch_bytes(c.cfg, n), "cuda").fill_(0xff)   # NaN where nothing is written
+    N.nrc_train_step(c, enc, torch.rand((n, 3), device="cuda"), scratch=sc)
+    slots = sc[:4 * c.n_params * 4 * cus].view(torch.float32).view(4 * cus, c.n_params)
+    written = ~slots.isnan().all(dim=1)
+    assert int(written.sum()) == per_cu * cus and bool(written[:per_cu * cus].all())
