@@ -161,11 +161,12 @@ __device__ inline void mlp_query_mfma(const f4* __restrict__ sw, int H, int lane
     }
 }
 
-// Inference from many raw records, encoded in the lane (Sec. 3.6).  A wave
-// takes 64 consecutive queries per tile; lanes past the end compute on the last
-// query and store nothing, so every lane joins every matrix instruction.
-template <int PRESET, int LAYOUT>
-__device__ inline void query_tiles(const float* __restrict__ w, const float* __restrict__ raw, int64_t n,
+// Inference from many records: encoded rows (RAW = false), or raw records, encoded
+// in the lane (Sec. 3.6).  A wave takes 64 consecutive queries per tile; lanes past
+// the end compute on the last query and store nothing, so every lane joins every
+// matrix instruction.
+template <bool RAW, int PRESET, int LAYOUT>
+__device__ inline void query_tiles(const float* __restrict__ w, const float* __restrict__ in, int64_t n,
                                    float* __restrict__ rgb, int H, int fcol) {
     extern __shared__ f4 sw[];
     __shared__ int claimed;                 // tiles of the workgroup's share handed out so far
@@ -191,14 +192,23 @@ __device__ inline void query_tiles(const float* __restrict__ w, const float* __r
         const bool valid = s < n;
         if (!valid) s = n - 1;
         float h[kW];
-        float x[RW];
-        const float2* src = reinterpret_cast<const float2*>(raw + s * RW);
-        #pragma unroll
-        for (int q = 0; q < RW / 2; ++q) {
-            const float2 v = src[q];
-            x[2 * q] = v.x; x[2 * q + 1] = v.y;
+        if constexpr (RAW) {
+            float x[RW];
+            const float2* src = reinterpret_cast<const float2*>(in + s * RW);
+            #pragma unroll
+            for (int q = 0; q < RW / 2; ++q) {
+                const float2 v = src[q];
+                x[2 * q] = v.x; x[2 * q + 1] = v.y;
+            }
+            encode_record<PRESET, LAYOUT>(x, h);
+        } else {
+            const float4* row = reinterpret_cast<const float4*>(in + s * kEncWidth);
+            #pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const float4 v = row[q];
+                h[4 * q] = v.x; h[4 * q + 1] = v.y; h[4 * q + 2] = v.z; h[4 * q + 3] = v.w;
+            }
         }
-        encode_record<PRESET, LAYOUT>(x, h);
         float r[kNOut], y[kNOut];
         reflectance_row(h, fcol, r);
         mlp_query_mfma(sw, H, lane, wo, h, y);
@@ -210,7 +220,13 @@ template <int PRESET, int LAYOUT>
 __global__ __launch_bounds__(64 * kQWaves) void k_fwd_raw_fp32(const float* __restrict__ w,
                                                               const float* __restrict__ raw, int64_t n,
                                                               float* __restrict__ rgb, int n_hidden, int fcol) {
-    query_tiles<PRESET, LAYOUT>(w, raw, n, rgb, n_hidden, fcol);
+    query_tiles<true, PRESET, LAYOUT>(w, raw, n, rgb, n_hidden, fcol);
+}
+
+__global__ __launch_bounds__(64 * kQWaves) void k_fwd_fp32_tiles(const float* __restrict__ w,
+                                                                const float* __restrict__ enc, int64_t n,
+                                                                float* __restrict__ rgb, int n_hidden, int fcol) {
+    query_tiles<false, NRC_PRESET_CONFIG, NRC_RAW14>(w, enc, n, rgb, n_hidden, fcol);
 }
 
 // The lane's record x (its four lane groups hold the same one) encoded into the
@@ -252,9 +268,9 @@ __device__ inline void wave_lds_sync() {
 }
 
 // Inference in units of 16 queries (one operand column) per wave: encoded rows
-// (RAW = false), or few raw records, encoded by the four lane groups together.
-// A unit keeps its wave for a quarter of a 64-query tile's 18 us, so the units
-// fill the SIMDs of a small batch and the last round of a large one.  A
+// (RAW = false), or raw records, encoded by the four lane groups together.  A unit
+// keeps its wave for a quarter of a 64-query tile's 18 us, so the units fill the SIMDs
+// of a small batch and the last round of a large one (encoded_in_units, raw_in_units).  A
 // column's products per layer and accumulator are those of mlp_query_mfma in
 // the same order, and the output layer's sums too, so the outputs are equal bit
 // for bit.  Bound by the FP32 matrix cores: each A fragment read from LDS
@@ -948,18 +964,48 @@ hipError_t query_launch(K kernel, const Geo& d, size_t lds, const float* w, cons
     return hipGetLastError();
 }
 
-// Raw records: units of 16 queries up to 24 64-query tiles per CU (393,216
-// queries), tiles of 64 above.  A tile keeps its wave for 18 us, so with few
-// tiles per wave the last round is long; a unit takes a quarter of that, but
-// the divergent shared encoding costs 170 vector instructions per 16 queries
-// instead of 270 per 64.  Measured (5 layers, us, units / tiles): 1,000 queries
-// 9.9 / 23.6, 20,011 14.8 / 23.8, 70,000 30.5 / 42.5, 300,000 105.5 / 119.1,
-// 400,000 136 / 139, 500,000 163 / 158, 2,073,600 655 / 618.
-constexpr int kUnitTilesPerCu = 24;
+// Units of 16 queries or tiles of 64?  A tile keeps its wave for 18 us at depth 5, and
+// the fullest CU's r tiles take (r + 3) / 4 rounds, the last one as long with one tile
+// as with four; units take a quarter of that, but cost more per query: each weight is
+// read for 16 queries instead of 64, and raw records are encoded by divergent lanes.
+inline int64_t fullest_cu(int64_t n) {
+    const int64_t cus = device_cu_count();
+    return ((n + 63) / 64 + cus - 1) / cus;
+}
+
+// Encoded rows: units, but for batches that fill the tiles' last round and take a
+// multiple of three of them, and at depth 6 from the fourth round on.  us, units / tiles:
+// depth 5, 12 tiles per CU 69.2 / 64.9, 24 127.8 / 122.1, 16 88.7 / 98.7, 13 70.3 / 82.7;
+// depth 2, 12 32.2 / 30.8, 16 40.8 / 45.8; depth 6, 12 81.3 / 76.4, 16 104.8 / 100.3, 20
+// 128.0 / 122.7, 13 81.9 / 98.3.
+inline bool encoded_in_units(int H, int64_t n) {
+    const int64_t r = fullest_cu(n);
+    return r % 12 != 0 && !(H == 6 && r > 12 && r % 4 == 0);
+}
+
+// Raw records: units where r of them cost less than the rounds, the encoding counted as
+// a part of a layer (Gaussian one-blobs as a larger one); none past 24 tiles per CU.
+// But for Gaussian one-blobs the first round counts a little more.  With the lightest
+// encodings (angles given, 6 octaves or triangle waves) 18 tiles and more take six
+// rounds: the waves have drifted apart, and tiles left over meet on one SIMD.  us, units /
+// tiles, config preset: depth 1, 2 tiles per CU 7.4 / 7.7, 8 15.2 / 12.3, 16 27.8 / 21.5;
+// depth 2, 6 18.3 / 19.9, 8 24.3 / 20.0; depth 5, 1 10.3 / 23.6, 6 35.9 / 42.6, 8 50.0 /
+// 42.9, 9 50.9 / 61.6, 12 71.3 / 62.0, 18 99.6 / 118.9, 24 127.9 / 119.9.  Gaussian
+// one-blobs on unit vectors: depth 5, 6 41.4 / 44.5, 7 47.2 / 44.6, 18 113.1 / 104.3; depth
+// 2, 2 10.4 / 13.2, 4 17.1 / 14.9.
+template <int PRESET, int LAYOUT>
+inline bool raw_in_units(int H, int64_t n) {
+    constexpr bool gauss = PRESET == NRC_PRESET_PAPER_GAUSS;
+    constexpr bool light = LAYOUT == NRC_RAW14 && (PRESET == NRC_PRESET_CONFIG || PRESET == NRC_PRESET_PAPER_TRI);
+    const int64_t r = fullest_cu(n);
+    if (r > 24) return false;
+    const double rounds = !gauss && r <= 4 ? 1.25 : light && r >= 18 ? 6 : (r + 3) / 4;
+    return r * (H + (gauss ? 0.7 : 0.5)) <= 3.85 * rounds * H;
+}
 
 template <int PRESET, int LAYOUT>
 hipError_t launch_raw_query(const Geo& d, const float* w, const float* raw, int64_t n, float* rgb, hipStream_t s) {
-    if ((n + 63) / 64 <= (int64_t)kUnitTilesPerCu * device_cu_count())
+    if (raw_in_units<PRESET, LAYOUT>(d.H, n))
         return query_launch(k_fwd_raw_fp32_units<PRESET, LAYOUT>, d,
                             query_lds_bytes(d) + (size_t)kQWaves * 16 * kLd * sizeof(float), w, raw, n, rgb, s);
     return query_launch(k_fwd_raw_fp32<PRESET, LAYOUT>, d, query_lds_bytes(d), w, raw, n, rgb, s);
@@ -969,7 +1015,8 @@ hipError_t launch_raw_query(const Geo& d, const float* w, const float* raw, int6
 
 hipError_t launch_fwd_fp32(const Geo& d, const float* w, const float* enc, int64_t n, float* rgb,
                            hipStream_t s) {
-    return query_launch(k_fwd_fp32, d, query_lds_bytes(d), w, enc, n, rgb, s);
+    return query_launch(encoded_in_units(d.H, n) ? k_fwd_fp32 : k_fwd_fp32_tiles, d, query_lds_bytes(d), w, enc, n, rgb,
+                        s);
 }
 
 hipError_t launch_fwd_raw_fp32(const Geo& d, int preset, int layout, const float* w, const float* raw,

@@ -174,3 +174,28 @@ def test_device_weights_set_inside_a_graph(N):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(c.ws, ref.ws)
+
+
+# tiles of the fullest compute unit and hidden layers: FP32 queries on either side of the
+# lines between 16-query units and 64-query tiles (a last round full, or nearly so)
+@pytest.mark.parametrize("n_hidden,r", [(1, 2), (1, 3), (2, 6), (2, 8), (5, 7), (5, 8), (5, 9), (5, 12), (5, 13),
+                                        (3, 17), (3, 18), (6, 16), (6, 21), (4, 24), (4, 25)])
+@pytest.mark.parametrize("raw_form", [False, True])
+@pytest.mark.parametrize("rest", [0, -37])
+def test_fp32_batches_of_units_and_of_tiles_agree(N, n_hidden, r, raw_form, rest):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    test_batches_and_their_slices_agree(N, "fp32", 64, n_hidden, raw_form, 64 * r * cus + rest - 24 * 64 * cus)
+
+
+@pytest.mark.parametrize("preset,layout", [(0, 1), (1, 0), (2, 1), (3, 0), (3, 1)])
+@pytest.mark.parametrize("r", [3, 8, 18])
+def test_fp32_raw_batches_of_units_and_of_tiles_agree(N, preset, layout, r):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 64 * r * cus - 5
+    c = N.Cache(N.make_config(n_hidden=3, precision="fp32", enc_preset=preset, factorize=True))
+    c.set_weights(sd.glorot_weights(64, 3, seed=3))
+    raw = torch.from_numpy(sd.raw_records(n, 41, layout)).cuda()
+    whole = N.nrc_forward_raw(c, raw, layout)
+    assert torch.equal(N.nrc_forward(c, N.nrc_encode(c, raw, layout)), whole)
+    for lo in (0, 64 * cus * (r - 1)):
+        assert torch.equal(N.nrc_forward_raw(c, raw[lo:lo + 64 * cus].clone(), layout), whole[lo:lo + 64 * cus])
