@@ -178,7 +178,8 @@ def enc_dtype(cfg: nrc_config):
 def _stream(stream) -> int:
     if stream is None:
         torch = _torch()
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # not in torch's public interface
+        return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

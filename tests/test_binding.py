@@ -53,3 +53,18 @@ def test_device_weights_with_gaps_or_repeats_are_refused(upload, view):
     assert w.numel() == 323 * 64
     with pytest.raises(ValueError, match="contiguous"):
         upload(w)
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_the_current_stream_without_torchs_private_call(monkeypatch, private):
+    class Stream:
+        cuda_stream = 0x1230
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream)
+    if private:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x4560 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert N._stream(None) == (0x4563 if private else 0x1230)
+    assert N._stream(Stream) == 0x1230 and N._stream(7) == 7
