@@ -20,8 +20,6 @@ namespace {
 constexpr int kEncRows = 64, kEncBlock = 5 * 64;   // vertices and threads per workgroup
 constexpr int64_t kEncMax = 1 << 29;               // vertices per launch (a grid has fewer than 2^32 threads)
 
-template <int N> struct At { static constexpr int value = N; };
-
 template <typename T> __device__ inline T to_t(float x);
 template <> __device__ inline float to_t<float>(float x) { return x; }
 template <> __device__ inline _Float16 to_t<_Float16>(float x) { return (_Float16)x; }
@@ -60,19 +58,19 @@ __global__ __launch_bounds__(kEncBlock) void k_encode(const float* __restrict__ 
         };
         if (part == 0) {
             encode_part<PRESET, LAYOUT, 0>(x, f);
-            put(At<0>{}, At<12>{});
+            put(IntC<0>{}, IntC<12>{});
         } else if (part == 1) {
             encode_part<PRESET, LAYOUT, 1>(x, f);
-            put(At<12>{}, At<24>{});
+            put(IntC<12>{}, IntC<24>{});
         } else if (part == 2) {
             encode_part<PRESET, LAYOUT, 2>(x, f);
-            put(At<24>{}, At<36>{});
+            put(IntC<24>{}, IntC<36>{});
         } else if (part == 3) {
             encode_part<PRESET, LAYOUT, 3>(x, f);
-            put(At<36>{}, At<44>{});
+            put(IntC<36>{}, IntC<44>{});
         } else {
             encode_part<PRESET, LAYOUT, 4>(x, f);
-            put(At<44>{}, At<64>{});
+            put(IntC<44>{}, IntC<64>{});
         }
     }
     __syncthreads();

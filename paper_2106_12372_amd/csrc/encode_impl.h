@@ -174,4 +174,62 @@ __device__ inline void encode_record(const float* x, float* o) {
     encode_part<PRESET, LAYOUT, 4>(x, o);
 }
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Features f[0 .. 3], rounded to T (FP16 and BF16: to nearest even), into an LDS row
+// (aligned to their size).
+template <typename T>
+__device__ inline void store4(T* dst, const float* f) {
+    if constexpr (__is_same(T, float)) {
+        *reinterpret_cast<float4*>(dst) = make_float4(f[0], f[1], f[2], f[3]);
+    } else if constexpr (__is_same(T, _Float16)) {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<h4*>(dst) = __builtin_convertvector(f4{f[0], f[1], f[2], f[3]}, h4);
+    } else {
+        uint2 r;
+        r.x = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{f[0], f[1]}, bf16x2));
+        r.y = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{f[2], f[3]}, bf16x2));
+        *reinterpret_cast<uint2*>(dst) = r;
+    }
+}
+
+// The lane's record x (its four lane groups hold the same one) encoded into the
+// LDS row h0, a share of the features per group: groups 0..2 the frequency
+// encoding of position coordinate g (the same code for the three, features
+// 12g .. 12g + 11), group 3 the rest (36 .. 63).  valid = false: a row of zeros.
+template <typename T, int PRESET, int LAYOUT, int RW>
+__device__ inline void encode_shared(const float (&x)[RW], T* h0, int g, bool valid) {
+    float f[64];
+    if (g < 3) {
+        float xc[RW];
+        xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
+        encode_part<PRESET, LAYOUT, 0>(xc, f);
+        if (!valid) {
+            #pragma unroll
+            for (int k = 0; k < 12; ++k) f[k] = 0.0f;
+        }
+        #pragma unroll
+        for (int q = 0; q < 3; ++q) store4<T>(h0 + 12 * g + 4 * q, f + 4 * q);
+    } else {
+        encode_part<PRESET, LAYOUT, 3>(x, f);
+        encode_part<PRESET, LAYOUT, 4>(x, f);
+        if (!valid) {
+            #pragma unroll
+            for (int k = 36; k < 64; ++k) f[k] = 0.0f;
+        }
+        #pragma unroll
+        for (int q = 9; q < 16; ++q) store4<T>(h0 + 4 * q, f + 4 * q);
+    }
+}
+
+// Orders a wave's LDS accesses: those before complete before those after,
+// across the wave's lanes.
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace nrc

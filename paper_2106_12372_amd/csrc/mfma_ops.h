@@ -1,6 +1,6 @@
 // Device-side pieces shared by the FP16/BF16 matrix-core kernels: operand types,
 // the matrix instruction, packing of accumulators into the next operand, and the
-// encoding of a record into an LDS row.
+// encoding of a record into an LDS row by eight lanes.
 #pragma once
 
 #include "encode_impl.h"
@@ -37,9 +37,6 @@ template <typename T> __device__ inline T mul_to(float x, float r) {
     }
 }
 
-// A compile-time integer as an argument.
-template <int N> struct IntC { static constexpr int value = N; };
-
 template <typename V> __device__ inline V zero8() {
     V v;
     #pragma unroll
@@ -50,8 +47,6 @@ template <typename V> __device__ inline V zero8() {
 // Two accumulator blocks (features 4g..4g+3 and 16+4g..16+4g+3 of a chunk)
 // -> one B operand in chained order.
 typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <typename T, typename V> __device__ inline V pack8(f32x4 lo, f32x4 hi) {
     if constexpr (sizeof(T) == 2 && !__is_same(T, _Float16)) {
@@ -81,13 +76,6 @@ template <typename V> __device__ inline V relu_packed(V v) {
     return __builtin_bit_cast(V, i);
 }
 
-__device__ inline f32x4 relu4(f32x4 a) {
-    f32x4 r;
-    #pragma unroll
-    for (int j = 0; j < 4; ++j) r[j] = fmaxf(a[j], 0.0f);
-    return r;
-}
-
 // Reflectance factor alpha + beta (Sec. 5) of record ln from the B operand
 // holding input features 32..63 in natural order (lane 16g + ln: features
 // 32 + 8g .. 32 + 8g + 7); valid in lanes 0..15, 1 when fcol == 0.  Config
@@ -115,59 +103,6 @@ __device__ inline void store8(T* dst, const float* f, int q) {
     const f32x4 hi = f32x4{f[8 * q + 4], f[8 * q + 5], f[8 * q + 6], f[8 * q + 7]};
     *reinterpret_cast<V*>(dst + 8 * q) = pack8<T, V>(lo, hi);
 }
-
-// Features f[0 .. 3], rounded to T, into an LDS row (8-byte aligned); the same
-// rounding as store8.
-template <typename T>
-__device__ inline void store4(T* dst, const float* f) {
-    if constexpr (sizeof(T) == 2 && !__is_same(T, _Float16)) {
-        uint2 r;
-        r.x = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{f[0], f[1]}, bf16x2));
-        r.y = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{f[2], f[3]}, bf16x2));
-        *reinterpret_cast<uint2*>(dst) = r;
-    } else {
-        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-        *reinterpret_cast<h4*>(dst) = __builtin_convertvector(f32x4{f[0], f[1], f[2], f[3]}, h4);
-    }
-}
-
-// Orders a wave's LDS accesses: those before complete before those after,
-// across the wave's lanes.
-__device__ inline void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The lane's record x (its four lane groups hold the same one) encoded into the
-// LDS row h0, a share of the features per group: groups 0..2 the frequency
-// encoding of position coordinate g (the same code for the three, features
-// 12g .. 12g + 11), group 3 the rest (36 .. 63).  valid = false: a row of zeros.
-template <typename T, int PRESET, int LAYOUT, int RW>
-__device__ inline void encode_shared(const float (&x)[RW], T* h0, int g, bool valid) {
-    float f[64];
-    if (g < 3) {
-        float xc[RW];
-        xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
-        encode_part<PRESET, LAYOUT, 0>(xc, f);
-        if (!valid) {
-            #pragma unroll
-            for (int k = 0; k < 12; ++k) f[k] = 0.0f;
-        }
-        #pragma unroll
-        for (int q = 0; q < 3; ++q) store4<T>(h0 + 12 * g + 4 * q, f + 4 * q);
-    } else {
-        encode_part<PRESET, LAYOUT, 3>(x, f);
-        encode_part<PRESET, LAYOUT, 4>(x, f);
-        if (!valid) {
-            #pragma unroll
-            for (int k = 36; k < 64; ++k) f[k] = 0.0f;
-        }
-        #pragma unroll
-        for (int q = 9; q < 16; ++q) store4<T>(h0 + 4 * q, f + 4 * q);
-    }
-}
-
 
 // A record at rr (14 or 16 floats) encoded into the LDS row h0 by eight lanes, two
 // of each of four lane groups: first (half 0) the frequency encodings, position

@@ -229,44 +229,6 @@ __global__ __launch_bounds__(64 * kQWaves) void k_fwd_fp32_tiles(const float* __
     query_tiles<false, NRC_PRESET_CONFIG, NRC_RAW14>(w, enc, n, rgb, n_hidden, fcol);
 }
 
-// The lane's record x (its four lane groups hold the same one) encoded into the
-// LDS row h0, a share of the features per group: groups 0..2 the frequency
-// encoding of position coordinate g (the same code for the three, features
-// 12g .. 12g + 11), group 3 the rest (36 .. 63).  valid = false: a row of zeros.
-template <int PRESET, int LAYOUT, int RW>
-__device__ inline void encode_shared(const float (&x)[RW], float* h0, int g, bool valid) {
-    float f[64];
-    if (g < 3) {
-        float xc[RW];
-        xc[0] = g == 0 ? x[0] : g == 1 ? x[1] : x[2];
-        encode_part<PRESET, LAYOUT, 0>(xc, f);
-        if (!valid) {
-            #pragma unroll
-            for (int k = 0; k < 12; ++k) f[k] = 0.0f;
-        }
-        #pragma unroll
-        for (int q = 0; q < 3; ++q)
-            *reinterpret_cast<float4*>(h0 + 12 * g + 4 * q) =
-                make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
-    } else {
-        encode_part<PRESET, LAYOUT, 3>(x, f);
-        encode_part<PRESET, LAYOUT, 4>(x, f);
-        if (!valid) {
-            #pragma unroll
-            for (int k = 36; k < 64; ++k) f[k] = 0.0f;
-        }
-        #pragma unroll
-        for (int q = 9; q < 16; ++q)
-            *reinterpret_cast<float4*>(h0 + 4 * q) = make_float4(f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3]);
-    }
-}
-
-__device__ inline void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Inference in units of 16 queries (one operand column) per wave: encoded rows
 // (RAW = false), or raw records, encoded by the four lane groups together.  A unit
 // keeps its wave for a quarter of a 64-query tile's 18 us, so the units fill the SIMDs
@@ -328,7 +290,7 @@ __device__ inline void query_units(const float* __restrict__ w, const float* __r
     f4 wo[4];
     load_out_weights(w, H, lane, wo);
     if constexpr (RAW) {
-        if (unit < u_end) encode_shared<PRESET, LAYOUT>(x, h0, g, true);
+        if (unit < u_end) encode_shared<float, PRESET, LAYOUT>(x, h0, g, true);
     }
     #pragma unroll
     for (int u = 0; u < NL; ++u)
@@ -413,7 +375,7 @@ __device__ inline void query_units(const float* __restrict__ w, const float* __r
                 *reinterpret_cast<f4*>(act + (n_units * 16 * H) * kW + s * 4) = f4{y[0], y[1], y[2], 0.0f};
         }
         if constexpr (RAW) {
-            if (more) encode_shared<PRESET, LAYOUT>(x, h0, g, true);
+            if (more) encode_shared<float, PRESET, LAYOUT>(x, h0, g, true);
         }
     }
 }
@@ -547,7 +509,7 @@ __global__ __launch_bounds__(64 * (kChainWaves + kGradWaves)) void k_train_fp32(
             #pragma unroll
             for (int k = 0; k < RW; ++k) x[k] = 0.0f;
         }
-        encode_shared<PRESET, RAWL>(x, h0, g, valid);
+        encode_shared<float, PRESET, RAWL>(x, h0, g, valid);
         wave_lds_sync();
         #pragma unroll
         for (int b = 0; b < 4; ++b) {

@@ -65,44 +65,32 @@ __device__ inline void stage_frags(V* dst, const V* src, int n_frags) {
 // first K chunk starts from a zero accumulator (an inline constant operand)
 // and ReLU is applied to the packed 16-bit result.  NH > 0 fixes the number
 // of hidden layers at compile time (the loop unrolls); NH = 0 reads n_hidden.
-template <typename T, int W, int COLS, int NH = 0>
-__device__ inline void mlp_tile(const typename Vec8<T>::type* sfr, typename Vec8<T>::type (&b)[COLS][W / 32],
+template <typename T, int COLS>
+__device__ inline void mlp_tile(const typename Vec8<T>::type* sfr, typename Vec8<T>::type (&b)[COLS][2],
                                 int n_hidden, int lane, f32x4 (&o)[COLS]) {
     using V = typename Vec8<T>::type;
-    constexpr int MB = W / 16, KC = W / 32;
-    if (NH > 0) n_hidden = NH;
+    constexpr int W = 64, MB = 4, KC = 2;
     const Geo geo(W, n_hidden);
-    auto layer = [&](int l) {
-        const int kc = l == 0 ? 2 : KC;    // the input layer has K = 64
+    for (int l = 0; l < n_hidden; ++l) {
         const V* fl = sfr + geo.fwd_base(l) * 64 + lane;
         f32x4 acc[COLS][MB];
         #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            const V a = fl[(mb * kc) * 64];
+            const V a = fl[(mb * KC) * 64];
             #pragma unroll
             for (int col = 0; col < COLS; ++col) acc[col][mb] = mfma(a, b[col][0], f32x4{0.f, 0.f, 0.f, 0.f});
         }
         #pragma unroll
-        for (int c = 1; c < KC; ++c) {
-            if (c >= kc) break;
+        for (int mb = 0; mb < MB; ++mb) {
+            const V a = fl[(mb * KC + 1) * 64];
             #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const V a = fl[(mb * kc + c) * 64];
-                #pragma unroll
-                for (int col = 0; col < COLS; ++col) acc[col][mb] = mfma(a, b[col][c], acc[col][mb]);
-            }
+            for (int col = 0; col < COLS; ++col) acc[col][mb] = mfma(a, b[col][1], acc[col][mb]);
         }
         #pragma unroll
         for (int col = 0; col < COLS; ++col)
             #pragma unroll
             for (int c = 0; c < KC; ++c)
                 b[col][c] = relu_packed(pack8<T, V>(acc[col][2 * c], acc[col][2 * c + 1]));
-    };
-    if constexpr (NH > 0) {
-        #pragma unroll
-        for (int l = 0; l < NH; ++l) layer(l);
-    } else {
-        for (int l = 0; l < n_hidden; ++l) layer(l);
     }
     const V* fo = sfr + geo.fwd_base(n_hidden) * 64 + lane;
     #pragma unroll
@@ -174,12 +162,12 @@ __device__ inline void store_rgb(const f32x4 (&o)[COLS], const float (&r)[COLS][
 // Inference from encoded rows.  A persistent workgroup stages the forward
 // weight fragments in LDS once; each wave streams tiles of 16*COLS records and
 // loads the next tile's rows while the current one computes.
-template <typename T, int W, int COLS>
+template <typename T, int COLS>
 __global__ __launch_bounds__(256, 2) void k_fwd_mfma(const T* __restrict__ ffr, int n_frags,
                                                      const T* __restrict__ enc, int64_t n,
                                                      float* __restrict__ rgb, int n_hidden, int fcol) {
     using V = typename Vec8<T>::type;
-    constexpr int KC = W / 32;
+    constexpr int KC = 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     V* sfr = reinterpret_cast<V*>(smem_raw);
     stage_frags(sfr, reinterpret_cast<const V*>(ffr), n_frags);
@@ -217,7 +205,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma(const T* __restrict__ ffr, 
         #pragma unroll
         for (int col = 0; col < COLS; ++col) reflectance_operand(b[col][1], fcol, ln, r[col]);
         f32x4 o[COLS];
-        mlp_tile<T, W, COLS>(sfr, b, n_hidden, lane, o);
+        mlp_tile<T, COLS>(sfr, b, n_hidden, lane, o);
         store_rgb<COLS>(o, r, tile * 16 * COLS, n, g, ln, rgb);
     }
 }
@@ -329,11 +317,11 @@ __global__ __launch_bounds__(64 * NW) void k_fwd_mfma_fixed(const T* __restrict_
 // queries of one cache that no training step separates).  Tile t of the
 // launch belongs to the segment whose cumulative tile range holds it; within
 // a segment the kernel is k_fwd_mfma.
-template <typename T, int W, int COLS>
+template <typename T, int COLS>
 __global__ __launch_bounds__(256, 2) void k_fwd_mfma_segs(const T* __restrict__ ffr, int n_frags, SegList segs,
                                                           int n_hidden, int fcol) {
     using V = typename Vec8<T>::type;
-    constexpr int KC = W / 32;
+    constexpr int KC = 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     V* sfr = reinterpret_cast<V*>(smem_raw);
     stage_frags(sfr, reinterpret_cast<const V*>(ffr), n_frags);
@@ -379,7 +367,7 @@ __global__ __launch_bounds__(256, 2) void k_fwd_mfma_segs(const T* __restrict__ 
         #pragma unroll
         for (int col = 0; col < COLS; ++col) reflectance_operand(b[col][1], fcol, ln, r[col]);
         f32x4 o[COLS];
-        mlp_tile<T, W, COLS>(sfr, b, n_hidden, lane, o);
+        mlp_tile<T, COLS>(sfr, b, n_hidden, lane, o);
         int sg;
         int64_t base;
         locate(tile, sg, base);
@@ -513,12 +501,12 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_fwd_wide(const T* __restric
 // writes its 64 features to the wave's own LDS rows, and the wave reads them
 // back as B operands.  HBM traffic per query: the raw record in, RGB out.
 // NW waves per workgroup share one copy of the weights in LDS.
-template <typename T, int W, int PRESET, int LAYOUT, int NW>
+template <typename T, int PRESET, int LAYOUT, int NW>
 __global__ __launch_bounds__(64 * NW) void k_fwd_raw_mfma(const T* __restrict__ ffr, int n_frags,
                                                          const float* __restrict__ raw, int64_t n,
                                                          float* __restrict__ rgb, int n_hidden, int fcol) {
     using V = typename Vec8<T>::type;
-    constexpr int COLS = 4, KC = W / 32;
+    constexpr int COLS = 4, KC = 2;
     constexpr int RW = LAYOUT == NRC_RAW14 ? 14 : 16;
     constexpr int ROW = 72;                     // LDS row stride of an encoded record, elements
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -582,7 +570,7 @@ __global__ __launch_bounds__(64 * NW) void k_fwd_raw_mfma(const T* __restrict__ 
         #pragma unroll
         for (int col = 0; col < COLS; ++col) reflectance_operand(b[col][1], fcol, ln, r[col]);
         f32x4 o[COLS];
-        mlp_tile<T, W, COLS>(sfr, b, n_hidden, lane, o);
+        mlp_tile<T, COLS>(sfr, b, n_hidden, lane, o);
         store_rgb<COLS>(o, r, tile * 64, n, g, ln, rgb);
     }
 }
@@ -820,7 +808,7 @@ __global__ __launch_bounds__(256) void k_fwd_small(const T* __restrict__ ffr, in
         float r[1][3];
         reflectance_operand(b[0][1], fcol, ln, r[0]);
         f32x4 o[1];
-        mlp_tile<T, W, 1>(sfr, b, n_hidden, lane, o);
+        mlp_tile<T, 1>(sfr, b, n_hidden, lane, o);
         const void* e;
         int64_t base, cnt;
         float* out;
@@ -905,17 +893,13 @@ __global__ __launch_bounds__(512) void k_train_mfma(const T* __restrict__ ffr,
     // BF16 form also its lo part, one fragment set further on (the pair carries
     // the weight to ~16 significant bits; both operands are BF16).
     constexpr bool SPLIT = __is_same(T, __bf16);
-    const int lo_f = geo.n_fwd_frags() * 64, lo_b = geo.n_bwd_frags() * 64;
+    const int lo_f = geo.n_fwd_frags() * 64;
     auto wf = [&](const V* f, int i, const V& bop, f32x4 c) {
         c = mfma(f[i], bop, c);
         if (SPLIT) c = mfma(f[i + lo_f], bop, c);
         return c;
     };
-    auto wb = [&](const V* f, int i, const V& bop, f32x4 c) {
-        c = mfma(f[i], bop, c);
-        if (SPLIT) c = mfma(f[i + lo_b], bop, c);
-        return c;
-    };
+    auto wb = [&](const V* f, int i, const V& bop, f32x4 c) { return mfma(f[i], bop, c); };   // FP16 only
 
     // A chained-order operand (features 32c + 4g .. +3 and 32c + 16 + 4g .. +3
     // of record sl) into a record-major store: two 8-byte writes.
@@ -1242,11 +1226,9 @@ hipError_t fwd_small_launch(const Geo& d, const void* ffr, const Src& src, int64
 }
 
 template <typename T, typename Src>
-hipError_t fwd_fixed_launch(const void* ffr, const Src& src, int64_t tiles, int fcol, hipStream_t s) {
+hipError_t fwd_fixed_launch(const void* ffr, const Src& src, int fcol, hipStream_t s) {
     constexpr int NW = kEncWaves;
-    // a workgroup per tile up to one per CU: the tiles spread over the chip
-    const int64_t blocks = tiles < device_cu_count() ? tiles : device_cu_count();
-    hipLaunchKernelGGL((k_fwd_mfma_fixed<T, NW, Src>), dim3((unsigned)blocks), dim3(64 * NW), 0, s,
+    hipLaunchKernelGGL((k_fwd_mfma_fixed<T, NW, Src>), dim3((unsigned)device_cu_count()), dim3(64 * NW), 0, s,
                        (const T*)ffr, src, fcol);
     return hipGetLastError();
 }
@@ -1286,12 +1268,12 @@ hipError_t fwd_segs_dispatch(const Geo& d, const void* ffr, const SegList& segs,
     if (tiles == 0) return hipSuccess;
     if constexpr (W == 128) return fwd_wide<T>(d, ffr, EncSegs{segs}, tiles, s);
     if (small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncSegs{segs}, tiles, s);
-    if (d.H == 5) return fwd_fixed_launch<T>(ffr, EncSegs{segs}, tiles, d.F, s);
+    if (d.H == 5) return fwd_fixed_launch<T>(ffr, EncSegs{segs}, d.F, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 64 * 16;
     int64_t blocks = (tiles + 3) / 4;
     const int64_t resident = resident_fwd_blocks(lds);
     if (blocks > resident) blocks = resident;
-    auto k = k_fwd_mfma_segs<T, 64, COLS>;
+    auto k = k_fwd_mfma_segs<T, COLS>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), lds, s, (const T*)ffr, d.n_fwd_frags(), segs, d.H,
                        d.F);
@@ -1307,12 +1289,12 @@ hipError_t fwd_dispatch(const Geo& d, const void* ffr, const void* enc, int64_t 
     if (tiles == 0) return hipSuccess;
     if constexpr (W == 128) return fwd_wide<T>(d, ffr, EncBatch{enc, n, rgb}, tiles, s);
     if (small_batch(tiles)) return fwd_small_launch<T, -1, NRC_PRESET_CONFIG>(d, ffr, EncBatch{enc, n, rgb}, tiles, s);
-    if (d.H == 5) return fwd_fixed_launch<T>(ffr, EncBatch{enc, n, rgb}, tiles, d.F, s);
+    if (d.H == 5) return fwd_fixed_launch<T>(ffr, EncBatch{enc, n, rgb}, d.F, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 64 * 16;
     int64_t blocks = (tiles + 3) / 4;
     const int64_t resident = resident_fwd_blocks(lds);
     if (blocks > resident) blocks = resident;
-    auto k = k_fwd_mfma<T, 64, COLS>;
+    auto k = k_fwd_mfma<T, COLS>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), lds, s, (const T*)ffr, d.n_fwd_frags(),
                        (const T*)enc, n, rgb, d.H, d.F);
@@ -1327,17 +1309,16 @@ hipError_t fwd_dispatch(const Geo& d, const void* ffr, const void* enc, int64_t 
 // and the 1080p pass took ~78 us instead of ~45.)
 constexpr int kRawWaves = 12;
 
-template <typename T, int W, int PRESET, int LAYOUT, int NW = kRawWaves>
+template <typename T, int PRESET, int LAYOUT, int NW>
 hipError_t fwd_raw_launch(const Geo& d, const void* ffr, const float* raw, int64_t n, float* rgb,
-                          hipStream_t s, int max_blocks) {
+                          hipStream_t s) {
     const int64_t tiles = (n + 63) / 64;
     if (tiles == 0) return hipSuccess;
     if (small_batch(tiles)) return fwd_small_launch<T, LAYOUT, PRESET>(d, ffr, EncBatch{raw, n, rgb}, tiles, s);
     const size_t lds = (size_t)d.n_fwd_frags() * 1024 + (size_t)NW * 64 * 72 * sizeof(T);
-    const int64_t blocks = tiles < max_blocks ? tiles : max_blocks;
-    auto k = k_fwd_raw_mfma<T, W, PRESET, LAYOUT, NW>;
+    auto k = k_fwd_raw_mfma<T, PRESET, LAYOUT, NW>;
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * NW), lds, s, (const T*)ffr, d.n_fwd_frags(), raw,
+    hipLaunchKernelGGL(k, dim3((unsigned)device_cu_count()), dim3(64 * NW), lds, s, (const T*)ffr, d.n_fwd_frags(), raw,
                        n, rgb, d.H, d.F);
     return hipGetLastError();
 }
@@ -1346,34 +1327,29 @@ hipError_t fwd_raw_launch(const Geo& d, const void* ffr, const float* raw, int64
 template <typename T, int PRESET, int LAYOUT>
 hipError_t fwd_raw_fixed_launch(const Geo& d, const void* ffr, const float* raw, int64_t n, float* rgb,
                                 hipStream_t s) {
-    const int max_blocks = device_cu_count();
     constexpr int NW = kRawWaves;
     const int64_t tiles = (n + 63) / 64;
     if (tiles == 0) return hipSuccess;
     if (small_batch(tiles)) return fwd_small_launch<T, LAYOUT, PRESET>(d, ffr, EncBatch{raw, n, rgb}, tiles, s);
-    const int64_t blocks = tiles < max_blocks ? tiles : max_blocks;   // spread over the CUs
-    hipLaunchKernelGGL((k_fwd_raw_mfma_fixed<T, PRESET, LAYOUT, 5, NW>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((k_fwd_raw_mfma_fixed<T, PRESET, LAYOUT, 5, NW>), dim3((unsigned)device_cu_count()),
                        dim3(64 * NW), 0, s, (const T*)ffr, raw, n, rgb, d.F);
     return hipGetLastError();
 }
 
-// Runtime-depth fused kernel: 12 waves per workgroup when the weights and 12
+// Runtime-depth fused kernel, one workgroup per CU: 12 waves when the weights and 12
 // encode buffers fit in the 160 KB of LDS, else 8 (deeper networks).
-template <typename T, int W, int PRESET, int LAYOUT>
+template <typename T, int PRESET, int LAYOUT>
 hipError_t fwd_raw_generic(const Geo& d, const void* ffr, const float* raw, int64_t n, float* rgb,
                            hipStream_t s) {
     const size_t lds12 = (size_t)d.n_fwd_frags() * 1024 + (size_t)12 * 64 * 72 * sizeof(T);
-    const size_t lds8 = (size_t)d.n_fwd_frags() * 1024 + (size_t)8 * 64 * 72 * sizeof(T);
-    const int cus = device_cu_count();
-    if (lds12 <= 160 * 1024) return fwd_raw_launch<T, W, PRESET, LAYOUT, 12>(d, ffr, raw, n, rgb, s, cus);
-    return fwd_raw_launch<T, W, PRESET, LAYOUT, 8>(d, ffr, raw, n, rgb, s,
-                                                   cus * (int)((160 * 1024) / lds8 > 0 ? (160 * 1024) / lds8 : 1));
+    if (lds12 <= 160 * 1024) return fwd_raw_launch<T, PRESET, LAYOUT, 12>(d, ffr, raw, n, rgb, s);
+    return fwd_raw_launch<T, PRESET, LAYOUT, 8>(d, ffr, raw, n, rgb, s);
 }
 
-template <typename T, int W>
+template <typename T>
 hipError_t fwd_raw_dispatch(const Geo& d, int preset, int layout, const void* ffr, const float* raw,
                             int64_t n, float* rgb, hipStream_t s) {
-    if (W == 64 && d.H == 5) {
+    if (d.H == 5) {
         if (preset == NRC_PRESET_PAPER_GAUSS)
             return layout == NRC_RAW14 ? fwd_raw_fixed_launch<T, NRC_PRESET_PAPER_GAUSS, NRC_RAW14>(d, ffr, raw, n, rgb, s)
                                        : fwd_raw_fixed_launch<T, NRC_PRESET_PAPER_GAUSS, NRC_RAW16>(d, ffr, raw, n, rgb, s);
@@ -1387,16 +1363,16 @@ hipError_t fwd_raw_dispatch(const Geo& d, int preset, int layout, const void* ff
                                    : fwd_raw_fixed_launch<T, NRC_PRESET_CONFIG, NRC_RAW16>(d, ffr, raw, n, rgb, s);
     }
     if (preset == NRC_PRESET_PAPER_GAUSS)
-        return layout == NRC_RAW14 ? fwd_raw_generic<T, W, NRC_PRESET_PAPER_GAUSS, NRC_RAW14>(d, ffr, raw, n, rgb, s)
-                                   : fwd_raw_generic<T, W, NRC_PRESET_PAPER_GAUSS, NRC_RAW16>(d, ffr, raw, n, rgb, s);
+        return layout == NRC_RAW14 ? fwd_raw_generic<T, NRC_PRESET_PAPER_GAUSS, NRC_RAW14>(d, ffr, raw, n, rgb, s)
+                                   : fwd_raw_generic<T, NRC_PRESET_PAPER_GAUSS, NRC_RAW16>(d, ffr, raw, n, rgb, s);
     if (preset == NRC_PRESET_PAPER_TRI)
-        return layout == NRC_RAW14 ? fwd_raw_generic<T, W, NRC_PRESET_PAPER_TRI, NRC_RAW14>(d, ffr, raw, n, rgb, s)
-                                   : fwd_raw_generic<T, W, NRC_PRESET_PAPER_TRI, NRC_RAW16>(d, ffr, raw, n, rgb, s);
+        return layout == NRC_RAW14 ? fwd_raw_generic<T, NRC_PRESET_PAPER_TRI, NRC_RAW14>(d, ffr, raw, n, rgb, s)
+                                   : fwd_raw_generic<T, NRC_PRESET_PAPER_TRI, NRC_RAW16>(d, ffr, raw, n, rgb, s);
     if (preset == NRC_PRESET_PAPER)
-        return layout == NRC_RAW14 ? fwd_raw_generic<T, W, NRC_PRESET_PAPER, NRC_RAW14>(d, ffr, raw, n, rgb, s)
-                                   : fwd_raw_generic<T, W, NRC_PRESET_PAPER, NRC_RAW16>(d, ffr, raw, n, rgb, s);
-    return layout == NRC_RAW14 ? fwd_raw_generic<T, W, NRC_PRESET_CONFIG, NRC_RAW14>(d, ffr, raw, n, rgb, s)
-                               : fwd_raw_generic<T, W, NRC_PRESET_CONFIG, NRC_RAW16>(d, ffr, raw, n, rgb, s);
+        return layout == NRC_RAW14 ? fwd_raw_generic<T, NRC_PRESET_PAPER, NRC_RAW14>(d, ffr, raw, n, rgb, s)
+                                   : fwd_raw_generic<T, NRC_PRESET_PAPER, NRC_RAW16>(d, ffr, raw, n, rgb, s);
+    return layout == NRC_RAW14 ? fwd_raw_generic<T, NRC_PRESET_CONFIG, NRC_RAW14>(d, ffr, raw, n, rgb, s)
+                               : fwd_raw_generic<T, NRC_PRESET_CONFIG, NRC_RAW16>(d, ffr, raw, n, rgb, s);
 }
 
 template <typename T, bool GE, int ACT>
@@ -1455,8 +1431,8 @@ hipError_t launch_fwd_mfma_segs(int precision, const Geo& d, const void* ffr, co
 // buffers in LDS side by side.
 hipError_t launch_fwd_raw_mfma(int precision, const Geo& d, int preset, int layout, const void* ffr,
                                const float* raw, int64_t n, float* rgb, hipStream_t s) {
-    if (precision == NRC_FP16) return fwd_raw_dispatch<_Float16, 64>(d, preset, layout, ffr, raw, n, rgb, s);
-    return fwd_raw_dispatch<__bf16, 64>(d, preset, layout, ffr, raw, n, rgb, s);
+    if (precision == NRC_FP16) return fwd_raw_dispatch<_Float16>(d, preset, layout, ffr, raw, n, rgb, s);
+    return fwd_raw_dispatch<__bf16>(d, preset, layout, ffr, raw, n, rgb, s);
 }
 
 // Where the activation buffer's network outputs start: past the rows of its last

@@ -127,6 +127,9 @@ __device__ inline void reflectance_row(const float (&h)[kEncWidth], int fcol, fl
                                           : 1.0f;
 }
 
+// A compile-time integer as an argument.
+template <int N> struct IntC { static constexpr int value = N; };
+
 // ReLU as the IEEE maximum of x and +0: one v_maximum3_f32 on gfx950, where
 // fmaxf's rule for NaN operands first needs a canonicalising max.  A NaN
 // propagates instead of becoming 0; -0 becomes +0.

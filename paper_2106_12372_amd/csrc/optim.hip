@@ -84,8 +84,6 @@ __device__ inline void write_frags(const Geo& d, int p, float w, T* ffr, T* bfr,
     put_frags<T>(d, fi, bi, w, ffr, bfr, split);
 }
 
-template <int N> struct Count { static constexpr int value = N; };
-
 constexpr int kRedParams = 32;   // weights per workgroup
 constexpr int kRedGroups = 8;    // tile groups per workgroup
 
@@ -173,13 +171,13 @@ __global__ __launch_bounds__(red_threads(ADAM)) void k_reduce(const float* __res
             for (int u = 0; u < K; ++u) neumaier_add(s, c, x[u]);
         };
         int k = n_tiles / kRedGroups;
-        for (; k >= 32; k -= 32) round(Count<32>{});
-        if (k & 16) round(Count<16>{});
-        if (k & 8) round(Count<8>{});
-        if (k & 4) round(Count<4>{});
-        if (k & 2) round(Count<2>{});
-        if (k & 1) round(Count<1>{});
-        if (grp < n_tiles % kRedGroups) round(Count<1>{});
+        for (; k >= 32; k -= 32) round(IntC<32>{});
+        if (k & 16) round(IntC<16>{});
+        if (k & 8) round(IntC<8>{});
+        if (k & 4) round(IntC<4>{});
+        if (k & 2) round(IntC<2>{});
+        if (k & 1) round(IntC<1>{});
+        if (grp < n_tiles % kRedGroups) round(IntC<1>{});
     }
     if (!side) {
         s_sum[grp][pl] = s;
