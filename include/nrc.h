@@ -119,9 +119,11 @@ int64_t nrc_param_count(const nrc_config* cfg);
 size_t nrc_cache_bytes(const nrc_config* cfg);
 
 /* Bytes of device scratch one nrc_train_step / nrc_backward over n records
- * needs: two regions of per-tile weight-gradient partials (consecutive steps
- * of a cache alternate between them), loss partials and flags.  0 (with
- * NRC_EINVAL as the last error) on an invalid config or n outside [0, 2^31]. */
+ * needs: two regions of weight-gradient partials (consecutive steps of a cache
+ * alternate between them), loss partials and flags, with room for one of each
+ * per 64 records (32 for the 16-bit forms at width 128; these write far fewer
+ * partials, one for each workgroup of a launch).  0 (with NRC_EINVAL as the last
+ * error) on an invalid config or n outside [0, 2^31]. */
 size_t nrc_train_scratch_bytes(const nrc_config* cfg, int64_t n);
 
 /* Bytes per element of the encoded input at the cache precision (4 or 2). */
@@ -149,9 +151,10 @@ int nrc_get_weights(const nrc_cache* cache, float* host_w, int64_t n, void* stre
 
 /*
  * Same as nrc_set_weights with the weights in device memory (FP32, n floats):
- * enqueues the copy and the rebuild of the reduced-precision copies on
- * `stream` without synchronising.  Adam moments and step count are reset.
- * Used by the autograd wrapper, whose weights are a device tensor.
+ * enqueues one kernel on `stream` that sets the master weights and the
+ * reduced-precision copies (after a copy of the weights to the cache's device,
+ * if they are not there), without synchronising.  Adam moments and step count
+ * are reset.  Used by the autograd wrapper, whose weights are a device tensor.
  */
 int nrc_set_weights_device(nrc_cache* cache, const float* dev_w, int64_t n, void* stream);
 

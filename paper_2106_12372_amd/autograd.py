@@ -1,9 +1,9 @@
 """torch.autograd.Function over the fused HIP forward and backward kernels.
 
 The weights are an ordinary FP32 device tensor (a torch Parameter), so any
-torch optimiser can drive them; each forward and backward call uploads them
-into the cache (a device-to-device copy plus the rebuild of the FP16/BF16
-operand copies).  By default the forward pass keeps every hidden layer's
+torch optimiser can drive them; each forward and backward call installs them
+in the cache (one kernel that sets the master weights and the FP16/BF16 operand
+copies).  By default the forward pass keeps every hidden layer's
 activations in a buffer (nrc_forward_train) that the backward pass reads
 (Sec. 4, "Training the fully fused neural network"); with
 keep_activations=False the backward kernel recomputes them instead, trading

@@ -12,14 +12,13 @@
 // accumulator layout), so activations never leave VGPRs.  The weights of all
 // layers sit in LDS as per-lane float4 A fragments, one workgroup per CU.
 //
-// Training: a workgroup of 16 waves owns a tile of 64 records.  Activations
-// of every layer stay in LDS ([sample][feature], padded rows).  Each of the
-// tile's three 64 x 64 products per layer (forward, data backward, weight
-// gradient) is 16 blocks of 16 x 16, one per wave, each block 16 FP32 matrix
-// instructions over a K of 64; operands come from LDS and, for weights, from
-// the L2-resident master copy.  Each tile writes its dW partial; a separate
-// fixed-order reduction sums the partials (no atomics, so results are
-// reproducible).
+// Batches whose last round of such tiles would be mostly empty take units of 16
+// queries, one column per wave (query_units).
+//
+// Training: a workgroup owns a tile of 64 records, with four waves for the chain of
+// layers and four for the weight gradients (k_train_fp32).  Each tile writes its dW
+// partial; a separate fixed-order reduction sums the partials (no atomics, so results
+// are reproducible).
 #include "encode_impl.h"
 #include "nrc_internal.h"
 

@@ -59,12 +59,11 @@ __device__ inline void stage_frags(V* dst, const V* src, int n_frags) {
     }
 }
 
-// The whole network on 16*COLS records held as B operands (b[col][0..1] =
+// The whole network (width 64) on 16*COLS records held as B operands (b[col][0..1] =
 // encoded features, natural order); returns the output accumulators (lanes
 // 0..15 hold rows 0..3, i.e. the RGB values and a zero row).  Each layer's
 // first K chunk starts from a zero accumulator (an inline constant operand)
-// and ReLU is applied to the packed 16-bit result.  NH > 0 fixes the number
-// of hidden layers at compile time (the loop unrolls); NH = 0 reads n_hidden.
+// and ReLU is applied to the packed 16-bit result.
 template <typename T, int COLS>
 __device__ inline void mlp_tile(const typename Vec8<T>::type* sfr, typename Vec8<T>::type (&b)[COLS][2],
                                 int n_hidden, int lane, f32x4 (&o)[COLS]) {
@@ -821,7 +820,7 @@ __global__ __launch_bounds__(256) void k_fwd_small(const T* __restrict__ ffr, in
 }
 
 // ---------------------------------------------------------------------------
-// Training: forward + loss gradient + data backward + per-tile weight gradient
+// Autograd form, width 64: forward into the activation buffer; FP16 backward, small batch
 // ---------------------------------------------------------------------------
 // One 64-record tile per workgroup: 4 chain waves, and as many weight-gradient
 // waves beside them.
@@ -1435,8 +1434,8 @@ hipError_t launch_fwd_raw_mfma(int precision, const Geo& d, int preset, int layo
     return fwd_raw_dispatch<__bf16>(d, preset, layout, ffr, raw, n, rgb, s);
 }
 
-// Where the activation buffer's network outputs start: past the rows of its last
-// 64-record (width 128: 32-record) tile.
+// Where the activation buffer's network outputs start: past its rows, whole units of
+// train_tile records.
 static float* act_outputs(const Geo& d, const void* act, int64_t n) {
     const int64_t ts = train_tile(NRC_FP16, d.W), rows = (n + ts - 1) / ts * ts;
     return act ? (float*)((char*)act + rows * d.H * d.W * 2) : nullptr;

@@ -1,7 +1,6 @@
 // A training step that allocates nothing, for callers that cannot allocate
 // device memory (code under stream capture, tight serving loops).  Its scratch
-// (the per-tile weight-gradient partials, loss partials and flags of one
-// step) is a file-scope device array of a fixed size instead of a caller
+// (the weight-gradient partials, loss partials and flags of one step) is a file-scope device array of a fixed size instead of a caller
 // buffer; the step itself is the one nrc_train_step enqueues, on the same
 // kernels.
 //

@@ -120,9 +120,10 @@ ScratchLayout scratch_layout(const nrc_config& c, int64_t n) {
     return L;
 }
 
-// Bytes of the autograd form's activation buffer: h_1 .. h_H of every record of
-// every training tile at the operand precision, then the network output of each as
-// four floats (layouts: k_train_tiles for FP16/BF16, k_train_fp32).
+// Bytes of the autograd form's activation buffer: h_1 .. h_H of every record, the
+// count rounded up to whole units of train_tile, at the operand precision, then the
+// network output of each as four floats (layouts: k_train_tiles for FP16/BF16,
+// k_train_fp32).
 size_t act_layout(const nrc_config& c, int64_t n) {
     const int ts = train_tile(c.precision, c.width);
     const size_t tiles = (size_t)((n + ts - 1) / ts);
@@ -137,8 +138,8 @@ Geo kernel_geo(const nrc_config& c) {
     return d;
 }
 
-// Weight-gradient partials a step over n records writes: one per tile, or one
-// per workgroup where workgroups take several tiles.
+// Weight-gradient partials a step over n records writes: one per tile, or one for
+// each workgroup of its launches where workgroups take several tiles.
 static int64_t step_parts(const nrc_config& c, const Geo& d, int64_t n, bool upstream, const ScratchLayout& sl) {
     return !fp32_form(c.precision) && train_in_tiles(c.precision, d, n, upstream) ? train_parts(d, n) : sl.tiles;
 }

@@ -17,9 +17,11 @@ struct CacheLayout {
 // Byte offsets inside the scratch of one training step / backward pass.
 struct ScratchLayout {
     int64_t tiles;
-    // partials: two regions of per-tile weight-gradient partials; consecutive
-    // training steps of a cache alternate between them, so a step's kernel
-    // never rewrites the lines the previous step's reduction has just read
+    // partials: two regions of weight-gradient partials, with room for one per
+    // train_tile records (the FP32 trainers write one per tile, the 16-bit trainer
+    // one for each workgroup of a launch); consecutive training steps of a cache
+    // alternate between them, so a step's kernel never rewrites the lines the
+    // previous step's reduction has just read
     // (measured: that rewrite costs the training kernel ~3 us per step).
     size_t partials, partials2, loss_part, grad, flags, loss, skipped, total;
 };

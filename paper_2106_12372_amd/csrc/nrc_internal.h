@@ -27,8 +27,9 @@ __host__ __device__ inline int albedo_col(int preset) {
 __host__ __device__ inline bool fp32_form(int precision) {
     return precision == NRC_FP32 || precision == NRC_FP32_VALU;
 }
-// Training records per workgroup tile: 64, except 32 for the width-128
-// matrix-core form (its activations and deltas must fit in LDS).
+// Records per unit of the training scratch and of the activation buffer's rounding: 64,
+// except 32 for the 16-bit forms at width 128.  Every trainer's tiles are of 64 records
+// now; the sizes that callers allocate, and batches refused by them, stay as they were.
 __host__ __device__ inline int train_tile(int precision, int width) {
     return (!fp32_form(precision) && width == 128) ? 32 : 64;
 }

@@ -1,18 +1,19 @@
 // Weight-gradient reduction and the Adam update (Sec. 5 "Optimizer").
 //
 // k_reduce<ADAM>: a workgroup owns 32 consecutive weights; its 8 groups of 32
-// lanes each sum every 8th tile's partial for one weight (coalesced 128-byte
-// rows), with Neumaier compensation, and the 8 group sums are combined in a
-// fixed order, so the reduced gradient does not depend on scheduling.
+// lanes each sum every 8th partial (a tile's, or a workgroup's of the 16-bit
+// trainer) for one weight (coalesced 128-byte rows), with Neumaier compensation, and
+// the 8 group sums are combined in a fixed order, so the reduced gradient does not
+// depend on scheduling.
 // Without ADAM the gradient is written out (backward of the autograd form).
-// With ADAM the workgroup first ORs the per-tile non-finite flags the training
-// kernel wrote: if any is set the whole step is skipped (weights, moments and
+// With ADAM the workgroup ORs the non-finite flags the training kernel wrote, one per
+// partial: if any is set the whole step is skipped (weights, moments and
 // step count stay as they are); otherwise each weight's FP32 master copy and
 // Adam moments are updated and its FP16/BF16 copies in both matrix-core
 // fragment layouts are refreshed.  The step count lives in two device slots
 // used in alternation (read one, write the other), so no thread of the launch
 // reads a value another thread of the same launch writes.  Workgroup 0 also
-// reduces the per-tile loss partials.
+// reduces the tiles' loss terms.
 #include "nrc_internal.h"
 
 namespace nrc {

@@ -20,16 +20,19 @@
 // the same order as in k_train_mfma; only the grouping of the records' weight
 // gradients differs.
 //
-// Bound by LDS traffic and the barrier between layers.  Cycle stamps of a tile:
-// width 128 (FP16) 28k cycles, 1.9k per forward layer, 3.2k per backward layer
-// with its weight gradient; width 64, two workgroups per CU, 15k, 0.9k and 1.4k
-// (a backward layer reads 88 KB from LDS, 0.7k cycles at 128 bytes each).
-// The partials' one write takes 27k cycles at width 128 (76 MB over the chip, at
-// the rate of a copy).  Whole training steps, us, k_train_mfma before and now:
-// width 64 FP16 16,384 records 17.5 / 16.0, 65,536 48 / 29, 262,144 183 / 72, BF16
-// 1,000 records 18.6 / 13.9, 262,144 232 / 82; width 128 FP16 1,000 records 53 / 28,
-// 16,384 97 / 41, 65,536 306 / 73, BF16 65,536 438 / 100.  At width 128 a wave with two row blocks and two columns
-// instead of one and four was slower (83 and 134 us: its fragments spill).
+// Bound by LDS traffic and the barrier between layers.  Cycle stamps of a tile: width
+// 128 (FP16) 28k cycles, 1.9k per forward layer, 3.2k per backward layer with its
+// weight gradient; width 64, two workgroups per CU, 15k, 0.9k and 1.4k (a backward
+// layer reads 88 KB from LDS, 0.7k cycles at 128 bytes each). The partials' one write
+// takes 27k cycles at width 128 (76 MB over the chip, at the rate of a copy).  At width
+// 128 the sums alone take 148 of a wave's 256 registers and some of the rest spill:
+// BF16 steps 22 (92 bytes of scratch per lane), backward passes 10 from the buffer and
+// 19 to 21 without; FP16 steps 8, recomputing backward passes 2 to 5, from the buffer
+// none.  Whole training steps, us, k_train_mfma before and now: width 64 FP16 16,384
+// records 17.5 / 16.0, 65,536 48 / 29, 262,144 183 / 72, BF16 1,000 records 18.6 /
+// 13.9, 262,144 232 / 82; width 128 FP16 1,000 records 53 / 28, 16,384 97 / 41, 65,536
+// 306 / 73, BF16 65,536 438 / 94.  At width 128 a wave with two row blocks and two
+// columns instead of one and four was slower (83 and 134 us: its fragments spill).
 #include "mfma_ops.h"
 #include "nrc_internal.h"
 
@@ -50,7 +53,7 @@ constexpr int kLdT = 72;          // dL/dy, feature-major
 // as here (more partials, 4 us from launch to launch): FP16 width 64 262,208 records
 // 73.9 / 81.6, 524,288 132 / 141, 1,048,576 252 / 279; width 128 262,144 208 / 232.
 // Starting the sums anew inside the kernel took 75.2, 139, 272 and 223, but spills more
-// registers at width 128 (BF16 65,536 records 93.9 / 96.4).
+// registers at width 128 (BF16 steps of 65,536 records 93.9 -> 96.4).
 constexpr int kHeld = 8;
 
 // Where a wave has 256 registers at width 64 (ROOMY), the LDS rows of h_0 .. h_H and
